@@ -236,7 +236,7 @@ def main():
     us1 = time_batches(lambda s: pa.prefill(pat_1, c_1, i_1, q1, k1, v1, o=o1, lse=l1), 20, 10)
     configs.append({"configuration": "1", "sink_blocks": 1, "shape": "b1, 2 heads, N=1024, D=64, block 64, W=2, fp32",
                     "attended_block_pairs": int(c_1.sum().item()), "kernel_us": stats(us1),
-                    "note": "fp32 FMA kernel, 1.6e8 flop: bound by launch latency, time only"})
+                    "note": "fp32 matrix kernel, 1.6e8 flop: bound by latency, time only"})
 
     # ---------------- decode as it runs in generation: step after step, each on another cache so that every
     # read is cold.  (Inside the step above the decode launch follows a 3 ms prefill and an event record; that

@@ -1,15 +1,27 @@
-// fp32 prefill (Equation 1 over the listed key blocks) with plain FMA arithmetic.
-// This is the full-precision path: fp32 inputs, fp32 products and sums.
+// fp32 prefill (Equation 1 over the listed key blocks): fp32 inputs, fp32 products and sums, on the fp32 matrix
+// instruction v_mfma_f32_16x16x4_f32 (its products and sums are those of an fp32 fused multiply-add).
 //
-// One workgroup owns KT consecutive query rows of one head (KT = min(B, 64)):
-// four lanes share a row, each holding an interleaved quarter of the head
-// dimension.  Key/value tiles of KT tokens are staged in LDS; for each tile the
-// four lanes form partial dot products, add them with two lane exchanges, take
-// the tile's row maximum, and accumulate exp2-weighted values (online softmax).
+// Decomposition.  A workgroup owns MQ tiles of 16 query rows of one head; its NW wavefronts share the KEYS: each walks
+// a contiguous part of the row's 16-key tiles for all of the workgroup's queries with an online softmax of its own,
+// and the (max, sum, O) of the wavefronts meet in LDS once, at the end.  No tile is staged in LDS and there is no
+// barrier in the loop: a wavefront loads its K and V rows straight into operand registers, each used by MQ tiles.
+//
+// In the transposed form S^T = K Q^T (A = K rows, B = Q^T) a lane owns one query column, and its four scores of a
+// 16-key tile are the keys 4*(lane/16) + r, which is what O^T += V^T P^T takes as its B operand when step r contracts
+// over the keys 4*(lane/16) + r, lane/16 = 0..3.  The contraction index of S^T is permuted so that one 16-byte load
+// of a K row feeds four steps, and the rows of O^T so that one 16-byte load of a V row feeds four tiles of it.
+//
+// Bound by the fp32 matrix rate (153 TFLOP/s in a large matrix product on the same card): 84 TFLOP/s at 8 heads,
+// head_dim 64, N = 8192, blocks of 64 keys, 79 at head_dim 128; a kernel of plain multiply-adds with K/V staged in LDS,
+// which this replaced, 4.  Short prompts are bound by latency (2 heads, N = 1024: 74 us before, 10.7 now).
+//
+// Loads run LA tiles ahead of the products (the K tiles of a step of TS tiles, then its V tiles, then the next step's).
 #include <math.h>
 #include "common.h"
 
 namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct f32_params {
   const float* q; const float* k; const float* v; float* o; float* lse;
@@ -19,113 +31,282 @@ struct f32_params {
   float c2;   // softmax scale * log2(e)
 };
 
-template <int D, int KT>
-__global__ __launch_bounds__(4 * KT) void pa_prefill_f32_kernel(f32_params p) {
-  constexpr int DQ = D / 4;        // floats of the head dimension per lane
-  constexpr int NCH = DQ / 4;      // float4 chunks per lane; chunk m covers d = 16m + 4c .. +3
-  __shared__ float4 Ks[KT * D / 4];
-  __shared__ float4 Vs[KT * D / 4];
+constexpr int NW = 4;              // wavefronts per workgroup (eight share the compute unit's matrix cores no better and
+                                   // have twice the partials to merge: 10-40 % slower at every size measured)
+constexpr float RAISE_BY = 8.0f;   // the exponentials' reference point is raised when exceeded by 2^8: any reference
+                                   // gives the same result, and raising it costs a multiplication of all of O
 
-  const int tiles_per_block = p.B / KT;
-  const int qb = blockIdx.x / tiles_per_block;
-  const int qt = blockIdx.x % tiles_per_block;
+constexpr int o_stride(int D) { return D + 4; }   // floats per query row of a wavefront's partial output in LDS
+template <int D, int MQ>
+constexpr size_t merge_lds() { return sizeof(float) * NW * 16 * MQ * (o_stride(D) + 2); }
+
+template <int D, int MQ>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void pa_prefill_f32_kernel(f32_params p) {
+  constexpr int NK = D / 16;                // 16-byte pieces of a K row per lane; each feeds four steps
+  constexpr int NV = D / 64;                // 16-byte pieces of a V row per lane; each feeds four tiles of O^T
+  constexpr int QR = 16 * MQ;               // query rows of the workgroup
+  constexpr int TS = MQ * D <= 128 ? 4 : 2; // 16-key tiles per step (scores held at a time)
+  constexpr int LA = MQ * D <= 64 ? 4 : MQ * D <= 128 ? 2 : 1;   // tiles loaded ahead
+  extern __shared__ __attribute__((aligned(16))) float s_o[];   // [NW][QR][D + 4], then the maxima and sums [NW][QR]
+  float* s_m = s_o + NW * QR * o_stride(D);
+  float* s_l = s_m + NW * QR;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 15, kg = lane >> 4;
+  const int per_block = p.B / QR;
+  const int qb = p.nb - 1 - (int)blockIdx.x / per_block;       // longest rows first
+  const int q_in_blk = ((int)blockIdx.x % per_block) * QR;
   const int h = blockIdx.y, b = blockIdx.z;
   const int kvh = h / (p.hq / p.hkv);
-  const int r = threadIdx.x >> 2, c = threadIdx.x & 3;
-  const int64_t qrow = (int64_t)qb * p.B + (int64_t)qt * KT + r;
-  const bool row_ok = qrow < p.N;
+  const int64_t q0 = (int64_t)qb * p.B + q_in_blk;
+  if (q0 >= p.N) return;                                       // uniform over the workgroup
 
-  const float4* q4 = reinterpret_cast<const float4*>(p.q + (((int64_t)b * p.hq + h) * p.N + (row_ok ? qrow : 0)) * D);
-  const float4* kbase = reinterpret_cast<const float4*>(p.k + ((int64_t)b * p.hkv + kvh) * p.N * D);
-  const float4* vbase = reinterpret_cast<const float4*>(p.v + ((int64_t)b * p.hkv + kvh) * p.N * D);
+  const float* qbase = p.q + ((int64_t)b * p.hq + h) * p.N * D;
+  const float* kbase = p.k + ((int64_t)b * p.hkv + kvh) * p.N * D;
+  const float* vbase = p.v + ((int64_t)b * p.hkv + kvh) * p.N * D;
 
-  float4 qreg[NCH];
+  // ---- the row's list, 64 entries at a time: lane e keeps entry list_base + e ----
+  const int32_t* list = p.kv_idx + (int64_t)qb * p.max_k;
+  auto list_lanes = [&](int base) -> int {
+    if (p.dense) return base + lane;
+    const int e = base + lane;
+    return list[e < p.max_k ? e : p.max_k - 1];
+  };
+  int row_e = list_lanes(0);                                   // requested beside the count, not after it
+  int n_list = qb + 1;
+  if (!p.dense) {
+    n_list = p.kv_cnt[qb];
+    if (n_list > p.max_k) n_list = p.max_k;
+  }
+  f32x4 qf[MQ][NK];
 #pragma unroll
-  for (int m = 0; m < NCH; ++m) qreg[m] = row_ok ? q4[4 * m + c] : make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 acc[NCH];
+  for (int m = 0; m < MQ; ++m) {
+    const int64_t row = q0 + 16 * m + ln;
 #pragma unroll
-  for (int m = 0; m < NCH; ++m) acc[m] = make_float4(0.f, 0.f, 0.f, 0.f);
-  float m_run = -INFINITY, l_run = 0.f;
+    for (int c = 0; c < NK; ++c)
+      qf[m][c] = row < p.N ? *reinterpret_cast<const f32x4*>(qbase + row * D + 16 * c + 4 * kg) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  n_list = __builtin_amdgcn_readfirstlane(n_list);
 
-  int n_list = p.dense ? qb + 1 : p.kv_cnt[qb];
-  if (!p.dense && n_list > p.max_k) n_list = p.max_k;
-
-  for (int t = 0; t < n_list; ++t) {
-    int j = p.dense ? t : p.kv_idx[(int64_t)qb * p.max_k + t];
-    if (j < 0 || j > qb) continue;                     // uniform over the workgroup
-    const int n_kt = (j == qb) ? qt + 1 : tiles_per_block;   // key tiles past the query tile are fully masked
-    for (int kt = 0; kt < n_kt; ++kt) {
-      const int64_t key0 = (int64_t)j * p.B + (int64_t)kt * KT;
-      __syncthreads();
-      for (int e = threadIdx.x; e < KT * D / 4; e += 4 * KT) {
-        int64_t krow = key0 + e / (D / 4);
-        bool ok = krow < p.N;
-        Ks[e] = ok ? kbase[key0 * (D / 4) + e] : make_float4(0.f, 0.f, 0.f, 0.f);
-        Vs[e] = ok ? vbase[key0 * (D / 4) + e] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      __syncthreads();
-
-      float s[KT];
-#pragma unroll
-      for (int jj = 0; jj < KT; ++jj) {
-        float part = 0.f;
-#pragma unroll
-        for (int m = 0; m < NCH; ++m) {
-          float4 kk = Ks[jj * (D / 4) + 4 * m + c];
-          part = fmaf(qreg[m].x, kk.x, part);
-          part = fmaf(qreg[m].y, kk.y, part);
-          part = fmaf(qreg[m].z, kk.z, part);
-          part = fmaf(qreg[m].w, kk.w, part);
-        }
-        part += __shfl_xor(part, 1);
-        part += __shfl_xor(part, 2);
-        s[jj] = part * p.c2;
-      }
-      if (j == qb && kt == qt) {     // diagonal tile: token-level causality
-#pragma unroll
-        for (int jj = 0; jj < KT; ++jj) if (jj > r) s[jj] = -INFINITY;
-      }
-      float tmax = s[0];
-#pragma unroll
-      for (int jj = 1; jj < KT; ++jj) tmax = fmaxf(tmax, s[jj]);
-      const float m_new = fmaxf(m_run, tmax);          // finite: key 0 of the first tile is always visible
-      const float alpha = exp2f(m_run - m_new);
-      l_run *= alpha;
-#pragma unroll
-      for (int m = 0; m < NCH; ++m) { acc[m].x *= alpha; acc[m].y *= alpha; acc[m].z *= alpha; acc[m].w *= alpha; }
-#pragma unroll
-      for (int jj = 0; jj < KT; ++jj) {
-        const float pj = exp2f(s[jj] - m_new);
-        l_run += pj;
-#pragma unroll
-        for (int m = 0; m < NCH; ++m) {
-          float4 vv = Vs[jj * (D / 4) + 4 * m + c];
-          acc[m].x = fmaf(pj, vv.x, acc[m].x);
-          acc[m].y = fmaf(pj, vv.y, acc[m].y);
-          acc[m].z = fmaf(pj, vv.z, acc[m].z);
-          acc[m].w = fmaf(pj, vv.w, acc[m].w);
-        }
-      }
-      m_run = m_new;
+  // ---- this wavefront's 16-key tiles: tile tau is piece tau % tpb of list entry tau / tpb ----
+  const int tpb = p.B / 16;
+  const int diag_tiles = q_in_blk / 16 + MQ;                   // tiles of the diagonal block that any query reaches
+  int64_t tiles = (int64_t)n_list * tpb;
+  int last_row = row_e;
+  if (n_list > 64) last_row = list_lanes((n_list - 1) & ~63);
+  if (n_list > 0 && __builtin_amdgcn_readlane(last_row, (n_list - 1) & 63) == qb) tiles -= tpb - diag_tiles;
+  const int64_t lo = tiles * wave / NW, hi = tiles * (wave + 1) / NW;
+  const int n_steps = (int)((hi - lo + TS - 1) / TS);
+  int ct = (int)(lo / tpb), cs = (int)(lo % tpb);              // cursor of the loads: list entry, piece
+  int left = (int)(hi - lo);
+  if (ct >= 64) row_e = list_lanes(ct & ~63);
+  const int last = (int)(p.N - 1);
+  auto next_key0 = [&]() -> int {                              // first key of the next tile, or -1: nothing to attend
+    const int j = __builtin_amdgcn_readlane(row_e, ct & 63);
+    const bool some = left > 0 && j >= 0 && (j < qb || (j == qb && cs < diag_tiles));
+    int key0 = some ? j * p.B + 16 * cs : -1;
+    if (key0 > last) key0 = -1;                                // (later query tiles of a last block that is not full)
+    --left;
+    if (++cs == tpb) {
+      cs = 0;
+      if ((++ct & 63) == 0) row_e = list_lanes(ct);
     }
+    return key0;
+  };
+
+  f32x4 kf[TS][NK], vf[TS][4][NV];
+  // A tile's address is scalar, a lane adds its row and piece; rows beyond the sequence repeat its last one (masked).
+  // "No tile" reads the start of the slab and its products are left out, so that nothing unattended reaches the sums.
+  auto load_k = [&](int i, int key0) {
+    const int k0 = key0 < 0 ? 0 : key0, lim = last - k0;
+    const float* src = kbase + (int64_t)k0 * D;
+    const uint32_t off = (uint32_t)(ln < lim ? ln : lim) * D + 4 * kg;
+#pragma unroll
+    for (int c = 0; c < NK; ++c) kf[i][c] = *reinterpret_cast<const f32x4*>(src + off + 16 * c);
+  };
+  auto load_v = [&](int i, int key0) {
+    const int k0 = key0 < 0 ? 0 : key0, lim = last - k0;
+    const float* src = vbase + (int64_t)k0 * D;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * kg + r;
+      const uint32_t off = (uint32_t)(row < lim ? row : lim) * D + 4 * ln;
+#pragma unroll
+      for (int x = 0; x < NV; ++x) vf[i][r][x] = *reinterpret_cast<const f32x4*>(src + off + 64 * x);
+    }
+  };
+
+  f32x4 O[MQ][4 * NV];
+  float m_run[MQ], l_run[MQ];
+#pragma unroll
+  for (int m = 0; m < MQ; ++m) {
+    m_run[m] = -INFINITY; l_run[m] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4 * NV; ++j) O[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  if (row_ok) {
-    const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;    // a row whose list is empty: o = 0, lse = -inf
-    float4* o4 = reinterpret_cast<float4*>(p.o + (((int64_t)b * p.hq + h) * p.N + qrow) * D);
+  int key0[TS], nkey0[TS];
 #pragma unroll
-    for (int m = 0; m < NCH; ++m)
-      o4[4 * m + c] = make_float4(acc[m].x * inv, acc[m].y * inv, acc[m].z * inv, acc[m].w * inv);
-    if (p.lse && c == 0)
-      p.lse[((int64_t)b * p.hq + h) * p.N + qrow] = (m_run + log2f(l_run)) * 0.69314718055994530942f;
+  for (int i = 0; i < TS; ++i) key0[i] = next_key0();
+#pragma unroll
+  for (int i = 0; i < LA; ++i) load_k(i, key0[i]);
+
+  for (int s = 0; s < n_steps; ++s) {
+#pragma unroll
+    for (int i = 0; i < TS; ++i) nkey0[i] = next_key0();
+    auto load_ahead = [&](int at) {                            // number at + LA of: the step's K tiles, its V tiles, the next K tiles
+      const int x = at + LA;
+      if (x < TS) load_k(x, key0[x % TS]);
+      else if (x < 2 * TS) load_v(x % TS, key0[x % TS]);
+      else load_k(x % TS, nkey0[x % TS]);
+    };
+    // ---- S^T = K Q^T ----
+    f32x4 S[MQ][TS];
+#pragma unroll
+    for (int i = 0; i < TS; ++i) {
+      load_ahead(i);
+      __builtin_amdgcn_sched_barrier(0);
+      if (key0[i] < 0) {
+#pragma unroll
+        for (int m = 0; m < MQ; ++m) S[m][i] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      } else {
+#pragma unroll
+        for (int m = 0; m < MQ; ++m) S[m][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NK; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int m = 0; m < MQ; ++m)
+              S[m][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][c][e], qf[m][c][e], S[m][i], 0, 0, 0);
+        if ((int64_t)key0[i] + 15 > q0) {                      // causality: a tile that reaches the workgroup's queries
+#pragma unroll
+          for (int m = 0; m < MQ; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if ((int64_t)key0[i] + 4 * kg + r > q0 + 16 * m + ln) S[m][i][r] = -INFINITY;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // ---- online softmax ----
+#pragma unroll
+    for (int m = 0; m < MQ; ++m) {
+      float mx = S[m][0][0];
+#pragma unroll
+      for (int x = 1; x < 4 * TS; ++x) mx = fmaxf(mx, S[m][x >> 2][x & 3]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * p.c2;
+      const bool raise = mx > m_run[m] + RAISE_BY;             // (a first score raises -inf)
+      if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+        const float m_new = raise ? mx : m_run[m];
+        const float alpha = raise ? __builtin_amdgcn_exp2f(m_run[m] - m_new) : 1.f;
+        m_run[m] = m_new;
+        l_run[m] *= alpha;
+#pragma unroll
+        for (int j = 0; j < 4 * NV; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) O[m][j][r] *= alpha;
+      }
+      const float ref = m_run[m] == -INFINITY ? 0.f : m_run[m];   // nothing attended yet: every exponential is 0
+      float sum = 0.f;
+#pragma unroll
+      for (int x = 0; x < 4 * TS; ++x) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(S[m][x >> 2][x & 3], p.c2, -ref));
+        S[m][x >> 2][x & 3] = pe;
+        sum += pe;
+      }
+      l_run[m] += sum;
+    }
+    // ---- O^T += V^T P^T: row R of tile 4x+j is d = 64x + 4R + j ----
+#pragma unroll
+    for (int i = 0; i < TS; ++i) {
+      load_ahead(TS + i);
+      __builtin_amdgcn_sched_barrier(0);
+      if (key0[i] >= 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int x = 0; x < NV; ++x)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int m = 0; m < MQ; ++m)
+                O[m][4 * x + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][x][j], S[m][i][r], O[m][4 * x + j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < TS; ++i) key0[i] = nkey0[i];
+  }
+
+  // ---- the wavefronts' partials meet in LDS ----
+#pragma unroll
+  for (int m = 0; m < MQ; ++m) {
+    const int row = wave * QR + 16 * m + ln;
+    float l = l_run[m] + __shfl_xor(l_run[m], 16);
+    l += __shfl_xor(l, 32);
+    if (kg == 0) { s_m[row] = m_run[m]; s_l[row] = l; }
+#pragma unroll
+    for (int x = 0; x < NV; ++x)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(s_o + row * o_stride(D) + 64 * x + 16 * kg + 4 * r) =
+            f32x4{O[m][4 * x][r], O[m][4 * x + 1][r], O[m][4 * x + 2][r], O[m][4 * x + 3][r]};
+  }
+  __syncthreads();
+  for (int e = tid; e < QR * (D / 4); e += 64 * NW) {
+    const int row = e / (D / 4), d4 = e % (D / 4);
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w * QR + row]);
+    float L = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float lw = s_l[w * QR + row];
+      const float wt = lw > 0.f ? __builtin_amdgcn_exp2f(s_m[w * QR + row] - M) : 0.f;
+      L = fmaf(wt, lw, L);
+      const f32x4 ow = *reinterpret_cast<const f32x4*>(s_o + (w * QR + row) * o_stride(D) + 4 * d4);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x] = fmaf(wt, ow[x], acc[x]);
+    }
+    const int64_t tok = q0 + row;
+    if (tok >= p.N) continue;
+    const float inv = L > 0.f ? 1.0f / L : 0.f;                // a row whose list is empty: o = 0, lse = -inf
+    const int64_t at = ((int64_t)b * p.hq + h) * p.N + tok;
+    *reinterpret_cast<f32x4*>(p.o + at * D + 4 * d4) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+    if (p.lse && d4 == 0) p.lse[at] = (M + log2f(L)) * 0.69314718055994530942f;
   }
 }
 
-template <int D, int KT>
+template <int D, int MQ>
 int launch(const f32_params& p, int32_t batch, hipStream_t stream) {
-  dim3 grid((uint32_t)p.nb * (uint32_t)(p.B / KT), (uint32_t)p.hq, (uint32_t)batch);
-  hipLaunchKernelGGL((pa_prefill_f32_kernel<D, KT>), grid, dim3(4 * KT), 0, stream, p);
+  constexpr size_t lds = merge_lds<D, MQ>();
+  static std::atomic<unsigned long long> done{0};
+  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_prefill_f32_kernel<D, MQ>), lds, done)) return st;
+  dim3 grid((uint32_t)p.nb * (uint32_t)(p.B / (16 * MQ)), (uint32_t)p.hq, (uint32_t)batch);
+  hipLaunchKernelGGL((pa_prefill_f32_kernel<D, MQ>), grid, dim3(64 * NW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
+}
+
+// Query tiles per workgroup.  A K/V row loaded once serves MQ tiles, so larger is better (8 heads, head_dim 64,
+// N = 8192: 59 / 70 / 84 TFLOP/s at 1 / 2 / 4) as long as every compute unit gets a workgroup: at 8 heads and N = 1024
+// 1 / 2 / 4 tiles (512 / 256 / 128 workgroups) take 19.8 / 16.3 / 26.1 us, at 2 heads 11.6 / 15.1 / 25.4.
+// At most 64 queries at head_dim 64 and 32 at 128, which is what the 256 registers of a wavefront hold.
+template <int D>
+int launch_d(const f32_params& p, int32_t batch, hipStream_t stream) {
+  constexpr int MQ_MAX = 256 / D;
+  int n_cu = 1;
+  pa_current_device(nullptr, &n_cu);
+  const int64_t tiles = (int64_t)p.nb * (p.B / 16) * p.hq * batch;
+  int mq = 1;
+  while (mq < MQ_MAX && p.B % (32 * mq) == 0 && tiles / (2 * mq) >= n_cu) mq *= 2;
+  if constexpr (MQ_MAX == 4)
+    if (mq == 4) return launch<D, 4>(p, batch, stream);
+  return mq == 2 ? launch<D, 2>(p, batch, stream) : launch<D, 1>(p, batch, stream);
 }
 
 }  // namespace
@@ -138,14 +319,6 @@ int pa_launch_prefill_f32(const pa_prefill_args& a) {
   p.N = a.seq_len;
   p.c2 = a.scale * 1.44269504088896340736f;
   if (a.hq > 65535 || a.batch > 65535) return POWATTN_UNSUPPORTED;
-  const int B = a.pat.block;
-  const int kt = (B % 64 == 0) ? 64 : (B % 32 == 0 ? 32 : 16);
-  if (a.head_dim == 64) {
-    if (kt == 64) return launch<64, 64>(p, a.batch, a.stream);
-    if (kt == 32) return launch<64, 32>(p, a.batch, a.stream);
-    return launch<64, 16>(p, a.batch, a.stream);
-  }
-  if (kt == 64) return launch<128, 64>(p, a.batch, a.stream);
-  if (kt == 32) return launch<128, 32>(p, a.batch, a.stream);
-  return launch<128, 16>(p, a.batch, a.stream);
+  if (a.seq_len > 0x7fffffffLL - 1024) return POWATTN_UNSUPPORTED;   // key positions are kept in 32 bits
+  return a.head_dim == 64 ? launch_d<64>(p, a.batch, a.stream) : launch_d<128>(p, a.batch, a.stream);
 }

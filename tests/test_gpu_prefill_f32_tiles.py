@@ -1,0 +1,50 @@
+"""fp32 prefill at the edges of its decomposition: query tiles of 16, 32 and 64 rows per workgroup, key tiles shared by
+four wavefronts (fewer tiles than wavefronts, counts that do not divide), block sizes that are odd multiples of 16,
+list rows beyond 64 entries, sequences that end inside a 16-key tile.  Bars: the task's 1e-5 (outputs) and 1e-3 (lse)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_03588_amd import binding as pa
+from gpu_util import check_prefill
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # hq, hkv, n, d, block, window, sink, flags
+    (1, 1, 1, 64, 64, 1, 0, pa.POWER),           # one row, one key
+    (1, 1, 17, 128, 16, 1, 0, pa.POWER),         # two query tiles, fewer key tiles than wavefronts
+    (2, 1, 333, 64, 48, 2, 1, pa.POWER),         # block of three key tiles
+    (2, 2, 401, 128, 80, 1, 1, pa.POWER),        # five
+    (16, 2, 1041, 64, 64, 3, 1, pa.POWER),       # 64 queries per workgroup, ragged end
+    (16, 4, 530, 128, 32, 2, 1, pa.POWER),       # 32 queries per workgroup
+    (9, 3, 499, 64, 32, 2, 0, pa.POWER),         # 32 queries of a possible 64
+    (2, 1, 1100, 64, 16, 1, 0, pa.DENSE),        # implicit rows of up to 69 entries
+    (1, 1, 1100, 128, 16, 69, 1, pa.POWER),      # listed rows of up to 69 entries
+]
+
+
+@pytest.mark.parametrize("hq,hkv,n,d,block,window,sink,flags", CASES)
+def test_prefill_f32_tiles(hq, hkv, n, d, block, window, sink, flags):
+    check_prefill(pa.Pattern(block, window, sink, flags), 1, hq, hkv, n, d, "f32", 300 + n)
+
+
+def test_prefill_f32_list_order_and_empty_row():
+    """A caller's own list: the diagonal block first, entries to be passed over, and a row without any key."""
+    pat = pa.Pattern(32, 1, 0)
+    n, d = 96, 64
+    q, k, v = (torch.randn((1, 1, n, d), generator=torch.Generator().manual_seed(7 + x)) for x in range(3))
+    cnt = torch.tensor([2, 0, 3], dtype=torch.int32, device="cuda")
+    idx = torch.tensor([[0, 1, -1], [0, 1, -1], [2, -1, 0]], dtype=torch.int32, device="cuda")
+    o, lse = pa.prefill(pat, cnt, idx, q.cuda(), k.cuda(), v.cuda())
+    o, lse = o.cpu().double()[0, 0], lse.cpu().double()[0, 0]
+    s = (q.double() @ k.double().transpose(2, 3))[0, 0] / d ** 0.5
+    t = torch.arange(n)
+    blk = t // 32
+    keep = (t[:, None] >= t[None]) & torch.tensor([[True, False, False], [False] * 3, [True, False, True]])[blk][:, blk]
+    s = s.masked_fill(~keep, -float("inf"))
+    rows = blk != 1
+    ref = torch.softmax(s[rows], -1) @ v.double()[0, 0]
+    assert float((o[rows] - ref).abs().max()) <= 1e-5
+    assert float((lse[rows] - torch.logsumexp(s[rows], -1)).abs().max()) <= 1e-3
+    assert float(o[~rows].abs().max()) == 0.0 and bool(torch.isneginf(lse[~rows]).all())
