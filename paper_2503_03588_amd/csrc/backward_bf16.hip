@@ -10,15 +10,15 @@
 //           lane = one query.  S^T = K Q^T and dP^T = V dO^T share the K/V tiles in LDS; dQ^T += K^T dS^T.
 //           It also forms Delta = rowsum(dO * O) of its rows (dO is in its registers anyway) and leaves it, with
 //           the log-sum-exp in base-2 units, in the workspace for the kernel below.
-//   dkv   : a workgroup per (batch, KV head, key block) walks the COLUMN of the block mask: the query blocks
-//           j .. j+W-1 and j + 2^k (closed form), all of them for a sink block; wavefront = 32 keys, lane = one key.
-//           Q and dO tiles of 64 queries go through LDS; dV^T += dO^T P, dK^T += Q^T dS.  A sink block's column is
+//   dkv   : a workgroup per (batch, KV head, slab of 64 or 128 keys of a block) walks the COLUMN of the block mask: the
+//           query blocks j .. j+W-1 and j + 2^k (closed form), all of them for a sink block; lane = one key.
+//           Q and dO tiles go through LDS; dV^T += dO^T P, dK^T += Q^T dS.  A sink block's column is
 //           as long as the sequence: it is cut into parts that add into an fp32 buffer, converted at the end.
-//           At 128 keys per block the two halves of this work sit on different wavefronts (dkv_split below).
+//           The two halves of this work sit on different wavefronts.
 // Both products of a pair reuse the forward kernel's operand trick: in the transposed form the accumulator layout
 // of the first product is the B-operand layout of the second (the permutation of the contraction index inside a
 // 16-step is applied to both operands).  Tiles use the forward kernel's LDS layout (chunk-major kilobytes, padded),
-// copied asynchronously global -> LDS, two stages, one barrier per tile.  Not yet scheduled by hand.
+// copied asynchronously global -> LDS, one barrier per tile.
 #include <math.h>
 #include <type_traits>
 #include "common.h"
@@ -37,20 +37,20 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
 constexpr int KT = 64;            // rows per staged tile
 constexpr int TILE_CAP = 2048;    // tiles per query block in the dq kernel
-constexpr int PART = 16;          // query blocks per part of a sink block's column
+constexpr int PART = 16;          // query blocks per part of a sink block's column, at most
 constexpr int PFD = 2;            // matrix instructions per group of LDS fragment reads
-constexpr int NSTG = 2;           // LDS stages of the tile stream: copies run NSTG-1 tiles ahead of the products (3 was
-                                  // slower: the extra LDS halves the workgroups per compute unit at block 64)
 constexpr float LOG2E = 1.44269504088896340736f;
 constexpr int dq_stages(int) { return 2; }   // LDS stages of the dQ kernel's tile stream (see there)
 
 struct bwd_params {
   const __bf16* q; const __bf16* k; const __bf16* v; const __bf16* o; const __bf16* dout; const float* lse;
   __bf16* dq; __bf16* dk; __bf16* dv;
-  float* delta;          // [batch, hq, N]
+  float* delta;          // [batch, hq, N]: -Delta
   float* lse2;           // [batch, hq, N]: the log-sum-exp in base-2 units (lse * log2 e)
   float* dk_sink;        // [batch, hkv, sink_rows, D] fp32 sums of the sink blocks' parts
   float* dv_sink;
@@ -58,6 +58,7 @@ struct bwd_params {
   int32_t max_k, nb, B, W, S; uint32_t flags;
   int32_t hq, hkv, G, subs, tasks, chunks;
   int32_t sink_blocks;   // min(S, nb) (0 when the column of no block is cut)
+  int32_t part;          // query blocks per part of a sink block's column
   int32_t max_parts;     // parts of the longest column
   int64_t N;
   float scale, c2;
@@ -189,7 +190,7 @@ __device__ __forceinline__ void pipelined_mfma(LoadF load, MmaF mma) {
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < GRP; ++j) mma(g * GRP + j, fr[g * GRP + j]);
+    for (int j = GRP - 1; j >= 0; --j) mma(g * GRP + j, fr[g * GRP + j]);   // the last one first: LDS answers in order, so its wait covers the group
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -297,10 +298,14 @@ void pa_bwd_dq_kernel(bwd_params p) {
     if (ok) {
       dl = part;
       lse2 = p.lse[qrow] * LOG2E;
-      if (hh == 0) { p.delta[qrow] = dl; p.lse2[qrow] = lse2; }
+      if (hh == 0) { p.delta[qrow] = -dl; p.lse2[qrow] = lse2; }
     }
   }
   const int tok32 = (int)tok, n32 = (int)p.N;                    // positions fit 32 bits (checked by the host)
+  // the sums of dP start at -Delta (every element of a lane belongs to its one query): no subtraction per element
+  f32x16 minus_delta;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) minus_delta[r] = -dl;
 
   f32x16 acc[ND];
 #pragma unroll
@@ -322,16 +327,16 @@ void pa_bwd_dq_kernel(bwd_params p) {
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { S[rt][r] = 0.f; dP[rt][r] = 0.f; }
+      for (int r = 0; r < 16; ++r) S[rt][r] = 0.f;
     // instruction m: d-step c = m/4, key half rt = (m/2)%2, S (K tile) or dP (V tile) = m%2: four independent chains
     pipelined_mfma<4 * NC, PFD>(
         [&](int m) { return row_frag<D>((m & 1) ? vt : kt, m >> 2, (m >> 1) & 1, lane); },
         [&](int m, bf16x8 a) {
           const int c = m >> 2, rt = (m >> 1) & 1;
-          if (m & 1) dP[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dof[c], dP[rt], 0, 0, 0);
+          if (m & 1) dP[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dof[c], c == 0 ? minus_delta : dP[rt], 0, 0, 0);
           else S[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[c], S[rt], 0, 0, 0);
         });
-    // dS^T = P^T * (dP^T - Delta), packed to bf16 in the B-operand order of the next product
+    // dS^T = P^T * (dP^T - Delta), the difference formed by the sums above, packed to bf16 in the B-operand order of the next product
     u32x4 ds[4];
     // Only tiles that reach the diagonal or the end of the sequence need the mask (wavefront-uniform test); the
     // others skip the compares and selects.  Idle lanes (query beyond the sequence) carry lse = inf: P = 0.
@@ -345,7 +350,7 @@ void pa_bwd_dq_kernel(bwd_params p) {
           for (int e = 0; e < 2; ++e) {
             // computed for every element and selected afterwards: a conditional exponential becomes a branch
             const float pr = __builtin_amdgcn_exp2f(fmaf(S[rt][r + e], p.c2, -lse2));
-            x[e] = pr * (dP[rt][r + e] - dl);
+            x[e] = pr * dP[rt][r + e];
             if (decltype(masked)::value) {
               const int key = key0 + 32 * rt + acc_row(r + e, hh);
               x[e] = (key <= tok32 && key < n32) ? x[e] : 0.f;
@@ -382,219 +387,52 @@ void pa_bwd_dq_kernel(bwd_params p) {
 // ---------------------------------------------------------------------------------------------------------------
 // dK, dV
 // ---------------------------------------------------------------------------------------------------------------
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) void pa_bwd_dkv_kernel(bwd_params p) {
-  using G = tile_geo<D>;
-  constexpr int NC = G::NC, ND = G::ND;
-  constexpr int STAGEB = 2 * G::TILEB + 512;     // Q tile, dO tile, 64 log-sum-exps, 64 Deltas
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ln = lane & 31, hh = lane >> 5;
-  const int kvh = blockIdx.y, b = blockIdx.z;
-
-  // ---- which key block, which part of its column ----
-  int j, part;
-  // the parts of the sink blocks' columns come first in the launch: they are the longest workgroups (PART query
-  // blocks each against a dozen for an ordinary column), and the last ones to start should be the shortest
-  const int n_extra = p.sink_blocks * (p.max_parts - 1);
-  if ((int)blockIdx.x >= n_extra) { j = (int)blockIdx.x - n_extra; part = 0; }
-  else {
-    const int e = (int)blockIdx.x;
-    j = e / (p.max_parts - 1);
-    part = 1 + e % (p.max_parts - 1);
-  }
-  const bool whole_column = j < p.sink_blocks;                    // a sink block: every later query block
-  const int parts = whole_column ? (p.nb - j + PART - 1) / PART : 1;
-  if (part >= parts) return;                                      // uniform over the workgroup
-  // entries of the column: query blocks j .. j+n_win-1, then j + 2^k for 2^k >= the window
-  const int weff = (p.flags & POWATTN_POWER) ? (p.W > 1 ? p.W : 1) : p.W;
-  int n_win, n_ent, first_pow = 1;
-  if (whole_column) {
-    n_win = p.nb - j - part * PART;
-    if (n_win > PART) n_win = PART;
-    n_ent = n_win;
-  } else {
-    n_win = weff < p.nb - j ? weff : p.nb - j;
-    n_ent = n_win;
-    if (p.flags & POWATTN_POWER) {
-      while (first_pow < weff) first_pow <<= 1;
-      for (int64_t pw = first_pow; j + pw < p.nb; pw <<= 1) ++n_ent;
-    }
-  }
-  auto entry = [&](int e) -> int {
-    if (whole_column) return j + part * PART + e;
-    if (e < n_win) return j + e;
-    return j + (first_pow << (e - n_win));
-  };
-
-  // ---- this lane's key: its K and V rows stay in registers as B operands ----
-  const int64_t key = (int64_t)j * p.B + 32 * wave + ln;
-  const bool kok = key < p.N;
-  const int key32 = (int)key, n32 = (int)p.N;          // positions fit 32 bits (checked by the host)
-  const int64_t krow = ((int64_t)b * p.hkv + kvh) * p.N + (kok ? key : 0);
-  bf16x8 kf[NC], vf[NC];
-  reg_rows<D>(p.k + krow * D, kok, lane, kf);
-  reg_rows<D>(p.v + krow * D, kok, lane, vf);
-
-  f32x16 dkt[ND], dvt[ND];
-#pragma unroll
-  for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dkt[dt][r] = 0.f; dvt[dt][r] = 0.f; }
-
-  // tile sequence: entry e, query head g of the group, 64-query piece u of the block
-  const int n_tiles = n_ent * p.G * p.subs;
-  // Two cursors walk it, one for the copies (ahead) and one for the products; they advance digit by digit, so
-  // that the loop has no divisions.
-  struct cursor_t { int u, gg, e; };
-  auto advance = [&](cursor_t& c) {
-    if (++c.u == p.subs) { c.u = 0; if (++c.gg == p.G) { c.gg = 0; ++c.e; } }
-  };
-  auto locate = [&](const cursor_t& c, int& i, int& h, int64_t& q0) {
-    i = entry(c.e);
-    h = kvh * p.G + c.gg;
-    q0 = (int64_t)i * p.B + c.u * KT;
-  };
-  cursor_t cf = {0, 0, 0}, cc = {0, 0, 0};
-  auto fill = [&](int t) {
-    int i, h; int64_t q0;
-    locate(cf, i, h, q0);
-    advance(cf);
-    const uint32_t dst = lds0 + (t % NSTG) * STAGEB;
-    const int64_t head_rows = ((int64_t)b * p.hq + h) * p.N;
-    copy_tile<D, NW>(p.q + head_rows * D, q0, p.N - 1, dst, wave, lane);
-    copy_tile<D, NW>(p.dout + head_rows * D, q0, p.N - 1, dst + G::TILEB, wave, lane);
-    if (wave == 0) {
-      // the tile's 64 log-sum-exps and Deltas, copied asynchronously like the tiles (a load through registers
-      // would make this wavefront wait for memory in every iteration); rows beyond the sequence repeat the last
-      // one and are masked where they are used
-      int64_t qi = q0 + lane;
-      qi = qi < p.N ? qi : p.N - 1;
-      const uint32_t vdst = __builtin_amdgcn_readfirstlane(dst + 2 * G::TILEB);
-      async_copy4(p.lse2 + head_rows + qi, vdst);
-      async_copy4(p.delta + head_rows + qi, vdst + 256);
-    }
-  };
-  static_assert(G::IPT % NW == 0, "tile copies must divide over the wavefronts");
-  constexpr int CPF = 2 * G::IPT / NW;     // copies per wavefront and fill (Q and dO); the first wavefront adds two
-  for (int s0 = 0; s0 < NSTG - 1; ++s0)
-    if (s0 < n_tiles) fill(s0);
-  for (int t = 0; t < n_tiles; ++t) {
-    if (t + NSTG - 1 <= n_tiles) {
-      if (wave == 0) wait_vmcnt<(NSTG - 2) * (CPF + 2)>(); else wait_vmcnt<(NSTG - 2) * CPF>();
-    } else {
-      wait_vmcnt<0>();
-    }
-    __syncthreads();
-    if (t + NSTG - 1 < n_tiles) fill(t + NSTG - 1);
-    int i, h; int64_t q0;
-    locate(cc, i, h, q0);
-    advance(cc);
-    const uint32_t qt = lds0 + (t % NSTG) * STAGEB, dot = qt + G::TILEB;
-    const float* vec = reinterpret_cast<const float*>(smem + (t % NSTG) * STAGEB + 2 * G::TILEB);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      // (no shortcut for halves that the causal mask or the end of the sequence empties: the mask below zeroes
-      // them, and a branch around the products makes the compiler copy the 128 accumulator registers)
-      f32x16 S, dP;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { S[r] = 0.f; dP[r] = 0.f; }
-      pipelined_mfma<2 * NC, PFD>(
-          [&](int m) { return row_frag<D>((m & 1) ? dot : qt, m >> 1, half, lane); },
-          [&](int m, bf16x8 a) {
-            if (m & 1) dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vf[m >> 1], dP, 0, 0, 0);
-            else S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[m >> 1], S, 0, 0, 0);
-          });
-      u32x4 pp[2], dsp[2];
-      auto elements = [&](auto masked) {
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int lr0 = 32 * half + 8 * r4 + 4 * hh;                // rows lr0 .. lr0+3 of the tile
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(vec + lr0);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(vec + 64 + lr0);
-          float x[4], y[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // computed for every element and selected afterwards: a conditional exponential becomes a branch
-            const float pr = __builtin_amdgcn_exp2f(fmaf(S[4 * r4 + e], p.c2, -l4[e]));
-            x[e] = pr;
-            y[e] = pr * (dP[4 * r4 + e] - d4[e]);
-            if (decltype(masked)::value) {
-              const int qi = (int)q0 + lr0 + e;
-              const bool att = kok && qi >= key32 && qi < n32;
-              x[e] = att ? x[e] : 0.f;
-              y[e] = att ? y[e] : 0.f;
-            }
-          }
-          const int r = 4 * r4;
-          pp[r >> 3][(r & 7) >> 1] = pack2(x[0], x[1]);
-          pp[r >> 3][((r & 7) >> 1) + 1] = pack2(x[2], x[3]);
-          dsp[r >> 3][(r & 7) >> 1] = pack2(y[0], y[1]);
-          dsp[r >> 3][((r & 7) >> 1) + 1] = pack2(y[2], y[3]);
-        }
-      };
-      // the mask matters on the diagonal block and where queries or keys run past the sequence (uniform test)
-      if (i == j || q0 + KT > p.N || ((int64_t)j + 1) * p.B > p.N) elements(std::true_type{});
-      else elements(std::false_type{});
-      // instruction m: 16-query step k2 = m / (2 ND), d tile dt = (m/2) % ND, dV (dO tile) or dK (Q tile) = m%2
-      pipelined_mfma<4 * ND, PFD>(
-          [&](int m) { return tr_frag<D>((m & 1) ? qt : dot, 2 * half + m / (2 * ND), (m >> 1) % ND, lane); },
-          [&](int m, bf16x8 a) {
-            const int k2 = m / (2 * ND), dt = (m >> 1) % ND;
-            if (m & 1) dkt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, dsp[k2]), dkt[dt], 0, 0, 0);
-            else dvt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, pp[k2]), dvt[dt], 0, 0, 0);
-          });
-    }
-  }
-  wait_vmcnt<0>();
-
-  if (!kok) return;
-  if (!whole_column) {
-    __bf16* ok_ = p.dk + krow * D;
-    __bf16* ov_ = p.dv + krow * D;
-#pragma unroll
-    for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const u32x2 wk = {pack2(dkt[dt][4 * r4] * p.scale, dkt[dt][4 * r4 + 1] * p.scale),
-                          pack2(dkt[dt][4 * r4 + 2] * p.scale, dkt[dt][4 * r4 + 3] * p.scale)};
-        const u32x2 wv = {pack2(dvt[dt][4 * r4], dvt[dt][4 * r4 + 1]), pack2(dvt[dt][4 * r4 + 2], dvt[dt][4 * r4 + 3])};
-        *reinterpret_cast<u32x2*>(ok_ + 32 * dt + 8 * r4 + 4 * hh) = wk;
-        *reinterpret_cast<u32x2*>(ov_ + 32 * dt + 8 * r4 + 4 * hh) = wv;
-      }
-  } else {
-    const int64_t srow = ((int64_t)b * p.hkv + kvh) * ((int64_t)p.sink_blocks * p.B) + key;   // key < sink_blocks * B
-    float* sk = p.dk_sink + srow * D;
-    float* sv = p.dv_sink + srow * D;
-#pragma unroll
-    for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int d = 32 * dt + acc_row(r, hh);
-        atomicAdd(sk + d, dkt[dt][r] * p.scale);
-        atomicAdd(sv + d, dvt[dt][r]);
-      }
-  }
-}
-
-// dK, dV with the two halves of the work on different wavefronts (blocks of 64 or 128 keys).  The kernel above keeps
-// both transposed accumulators plus the K and V rows of its keys in one wavefront: more than 256 registers, one
-// wavefront per SIMD, nothing to overlap with.  Here every 32-key slice has a wavefront that forms S and P and
+// The two halves of the work sit on different wavefronts: every 32-key slice has a wavefront that forms S and P and
 // accumulates dV^T, and one that forms dP and dS and accumulates dK^T.  P travels through LDS, lane to same lane
 // (both hold the same element layout), and the second wavefront runs one tile behind the first, so that the step's
-// one barrier orders the exchange.  Each needs about 170 registers: two per SIMD, one of each kind.
-template <int D, int NSL>
-__global__ __launch_bounds__(128 * NSL) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void pa_bwd_dkv_split_kernel(bwd_params p) {
+// one barrier orders the exchange.  Each needs about 170 registers: two per SIMD, one of each kind.  (With both
+// accumulators in one wavefront a lane needs 356 registers: one wavefront per SIMD, or spills.)
+//
+// A workgroup owns NSL slices (a slab of 32 NSL keys; a block of B keys is B / (32 NSL) slabs) and stages tiles of
+// 32 QW QI queries: QW groups of wavefronts share a tile's 32-query pieces, QI pieces each, and add their sums up in
+// LDS at the end.
+//
+// Bound: instruction issue (a SIMD issues about one instruction per 4 to 5 cycles, a matrix instruction lasts 32).  Per
+// matrix instruction the loops take 9.0 instructions at 128-key slabs and head_dim 128; 13.0 with a cursor each
+// for copies and products, Delta subtracted element by element and a wait per matrix instruction.  Training steps with
+// 32 query heads on 8 (28 on 4 at block 256), N = 32768: block 64 2.19 -> 1.98 ms, block 256 6.29 -> 4.65 ms (of which
+// the kernel 3.9 -> 2.3); N = 2000, block 64: 232 -> 144 us, block 256: 766 -> 254 us.
+template <int NSL, int QW, int QI, bool P32>
+struct dkv_geo {
+  static constexpr int NW = 2 * NSL * QW;        // wavefronts
+  static constexpr int TR = 32 * QW * QI;        // queries per tile
+  static constexpr int PPIECE = P32 ? 4096 : 2048;       // P of a 32 x 32 piece, fp32 or bf16
+  static constexpr int PBUF = NSL * QW * QI * PPIECE;    // P of one tile
+  template <int D> static constexpr int tileb() { return TR / tile_geo<D>::RPI * tile_geo<D>::SRB; }
+  template <int D> static constexpr int stageb() { return 2 * tileb<D>() + 8 * TR; }   // Q, dO, log-sum-exps, Deltas
+  static constexpr int NST = 3;                  // tile it+1 arriving, tile it (P side), tile it-1 (dS side)
+  template <int D> static constexpr size_t lds() { return NST * (size_t)stageb<D>() + 2 * (size_t)PBUF; }
+};
+// copy instruction x of a wavefront's share of a tile and, if BOTH, of the tile behind it
+template <int D, int NW, int TILEB, bool BOTH>
+__device__ __forceinline__ void dkv_copy(const __bf16* qb, const __bf16* ob, uint32_t voff, uint32_t dst, int x) {
+  constexpr int STEP = NW * tile_geo<D>::SRB;
+  static_assert(tile_geo<D>::IPT / NW <= 4, "the switch lists the copies");
+  switch (x) {                                   // x is a constant wherever this is called (unrolled loops)
+    case 0: async_copy16_at<0>(qb, voff, dst); if (BOTH) async_copy16_at<TILEB>(ob, voff, dst); break;
+    case 1: async_copy16_at<STEP>(qb, voff, dst); if (BOTH) async_copy16_at<TILEB + STEP>(ob, voff, dst); break;
+    case 2: async_copy16_at<2 * STEP>(qb, voff, dst); if (BOTH) async_copy16_at<TILEB + 2 * STEP>(ob, voff, dst); break;
+    default: async_copy16_at<3 * STEP>(qb, voff, dst); if (BOTH) async_copy16_at<TILEB + 3 * STEP>(ob, voff, dst); break;
+  }
+}
+template <int D, int NSL, int QW, int QI, bool P32>
+__global__ __launch_bounds__(128 * NSL * QW) __attribute__((amdgpu_waves_per_eu(2)))
+void pa_bwd_dkv_kernel(bwd_params p) {
   using G = tile_geo<D>;
-  constexpr int NW = 2 * NSL;
+  using W = dkv_geo<NSL, QW, QI, P32>;
+  constexpr int NW = W::NW, TR = W::TR, PBUF = W::PBUF, NST = W::NST;
   constexpr int NC = G::NC, ND = G::ND;
-  constexpr int STAGEB = 2 * G::TILEB + 512;     // Q tile, dO tile, 64 log-sum-exps, 64 Deltas
-  constexpr int NST = 3;                         // tile t+1 arriving, tile t (P side), tile t-1 (dS side)
-  constexpr int PBUF = NSL * 4096;               // P of one tile: per slice 2 halves x 2 KB
+  constexpr int TILEB = W::template tileb<D>(), STAGEB = W::template stageb<D>();
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
 
@@ -603,26 +441,32 @@ void pa_bwd_dkv_split_kernel(bwd_params p) {
   const int ln = lane & 31, hh = lane >> 5;
   const int kvh = blockIdx.y, b = blockIdx.z;
   const int slice = wave % NSL;
-  const bool krole = wave >= NSL;                // false: S, P, dV^T; true: dP, dS, dK^T
+  const int qg = QW == 1 ? 0 : (wave / NSL) % QW;
+  const bool krole = wave >= NSL * QW;           // false: S, P, dV^T; true: dP, dS, dK^T
 
+  // ---- which slab of which key block, which part of its column ----
   int j, part;
-  // the parts of the sink blocks' columns come first in the launch: they are the longest workgroups (PART query
-  // blocks each against a dozen for an ordinary column), and the last ones to start should be the shortest
+  // the parts of the sink blocks' columns come first in the launch: they are the longest workgroups,
+  // and the last ones to start should be the shortest
+  const int slabs = p.B / (32 * NSL);
+  const int slab = (int)blockIdx.x % slabs, e0 = (int)blockIdx.x / slabs;
   const int n_extra = p.sink_blocks * (p.max_parts - 1);
-  if ((int)blockIdx.x >= n_extra) { j = (int)blockIdx.x - n_extra; part = 0; }
+  if (e0 >= n_extra) { j = e0 - n_extra; part = 0; }
   else {
-    const int e = (int)blockIdx.x;
-    j = e / (p.max_parts - 1);
-    part = 1 + e % (p.max_parts - 1);
+    j = e0 / (p.max_parts - 1);
+    part = 1 + e0 % (p.max_parts - 1);
   }
-  const bool whole_column = j < p.sink_blocks;
-  const int parts = whole_column ? (p.nb - j + PART - 1) / PART : 1;
-  if (part >= parts) return;
+  const bool whole_column = j < p.sink_blocks;                    // a sink block: every later query block
+  const int parts = whole_column ? (p.nb - j + p.part - 1) / p.part : 1;
+  if (part >= parts) return;                                      // uniform over the workgroup
+  const int64_t slab0 = (int64_t)j * p.B + slab * (32 * NSL);     // its first key
+  if (slab0 >= p.N) return;
+  // entries of the column: query blocks j .. j+n_win-1, then j + 2^k for 2^k >= the window
   const int weff = (p.flags & POWATTN_POWER) ? (p.W > 1 ? p.W : 1) : p.W;
   int n_win, n_ent, first_pow = 1;
   if (whole_column) {
-    n_win = p.nb - j - part * PART;
-    if (n_win > PART) n_win = PART;
+    n_win = p.nb - j - part * p.part;
+    if (n_win > p.part) n_win = p.part;
     n_ent = n_win;
   } else {
     n_win = weff < p.nb - j ? weff : p.nb - j;
@@ -633,15 +477,15 @@ void pa_bwd_dkv_split_kernel(bwd_params p) {
     }
   }
   auto entry = [&](int e) -> int {
-    if (whole_column) return j + part * PART + e;
+    if (whole_column) return j + part * p.part + e;
     if (e < n_win) return j + e;
     return j + (first_pow << (e - n_win));
   };
 
   // this lane's key; its K row (P side) or V row (dS side) as B operand
-  const int64_t key = (int64_t)j * p.B + 32 * slice + ln;
+  const int64_t key = slab0 + 32 * slice + ln;
   const bool kok = key < p.N;
-  const int key32 = (int)key, n32 = (int)p.N;
+  const int key32 = (int)key, n32 = (int)p.N;          // positions fit 32 bits (checked by the host)
   const int64_t krow = ((int64_t)b * p.hkv + kvh) * p.N + (kok ? key : 0);
   bf16x8 xf[NC];
 
@@ -651,121 +495,234 @@ void pa_bwd_dkv_split_kernel(bwd_params p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[dt][r] = 0.f;
 
-  const int n_tiles = n_ent * p.G * p.subs;
-  // The tiles of the column in order: the 64-query tiles of a query block, for each head of the group, for each
-  // entry of the column.  A cursor carries what a tile needs (query block, first query, first row of the head's
-  // slab, LDS stage) and moves on by additions: one runs ahead with the copies, one goes with the products.
-  struct cursor_t { int u, gg, e, i; int64_t q0, head_rows; uint32_t stage; };
-  auto advance = [&](cursor_t& c) {
-    c.stage = c.stage == (NST - 1) * STAGEB ? 0u : c.stage + STAGEB;
-    if (++c.u < p.subs) { c.q0 += KT; return; }
-    c.u = 0;
-    if (++c.gg < p.G) { c.head_rows += p.N; }
-    else {
-      c.gg = 0;
-      c.head_rows -= (int64_t)(p.G - 1) * p.N;
-      if (++c.e < n_ent) c.i = entry(c.e);
-    }
-    c.q0 = (int64_t)c.i * p.B;
+  // The tiles of the column in order: the tiles of a query block (those of the diagonal block that end before the
+  // slab's first key are masked out entirely and left out), for each head of the group, for each entry of the column.
+  // A SIMD issues about one instruction of any kind every 4 to 5 cycles, so the walk has to be short: one cursor, run
+  // by the copies, moved on by additions; the products get a tile's first query handed on from the copies.
+  const int tpb = p.B / TR;                                       // tiles per query block
+  const int u_diag = slab * (32 * NSL) / TR;                      // first tile of the diagonal block
+  const int n_tiles = n_ent * p.G * tpb - (part == 0 ? p.G * u_diag : 0);   // (the diagonal is the first entry of part 0)
+  int c_e = 0, c_gg = 0, c_left = 0;             // entry, head of the group, tiles left of that head's
+  int c_q0 = 0, c_first = 0, c_cnt = 0;          // first query of the tile; of the entry's first tile; tiles per head
+  int64_t c_row = 0;                             // the tile's first row in [batch, hq, N]
+  uint32_t c_stage = 0;
+  auto enter = [&]() {                           // the first tile of the first head of entry c_e
+    const int i = entry(c_e);
+    const int u = i == j ? u_diag : 0;
+    c_gg = 0;
+    c_cnt = tpb - u;
+    c_left = c_cnt;
+    c_q0 = c_first = i * p.B + u * TR;
+    c_row = ((int64_t)b * p.hq + (int64_t)kvh * p.G) * p.N + c_q0;
   };
-  cursor_t cf;                                   // the copies' cursor
-  cf.u = 0; cf.gg = 0; cf.e = 0; cf.i = entry(0); cf.q0 = (int64_t)cf.i * p.B;
-  cf.head_rows = ((int64_t)b * p.hq + (int64_t)kvh * p.G) * p.N; cf.stage = 0;
-  cursor_t cc = cf;                              // this wavefront's products
-  auto fill = [&]() {
-    const int64_t q0 = cf.q0, head_rows = cf.head_rows;
-    const uint32_t dst = lds0 + cf.stage;
-    advance(cf);
-    copy_tile<D, NW>(p.q + head_rows * D, q0, p.N - 1, dst, wave, lane);
-    copy_tile<D, NW>(p.dout + head_rows * D, q0, p.N - 1, dst + G::TILEB, wave, lane);
+  auto advance = [&]() {
+    c_stage = c_stage == (NST - 1) * STAGEB ? 0u : c_stage + STAGEB;
+    if (--c_left > 0) { c_q0 += TR; c_row += TR; return; }
+    if (++c_gg < p.G) {
+      c_row += n32 - (c_q0 - c_first);
+      c_q0 = c_first;
+      c_left = c_cnt;
+    } else if (++c_e < n_ent) {
+      enter();
+    }
+  };
+  enter();
+  // this lane's part of a tile copy that lies inside the sequence: byte offsets of its copy instructions, X apart
+  // (copy instructions per wavefront and tile; with twice as many wavefronts as instructions the lower half of them
+  // copies the Q tile and the upper half the dO tile)
+  constexpr bool EITHER = 2 * (TR / G::RPI) == NW;
+  constexpr int CPT = EITHER ? 1 : TR / G::RPI / NW;
+  const int cw = EITHER ? wave % (NW / 2) : wave;
+  uint32_t voff[CPT];
+#pragma unroll
+  for (int x = 0; x < CPT; ++x)
+    voff[x] = (uint32_t)(G::RPI * (cw + NW * x) + lane % G::RPI) * G::ROWB + (uint32_t)((lane / G::RPI) << 4);
+  const uint32_t w_dst = __builtin_amdgcn_readfirstlane(lds0 + cw * G::SRB + (EITHER && wave >= NW / 2 ? TILEB : 0));
+  // The copies of the next tile; returns its first query.
+  auto fill = [&]() -> int {
+    const int q0 = c_q0;
+    const __bf16* qb = uniform_ptr((EITHER && wave >= NW / 2 ? p.dout : p.q) + c_row * D);
+    const __bf16* ob = uniform_ptr(p.dout + c_row * D);
+    const uint32_t dst = w_dst + c_stage;
+    const bool inside = q0 + TR <= n32;
+    const int last = n32 - 1 - q0;               // rows beyond the sequence repeat its last row (masked where used)
+    if (inside) {
+#pragma unroll
+      for (int x = 0; x < CPT; ++x) dkv_copy<D, NW, TILEB, !EITHER>(qb, ob, voff[x], dst, x);
+    } else {
+#pragma unroll
+      for (int x = 0; x < CPT; ++x) {
+        int row = G::RPI * (cw + NW * x) + lane % G::RPI;
+        row = row < last ? row : last;           // (last may be negative: a tile that starts behind the sequence)
+        const int64_t back = last < 0 ? last : 0;
+        dkv_copy<D, NW, TILEB, !EITHER>(uniform_ptr(qb + back * D), uniform_ptr(ob + back * D),
+                               (uint32_t)(row - (int)back) * G::ROWB + (uint32_t)((lane / G::RPI) << 4), dst, x);
+      }
+    }
     if (wave == 0) {
-      int64_t qi = q0 + lane;
-      qi = qi < p.N ? qi : p.N - 1;
-      const uint32_t vdst = __builtin_amdgcn_readfirstlane(dst + 2 * G::TILEB);
-      async_copy4(p.lse2 + head_rows + qi, vdst);
-      async_copy4(p.delta + head_rows + qi, vdst + 256);
+      // the tile's log-sum-exps and Deltas, copied asynchronously like the tiles (a load through registers would make
+      // this wavefront wait for memory in every iteration)
+      const uint32_t vdst = __builtin_amdgcn_readfirstlane(lds0 + c_stage + 2 * TILEB);
+      int r = lane % TR;
+      r = r < last ? r : last;
+      if (TR == 32) {
+        async_copy4((hh ? p.delta : p.lse2) + c_row + r, vdst);
+      } else {
+        async_copy4(p.lse2 + c_row + r, vdst);
+        async_copy4(p.delta + c_row + r, vdst + 4 * TR);
+      }
     }
+    advance();
+    return q0;
   };
-  static_assert(G::IPT % NW == 0, "tile copies must divide over the wavefronts");
-  fill();
+  static_assert(TR == 32 || TR == 64, "a tile's vectors are one or two copy instructions");
+  static_assert((TR / G::RPI) % NW == 0 || EITHER, "tile copies must divide over the wavefronts");
+  // The mask matters on the diagonal block and where queries or keys run past the sequence: tiles whose first query
+  // lies outside [m_lo, m_lo + m_span].
+  int m_lo = (int)(((int64_t)j + 1) * p.B < n32 ? ((int64_t)j + 1) * p.B : n32);
+  uint32_t m_span = n32 - TR - m_lo > 0 ? (uint32_t)(n32 - TR - m_lo) : 0u;
+  if (n32 - TR < m_lo || slab0 + 32 * NSL > p.N) { m_lo = 0x7fffffff; m_span = 0; }     // every tile
+  const uint32_t pbase = lds0 + NST * STAGEB + (slice * QW + qg) * (QI * W::PPIECE) + lane * 16;
+
+  int q_next = fill();
   // (after the first tile's copies: they would queue behind these row-per-lane loads)
   reg_rows<D>((krole ? p.v : p.k) + krow * D, kok, lane, xf);
-  // iteration it: the P side works on tile it, the dS side on tile it-1
-  for (int it = 0; it <= n_tiles; ++it) {
-    wait_vmcnt<0>();
-    __syncthreads();      // tile it has landed; P of tile it-1 is in LDS; everybody is done with tile it-2
-    if (it + 1 < n_tiles) fill();                 // tile it+1
-    const int t = krole ? it - 1 : it;
-    if (t < 0 || t >= n_tiles) continue;          // uniform per wavefront; the barriers stay matched
-    const int i = cc.i;
-    const int64_t q0 = cc.q0;
-    const uint32_t qt = lds0 + cc.stage, dot = qt + G::TILEB;
-    const float* vec = reinterpret_cast<const float*>(smem + cc.stage + 2 * G::TILEB);
-    advance(cc);
-    const bool need_mask = i == j || q0 + KT > p.N || ((int64_t)j + 1) * p.B > p.N;
-    unsigned char* pb = smem + NST * STAGEB + (t & 1) * PBUF + slice * 4096 + lane * 16;
+
+  // One tile's products: piece by piece, S or dP, the elements, dV^T or dK^T.
+  auto products = [&](auto role, int q0, uint32_t stage, uint32_t pbuf) {
+    constexpr bool KR = decltype(role)::value;
+    const uint32_t qt = lds0 + stage, dot = qt + TILEB;
+    const uint32_t vec = qt + 2 * TILEB;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      f32x16 X;           // S on the P side, dP on the dS side
+    for (int x_ = 0; x_ < QI; ++x_) {
+      const int half = QI * qg + x_;              // the 32-query piece of the tile
+      f32x16 X;           // S on the P side, dP - Delta on the dS side
+      u32x4 w[2];         // packed P (P side) or dS (dS side): the B operand of the second product
+      const uint32_t vrow = vec + 4 * (32 * half + 4 * hh);          // this lane's rows of the vectors: +32 r4 bytes
+      lds_u32x4* slot = (lds_u32x4*)(uintptr_t)(pbuf + x_ * W::PPIECE);
+      u32x4 pr[P32 ? 4 : 2];
+      if (KR) {
+        // the accumulators start at -Delta of their rows
 #pragma unroll
-      for (int r = 0; r < 16; ++r) X[r] = 0.f;
-      const uint32_t rows_from = krole ? dot : qt;
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const f32x4 d4 = *(const lds_f32x4*)(uintptr_t)(vrow + 4 * TR + 32 * r4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) X[4 * r4 + e] = d4[e];
+        }
+#pragma unroll
+        for (int x = 0; x < (P32 ? 4 : 2); ++x) pr[x] = slot[64 * x];      // P of the same elements, masked by its producer
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X[r] = 0.f;
+      }
+      const uint32_t rows_from = KR ? dot : qt;
       pipelined_mfma<NC, PFD>(
           [&](int m) { return row_frag<D>(rows_from, m, half, lane); },
           [&](int m, bf16x8 a) { X = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[m], X, 0, 0, 0); });
-      u32x4 w[2];         // packed P (P side) or dS (dS side): the B operand of the second product
-      u32x4* slot = reinterpret_cast<u32x4*>(pb + half * 2048);
-      if (!krole) {
+      if (!KR) {
         auto elements = [&](auto masked) {
 #pragma unroll
           for (int r4 = 0; r4 < 4; ++r4) {
-            const int lr0 = 32 * half + 8 * r4 + 4 * hh;
-            const f32x4 l4 = *reinterpret_cast<const f32x4*>(vec + lr0);
+            const f32x4 l4 = *(const lds_f32x4*)(uintptr_t)(vrow + 32 * r4);
             float x[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
+              // computed for every element and selected afterwards: a conditional exponential becomes a branch
               x[e] = __builtin_amdgcn_exp2f(fmaf(X[4 * r4 + e], p.c2, -l4[e]));
               if (decltype(masked)::value) {
-                const int qi = (int)q0 + lr0 + e;
+                const int qi = q0 + 32 * half + 8 * r4 + 4 * hh + e;
                 x[e] = (kok && qi >= key32 && qi < n32) ? x[e] : 0.f;
               }
             }
             const int r = 4 * r4;
             w[r >> 3][(r & 7) >> 1] = pack2(x[0], x[1]);
             w[r >> 3][((r & 7) >> 1) + 1] = pack2(x[2], x[3]);
+            if (P32) slot[64 * r4] = __builtin_bit_cast(u32x4, f32x4{x[0], x[1], x[2], x[3]});
           }
         };
-        if (need_mask) elements(std::true_type{}); else elements(std::false_type{});
-        slot[0] = w[0];                            // lane l's two 16-byte pieces at l*16 and 1024 + l*16
-        slot[64] = w[1];
+        if ((uint32_t)(q0 - m_lo) > m_span) elements(std::true_type{}); else elements(std::false_type{});
+        if (!P32) {                                // lane l's 16-byte pieces at l*16, 1024 + l*16
+          slot[0] = w[0];
+          slot[64] = w[1];
+        }
       } else {
-        const u32x4 p0 = slot[0], p1 = slot[64];   // bf16 P of the same elements, masked by its producer
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-          const int lr0 = 32 * half + 8 * r4 + 4 * hh;
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(vec + 64 + lr0);
           float y[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int r = 4 * r4 + e;
-            const uint32_t pk = (r < 8 ? p0 : p1)[(r & 7) >> 1];
-            const float pr = __builtin_bit_cast(float, (r & 1) ? (pk & 0xffff0000u) : (pk << 16));
-            y[e] = pr * (X[r] - d4[e]);
+            uint32_t pk;
+            if (P32) pk = pr[r >> 2][r & 3];
+            else pk = (r & 1) ? (pr[r >> 3][(r & 7) >> 1] & 0xffff0000u) : (pr[r >> 3][(r & 7) >> 1] << 16);
+            y[e] = __builtin_bit_cast(float, pk) * X[r];
           }
           const int r = 4 * r4;
           w[r >> 3][(r & 7) >> 1] = pack2(y[0], y[1]);
           w[r >> 3][((r & 7) >> 1) + 1] = pack2(y[2], y[3]);
         }
       }
-      const uint32_t cols_from = krole ? qt : dot;
+      const uint32_t cols_from = KR ? qt : dot;
       pipelined_mfma<2 * ND, PFD>(
           [&](int m) { return tr_frag<D>(cols_from, 2 * half + m / ND, m % ND, lane); },
           [&](int m, bf16x8 a) {
             acc[m % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, w[m / ND]), acc[m % ND], 0, 0, 0);
           });
     }
+  };
+  // Iteration it: the P side works on tile it, the dS side on tile it-1 while the copies of tile it+1 are under way.
+  // A loop per side with the same number of barriers.
+  auto top = [&](int it) {
+    wait_vmcnt<0>();
+    __syncthreads();      // tile it has landed; P of tile it-1 is in LDS; everybody is done with tile it-2
+    if (it + 1 < n_tiles) q_next = fill();
+  };
+  uint32_t stage = 0, pbuf = pbase;
+  auto moved_on = [&]() {
+    stage = stage == (NST - 1) * STAGEB ? 0u : stage + STAGEB;
+    pbuf = pbuf == pbase ? pbase + PBUF : pbase;
+  };
+  if (!krole) {
+    for (int it = 0; it < n_tiles; ++it) {
+      const int q0 = q_next;
+      top(it);
+      products(std::false_type{}, q0, stage, pbuf);
+      moved_on();
+    }
+    top(n_tiles);
+  } else {
+    top(0);
+    for (int it = 1; it <= n_tiles; ++it) {
+      top(it);
+      products(std::true_type{}, 0, stage, pbuf);
+      moved_on();
+    }
   }
   wait_vmcnt<0>();
+
+  // the query groups' sums meet in LDS (the tiles are no longer needed), in a fixed order
+  if constexpr (QW > 1) {
+    static_assert(QW == 2 && (size_t)2 * NSL * ND * 4096 <= W::template lds<D>(), "one group hands its sums over");
+    f32x16* sums = reinterpret_cast<f32x16*>(smem) + ((krole ? NSL : 0) + slice) * (ND * 64);
+    __syncthreads();
+    if (qg == 1) {
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)               // lane-contiguous 16-byte pieces
+          reinterpret_cast<f32x4*>(sums)[(4 * dt + r4) * 64 + lane] = f32x4{acc[dt][4 * r4], acc[dt][4 * r4 + 1], acc[dt][4 * r4 + 2], acc[dt][4 * r4 + 3]};
+    }
+    __syncthreads();
+    if (qg == 1) return;
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 s4 = reinterpret_cast<const f32x4*>(sums)[(4 * dt + r4) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[dt][4 * r4 + e] += s4[e];
+      }
+  }
 
   if (!kok) return;
   const float f = krole ? p.scale : 1.0f;
@@ -809,22 +766,39 @@ int launch_dq(const bwd_params& p, int64_t items, hipStream_t stream) {
   hipLaunchKernelGGL((pa_bwd_dq_kernel<D, NW>), dim3((uint32_t)items), dim3(64 * NW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
 }
-template <int D, int NW>
-int launch_dkv(const bwd_params& p, dim3 grid, hipStream_t stream) {
-  constexpr size_t lds = NSTG * (2 * (size_t)tile_geo<D>::TILEB + 512);
+template <int D, int NSL, int QW, int QI, bool P32>
+int launch_dkv(const bwd_params& p, int batch, hipStream_t stream) {
+  constexpr size_t lds = dkv_geo<NSL, QW, QI, P32>::template lds<D>();
+  const int64_t gx = ((int64_t)p.nb + (int64_t)p.sink_blocks * (p.max_parts - 1)) * (p.B / (32 * NSL));
+  if (gx > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
+  const void* fn = reinterpret_cast<const void*>(&pa_bwd_dkv_kernel<D, NSL, QW, QI, P32>);
   static std::atomic<unsigned long long> done{0};
-  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_bwd_dkv_kernel<D, NW>), lds, done)) return st;
-  hipLaunchKernelGGL((pa_bwd_dkv_kernel<D, NW>), grid, dim3(64 * NW), lds, stream, p);
+  if (int st = pa_allow_dynamic_lds(fn, lds, done)) return st;
+  hipLaunchKernelGGL((pa_bwd_dkv_kernel<D, NSL, QW, QI, P32>), dim3((uint32_t)gx, (uint32_t)p.hkv, (uint32_t)batch),
+                     dim3(128 * NSL * QW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
 }
-
-template <int D, int NSL>
-int launch_dkv_split(const bwd_params& p, dim3 grid, hipStream_t stream) {
-  constexpr size_t lds = 3 * (2 * (size_t)tile_geo<D>::TILEB + 512) + 2 * (size_t)NSL * 4096;
-  static std::atomic<unsigned long long> done{0};
-  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_bwd_dkv_split_kernel<D, NSL>), lds, done)) return st;
-  hipLaunchKernelGGL((pa_bwd_dkv_split_kernel<D, NSL>), grid, dim3(128 * NSL), lds, stream, p);
-  return pa_note_hip(hipGetLastError());
+// Which form of the kernel.  Training steps (forward and backward, 32 query heads on 8), MI355X:
+//  * Up to one 64-key slab per compute unit the length of a column decides: 64-key slabs, two query groups.  Against
+//    one group: head_dim 128, N = 2000: block 64 0.139 / 0.149 ms, block 256 0.247 / 0.291; head_dim 64, N = 1000:
+//    block 64 0.063 / 0.078, block 128 0.089 / 0.115, block 256 0.117 / 0.158.
+//  * Blocks of 64 keys beyond that: one group, tiles of 32 queries, two or three workgroups per compute unit that are
+//    not in step with each other.  Against two groups: head_dim 128, N = 32768: 2.03 / 2.13 ms; head_dim 64: 1.21 / 1.26.
+//  * head_dim 128, larger blocks: 128-key slabs, which read the query tiles half as often (64-key slabs: block 128,
+//    N = 131072 15.4 ms against 14.5).  At blocks of 128 keys P goes from wavefront to wavefront in bf16 and the tiles are
+//    64 queries; at 256 it goes in fp32, which leaves room for tiles of 32 (block 256, N = 32768: 4.85 ms; block 128,
+//    N = 131072: 14.8 ms).
+//  * head_dim 64, larger blocks: 128-key slabs and two groups, sixteen wavefronts.  Against one group with tiles of 64
+//    and 64-key slabs: block 256, N = 32768 3.13 / 3.34 / 3.36 ms, N = 4000 0.317 / 0.345 / 0.351.
+template <int D>
+int launch_dkv_any(const bwd_params& p, int batch, hipStream_t stream) {
+  int n_cu = 1;
+  pa_current_device(nullptr, &n_cu);
+  const int64_t slabs64 = (int64_t)p.nb * (p.B / 64) * p.hkv * batch;
+  if (slabs64 <= n_cu) return launch_dkv<D, 2, 2, 1, true>(p, batch, stream);
+  if (p.B == 64) return launch_dkv<D, 2, 1, 1, true>(p, batch, stream);
+  if constexpr (D == 64) return launch_dkv<D, 4, 2, 1, true>(p, batch, stream);
+  else return p.B == 128 ? launch_dkv<D, 4, 1, 2, false>(p, batch, stream) : launch_dkv<D, 4, 1, 1, true>(p, batch, stream);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -860,7 +834,13 @@ int pa_launch_backward_bf16(const pa_backward_args& a) {
   const int nwq = (p.tasks > 4 && p.B >= 128) ? 8 : 4;
   p.chunks = (p.tasks + nwq - 1) / nwq;
   p.sink_blocks = a.pat.sink < a.nb ? a.pat.sink : a.nb;
-  p.max_parts = p.sink_blocks > 0 ? (a.nb + PART - 1) / PART : 1;
+  // A sink block's column is cut into parts as long as the longest ordinary column, at most PART blocks: on a short
+  // sequence longer ones would be all that is still running at the end.
+  int32_t longest = (a.pat.flags & POWATTN_POWER) ? (p.W > 1 ? p.W : 1) : p.W;
+  if (a.pat.flags & POWATTN_POWER)
+    for (int64_t pw = 1; pw < a.nb; pw <<= 1) longest += pw >= p.W ? 1 : 0;
+  p.part = longest < PART ? longest : PART;
+  p.max_parts = p.sink_blocks > 0 ? (a.nb + p.part - 1) / p.part : 1;
   if (p.max_parts < 2) p.max_parts = 2;                            // keeps the part arithmetic of the kernel defined
 
   // workspace: Delta, the log-sum-exp in base 2, then the sink blocks' sums
@@ -889,16 +869,7 @@ int pa_launch_backward_bf16(const pa_backward_args& a) {
   else st = nwq == 8 ? launch_dq<64, 8>(p, items, a.stream) : launch_dq<64, 4>(p, items, a.stream);
   if (st != POWATTN_OK) return st;
 
-  const int64_t gx = (int64_t)a.nb + (int64_t)p.sink_blocks * (p.max_parts - 1);
-  if (gx > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
-  const dim3 grid((uint32_t)gx, (uint32_t)a.hkv, (uint32_t)a.batch);
-  const int nwk = p.B / 32;
-  // blocks of 128 keys: the kernel with the work of a key slice split over two wavefronts (measured 10 % faster
-  // at the 128K workload; at 64 keys a workgroup of that kind has only four wavefronts and is slightly slower)
-  if (a.head_dim == 128)
-    st = nwk == 2 ? launch_dkv<128, 2>(p, grid, a.stream) : nwk == 4 ? launch_dkv_split<128, 4>(p, grid, a.stream) : launch_dkv<128, 8>(p, grid, a.stream);
-  else
-    st = nwk == 2 ? launch_dkv<64, 2>(p, grid, a.stream) : nwk == 4 ? launch_dkv_split<64, 4>(p, grid, a.stream) : launch_dkv<64, 8>(p, grid, a.stream);
+  st = a.head_dim == 128 ? launch_dkv_any<128>(p, a.batch, a.stream) : launch_dkv_any<64>(p, a.batch, a.stream);
   if (st != POWATTN_OK) return st;
 
   if (sink_elems > 0) {

@@ -184,3 +184,20 @@ def test_long_prefill_configuration_size_with_a_row_sparse_upstream_gradient():
 ])
 def test_degenerate_shapes(B, W, S, flags, hq, hkv, n, d):
     run_backward(pa.Pattern(B, W, S, flags), 1, hq, hkv, n, d, seed=57)
+
+
+# The dK/dV kernel's forms for more 64-key slabs than compute units (the shapes above have fewer): 32-query tiles at blocks
+# of 64 keys, 128-key slabs otherwise.  Sequences that end inside a slab, a tile and a block whose second slab is
+# empty; columns whose diagonal block starts behind its first tiles; a sink column in several parts.
+@pytest.mark.parametrize("B,W,S,flags,batch,hq,hkv,n,d", [
+    (64, 4, 1, pa.POWER, 1, 16, 8, 2111, 128),
+    (64, 2, 0, pa.POWER, 9, 8, 8, 225, 128),      # short sequences, many of them
+    (64, 4, 1, pa.POWER, 2, 8, 8, 2113, 64),
+    (128, 2, 2, pa.POWER, 1, 8, 8, 2177, 128),
+    (256, 5, 1, pa.POWER, 1, 8, 8, 2305, 128),
+    (256, 1, 0, pa.POWER, 3, 12, 4, 1471, 128),   # GQA 3, no sink
+    (128, 3, 1, pa.POWER, 3, 8, 8, 1409, 64),
+    (256, 2, 1, pa.POWER, 2, 8, 8, 1665, 64),
+])
+def test_more_slabs_than_compute_units(B, W, S, flags, batch, hq, hkv, n, d):
+    run_backward(pa.Pattern(B, W, S, flags), batch, hq, hkv, n, d, seed=58)
