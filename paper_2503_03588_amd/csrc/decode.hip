@@ -117,17 +117,8 @@ __device__ __forceinline__ dec_row dec_row_of(const dec_params& p, int64_t len) 
   r.i = p.subs == 1 ? chunk_of_t
       : chunk_of_t < (1 << 25) ? (int64_t)__umulhi((unsigned)chunk_of_t, p.subs_magic) : chunk_of_t / p.subs;
   r.rs = pa_shape_of_row(p.W, p.S, p.flags, r.i);
-  // The isolated blocks i - 2^k lie inside [pow_lo, win_start) exactly for i - win_start < 2^k <= i - pow_lo:
-  // a contiguous range of exponents, found with two leading-zero counts instead of a loop over the powers.
-  r.n_pow = 0; r.k_max = 0;
-  if (p.flags & POWATTN_POWER) {
-    const int64_t below = r.i - r.rs.win_start, upto = r.i - r.rs.pow_lo;
-    if (upto >= 1) {
-      const int k_min = below > 0 ? 64 - __builtin_clzll((unsigned long long)below) : 0;
-      r.k_max = 63 - __builtin_clzll((unsigned long long)upto);
-      r.n_pow = r.k_max >= k_min ? r.k_max - k_min + 1 : 0;
-    }
-  }
+  const pa_row_powers pw = pa_powers_of_row(r.rs, p.flags, r.i);
+  r.n_pow = pw.n_pow; r.k_max = pw.k_max;
   const int n_blocks = (int)r.rs.sink_end + r.n_pow + (int)(r.i - r.rs.win_start + 1);
   r.n_slots = n_blocks * p.subs;
   return r;

@@ -32,6 +32,22 @@ PA_HD pa_row_shape pa_shape_of_row(int32_t W, int32_t S, uint32_t flags, int64_t
   return r;
 }
 
+// The isolated blocks i - 2^k of a row lie inside [pow_lo, win_start) exactly for i - win_start < 2^k <= i - pow_lo:
+// n_pow exponents k_max, k_max-1, ... (ascending blocks), found with two leading-zero counts instead of a loop.
+struct pa_row_powers { int n_pow, k_max; };
+PA_HD pa_row_powers pa_powers_of_row(const pa_row_shape& r, uint32_t flags, int64_t i) {
+  pa_row_powers w = {0, 0};
+  if (flags & POWATTN_POWER) {
+    const int64_t below = i - r.win_start, upto = i - r.pow_lo;
+    if (upto >= 1) {
+      const int k_min = below > 0 ? 64 - __builtin_clzll((unsigned long long)below) : 0;
+      w.k_max = 63 - __builtin_clzll((unsigned long long)upto);
+      w.n_pow = w.k_max >= k_min ? w.k_max - k_min + 1 : 0;
+    }
+  }
+  return w;
+}
+
 // Calls emit(j) for every attended key block of query block i in ascending
 // order and returns how many there were.
 template <class F>

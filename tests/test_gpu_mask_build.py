@@ -63,3 +63,14 @@ def test_short_capacity_is_refused():
     with pytest.raises(pa.PowattnError) as e:
         pa.mask_build(pat, 65536, kv_idx=g_idx)
     assert e.value.status == pa.WORKSPACE_TOO_SMALL
+
+
+@pytest.mark.parametrize("n,B,W,S,flags", [
+    (7 * 64, 64, 4, 1, pa.POWER),          # rows of 7 entries: eight lanes share one
+    (9 * 64, 64, 9, 0, 0),                 # 9 entries on 16 lanes, no power term
+    (200 * 16, 16, 60, 9, pa.POWER),       # more than 64 entries: the lanes go round a second time
+    (100 * 16, 16, 0, 100, pa.POWER),      # every block a sink: the powers lie inside the sink range
+    (70 * 16, 16, 3, 70, pa.DENSE),
+])
+def test_row_lanes(n, B, W, S, flags):
+    test_lists_bit_exact(n, B, W, S, flags)
