@@ -973,6 +973,18 @@ int launch(const bf16_params& p, hipStream_t stream) {
   return p.chain ? launch_as<D, NW, NS, false, true, false>(p, stream) : launch_as<D, NW, NS, false, false, false>(p, stream);
 }
 
+// Whether a launch of few work items is better cut into workgroups of four wavefronts: when there is a compute unit for
+// every half-size item.  A lone wavefront per SIMD takes about 0.6 of the time for a step that two take each.
+// Eight / four wavefronts, us, 32 query heads on 8, blocks of 64 keys: head_dim 128 N = 200 15.2 / 12.8, N = 1000
+// 21.0 / 17.8; head_dim 64 N = 1000 14.9 / 12.0; 16 heads on 2, N = 2000 21.2 / 18.2; 8 on 8, blocks of 256, N = 4000
+// 45.2 / 36.1.  With three rounds of half-size items against two of whole ones (264 items) the two are level: 47.7 / 47.8.
+bool few_items_want_four_wavefronts(const bf16_params& p, const pa_prefill_args& a) {
+  int n_cu = 0;
+  pa_current_device(nullptr, &n_cu);
+  const int64_t per_chunk = (int64_t)a.batch * a.hkv * p.nb, slots = n_cu >= 8 ? n_cu / 8 : 1;
+  return (per_chunk * ((p.tasks + 3) / 4) + 7) / 8 <= slots;      // an eighth of the items per XCD
+}
+
 }  // namespace
 
 
@@ -992,7 +1004,8 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
   const int64_t tasks = (int64_t)p.G * p.B / QW;
   if (tasks > (1 << 20)) return POWATTN_UNSUPPORTED;
   p.tasks = (int32_t)tasks;
-  const int nw = p.tasks > 4 ? 8 : 4;
+  int nw = p.tasks > 4 ? 8 : 4;
+  if (nw == 8 && few_items_want_four_wavefronts(p, a)) nw = 4;
   p.chunks = (p.tasks + nw - 1) / nw;
   // Sequences of different lengths: an odd count of block numbers per sequence (the extra one lies behind every
   // sequence and is passed over), so that the power-of-two stride of a workgroup's item numbers walks through all
