@@ -8,6 +8,7 @@ built this module raises instead of computing anything itself.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -49,6 +50,13 @@ class Pattern:
 
     def c(self) -> _CPattern:
         return _CPattern(self.block, self.window, self.sink, self.flags)
+
+
+# The C struct of a pattern is built once per set of values (a call only reads it) instead of on every call: 1.3 us of
+# the 8 to 10 us of host time that bound the smallest calls.  typed: 64 and 64.0 stay different arguments.
+@functools.lru_cache(maxsize=256, typed=True)
+def _pattern_ref(block, window, sink, flags):
+    return ctypes.byref(_CPattern(block, window, sink, flags))
 
 
 _lib = None
@@ -122,7 +130,10 @@ def _ptr(t):
 
 def _stream(stream=None):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle itself: building a torch.cuda.Stream object for it takes longer than the look-up
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -149,14 +160,14 @@ def strerror(status: int) -> str:
 
 
 def num_blocks(pattern: Pattern, seq_len: int) -> int:
-    n = lib().powattn_num_blocks(ctypes.byref(pattern.c()), seq_len)
+    n = lib().powattn_num_blocks(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len)
     if n < 0:
         raise PowattnError(-n, "powattn_num_blocks")
     return n
 
 
 def max_k(pattern: Pattern, seq_len: int) -> int:
-    n = lib().powattn_max_k(ctypes.byref(pattern.c()), seq_len)
+    n = lib().powattn_max_k(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len)
     if n < 0:
         raise PowattnError(-n, "powattn_max_k")
     return n
@@ -176,7 +187,7 @@ def row_host(pattern: Pattern, q_block: int):
 
 
 def decode_workspace_bytes(pattern: Pattern, batch, n_q_heads, n_kv_heads, head_dim, cache_capacity) -> int:
-    return lib().powattn_decode_workspace_bytes(ctypes.byref(pattern.c()), batch, n_q_heads, n_kv_heads,
+    return lib().powattn_decode_workspace_bytes(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), batch, n_q_heads, n_kv_heads,
                                                 head_dim, cache_capacity)
 
 
@@ -201,7 +212,7 @@ def mask_build(pattern: Pattern, seq_len: int, kv_cnt=None, kv_idx=None, block_m
         kv_cnt = torch.empty((nb,), dtype=torch.int32, device=device)
     if block_mask is None and want_block_mask:
         block_mask = torch.empty((nb, nb), dtype=torch.uint8, device=device)
-    st = lib().powattn_mask_build(ctypes.byref(pattern.c()), seq_len, _ptr(kv_cnt), _ptr(kv_idx),
+    st = lib().powattn_mask_build(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len, _ptr(kv_cnt), _ptr(kv_idx),
                                   kv_idx.shape[1], _ptr(block_mask), _stream(stream))
     _check(st, "powattn_mask_build")
     return kv_cnt, kv_idx, block_mask
@@ -223,7 +234,7 @@ def prefill(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o=None, lse=None, softmax
     mk = kv_idx.shape[1] if kv_idx is not None else 0
     if kv_idx is not None and kv_cnt.shape[0] * pattern.block < n:
         raise ValueError("block lists shorter than the sequence")
-    st = lib().powattn_prefill(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
                                batch, hq, hkv, n, d, _dtype_code(q), float(softmax_scale), _stream(stream))
     _check(st, "powattn_prefill")
@@ -247,7 +258,7 @@ def prefill_chunk(pattern: Pattern, kv_cnt, kv_idx, q, k_cache, v_cache, q_start
     mk = kv_idx.shape[1] if kv_idx is not None else 0
     if kv_idx is not None and kv_cnt.shape[0] * pattern.block < q_start + q_len:
         raise ValueError("block lists shorter than the context")
-    st = lib().powattn_prefill_chunk(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill_chunk(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                      _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(o), _ptr(lse),
                                      batch, hq, hkv, int(q_start), q_len, cap, d, _dtype_code(q),
                                      float(softmax_scale), _stream(stream))
@@ -279,7 +290,7 @@ def prefill_chunk_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
         o = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((batch, hq, q_len), dtype=torch.float32, device=q.device)
-    st = lib().powattn_prefill_chunk_paged(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_prefill_chunk_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                            _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
                                            block_table.shape[1], n_pages, _ptr(o), _ptr(lse),
                                            batch, hq, hkv, int(q_start), q_len, d, _dtype_code(q),
@@ -316,7 +327,7 @@ def prefill_batch_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
         o = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((batch, hq, q_rows), dtype=torch.float32, device=q.device)
-    st = lib().powattn_prefill_batch_paged(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_prefill_batch_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                            _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
                                            block_table.shape[1], n_pages, _ptr(q_start), _ptr(q_len), q_rows,
                                            _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
@@ -339,9 +350,8 @@ def decode(pattern: Pattern, q, k_cache, v_cache, kv_len, o=None, lse=None, soft
     if lse is None and want_lse:
         lse = torch.empty((batch, hq), dtype=torch.float32, device=q.device)
     if workspace is None:
-        need = decode_workspace_bytes(pattern, batch, hq, hkv, d, cap)
         workspace = decode_workspace(pattern, batch, hq, hkv, d, cap, q.device)
-    st = lib().powattn_decode(ctypes.byref(pattern.c()), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
+    st = lib().powattn_decode(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
                               cap, _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
                               float(softmax_scale), _ptr(workspace), workspace.numel() * workspace.element_size(),
                               _stream(stream))
@@ -360,7 +370,7 @@ def decode_static(pattern: Pattern, q, k_cache, v_cache, kv_len, o, lse=None, so
         raise ValueError("kv_len must be int32 [batch]")
     if o.shape != q.shape or o.dtype != q.dtype:
         raise ValueError("o must have the shape and dtype of q")
-    st = lib().powattn_decode_static(ctypes.byref(pattern.c()), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
+    st = lib().powattn_decode_static(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
                                      cap, _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
                                      float(softmax_scale), _stream(stream))
     _check(st, "powattn_decode_static")
@@ -390,7 +400,7 @@ def decode_paged(pattern: Pattern, q, k_pages, v_pages, block_table, kv_len, o=N
         lse = torch.empty((batch, hq), dtype=torch.float32, device=q.device)
     if workspace is None:
         workspace = decode_workspace(pattern, batch, hq, hkv, d, stride * blk, q.device)
-    st = lib().powattn_decode_paged(ctypes.byref(pattern.c()), _ptr(q), _ptr(k_pages), _ptr(v_pages), n_pages,
+    st = lib().powattn_decode_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_pages), _ptr(v_pages), n_pages,
                                     _ptr(block_table), stride, _ptr(kv_len), _ptr(o), _ptr(lse),
                                     batch, hq, hkv, d, _dtype_code(q), float(softmax_scale),
                                     _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
@@ -399,7 +409,7 @@ def decode_paged(pattern: Pattern, q, k_pages, v_pages, block_table, kv_len, o=N
 
 
 def backward_workspace_bytes(pattern: Pattern, batch, n_q_heads, n_kv_heads, seq_len, head_dim) -> int:
-    return lib().powattn_backward_workspace_bytes(ctypes.byref(pattern.c()), batch, n_q_heads, n_kv_heads,
+    return lib().powattn_backward_workspace_bytes(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), batch, n_q_heads, n_kv_heads,
                                                   seq_len, head_dim)
 
 
@@ -429,7 +439,7 @@ def backward(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o, lse, d_o, dq=None, dk
         if need == 0:
             raise PowattnError(INVALID_ARG, "powattn_backward_workspace_bytes")
         workspace = torch.empty((need,), dtype=torch.uint8, device=q.device)
-    st = lib().powattn_backward(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_backward(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                 _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
                                 batch, hq, hkv, n, d, _dtype_code(q), float(softmax_scale),
                                 _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
@@ -456,7 +466,7 @@ def prefill_varlen(pattern: Pattern, kv_cnt, kv_idx, q, k, v, seq_lens, o=None, 
     if lse is None and want_lse:
         lse = torch.zeros((batch, hq, npad), dtype=torch.float32, device=q.device)
     mk = kv_idx.shape[1] if kv_idx is not None else 0
-    st = lib().powattn_prefill_varlen(ctypes.byref(pattern.c()), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill_varlen(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                       _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), batch, hq, hkv, _ptr(seq_lens),
                                       npad, d, _dtype_code(q), float(softmax_scale), _stream(stream))
     _check(st, "powattn_prefill_varlen")
