@@ -81,7 +81,7 @@ struct bf16_params {
   int32_t chunks;    // workgroups per (batch, kv head, query block)
   int32_t per_xcd;   // work items per XCD partition
   int32_t xcd_split; // sequences of different lengths, one or two KV heads: XCDs that share a KV head's items (else 0)
-  int64_t per_kvh;   // ... and the items of one KV head
+  int32_t b_shift;   // log2 of B, or -1
   int32_t chain;     // items may be chained in persistent workgroups
   int64_t total_wg;
   int64_t N;         // keys in the context: query q_start + r attends keys <= q_start + r, all of them < N
@@ -178,18 +178,78 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   // ---- this workgroup's work items: item k is number xcd*per_xcd + cuslot + nslots*k of the launch, so that
   // the workgroups of one XCD (one L2) work on neighbouring query blocks at any time ----
   const int xcd = pid & 7, cuslot = pid >> 3, nslots = (int)(gridDim.x >> 3);
-  int n_raw = 0;                       // item numbers that fall to this workgroup
+  int n_raw = 0;                       // items that fall to this workgroup
   int64_t first_item = (int64_t)xcd * p.per_xcd + cuslot;
   int item_step = nslots;
-  if (VARLEN && p.xcd_split > 1) {
-    // Sequences of different lengths and 1 or 2 KV heads: the XCDs that share a KV head take its item numbers
-    // in turn (number m goes to XCD m mod split of the head's group) instead of a contiguous part each, which would
-    // be some of the sequences and as much work as those happen to have.
-    const int sub = xcd % p.xcd_split;
-    const int64_t m0 = sub + (int64_t)p.xcd_split * cuslot;
-    item_step = p.xcd_split * nslots;
-    if (m0 < p.per_kvh) n_raw = (int)((p.per_kvh - m0 + item_step - 1) / item_step);
-    first_item = (int64_t)(xcd / p.xcd_split) * p.per_kvh + m0;
+  // Sequences of different lengths: keys and first query of sequence b (values outside the context or the slab of Q/O
+  // are clamped), and how many query blocks it has, counted from the one of its first query.
+  auto block_of = [&](int pos) -> int { return p.b_shift >= 0 ? pos >> p.b_shift : pos / p.B; };
+  struct seq_t { int n, qs, first, nblk; };
+  auto seq_of = [&](int b) -> seq_t {
+    seq_t q;
+    q.qs = 0;
+    const int len = p.seq_len[b];
+    if (p.q_start_dev) {
+      q.qs = p.q_start_dev[b];
+      q.qs = q.qs < 0 ? 0 : (q.qs > (int)p.N ? (int)p.N : q.qs);
+    }
+    int room = (int)p.N - q.qs;        // rows that fit the context, and the slab of Q/O
+    if ((int64_t)room > p.q_rows) room = (int)p.q_rows;
+    q.n = q.qs + (len < 0 ? 0 : (len > room ? room : len));
+    q.first = block_of(q.qs);
+    q.nblk = q.n > q.qs ? block_of(q.n - 1) - q.first + 1 : 0;
+    return q;
+  };
+  int v_kvh = 0, v_chunk = 0, v_b = 0, v_r = 0;          // VARLEN: the first item
+  if (VARLEN) {
+    // Only the query blocks that exist are numbered, so that every workgroup gets the same number of items whatever the
+    // mix of lengths (numbered as if all sequences had the padded length, the fullest of 256 workgroups got 20 items
+    // where 17 were the mean, at 32 pieces of 1 .. 2048 rows: 528 -> 501 us; 32 prompts of 300 .. 8192: 1447 -> 1369 us).  64 sequences at a time, one
+    // per lane: how many blocks they have, and a prefix sum to find the first item's sequence.
+    auto prefix = [&](int base, int& own) -> int {       // blocks of the sequences base .. base + lane
+      own = base + lane < p.batch ? seq_of(base + lane).nblk : 0;
+      int sum = own;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(sum, d);
+        if (lane >= d) sum += up;
+      }
+      return sum;
+    };
+    int blocks = 0, own = 0;                             // query blocks of all sequences, for one KV head
+    for (int base = 0; base < p.batch; base += 64) blocks += __builtin_amdgcn_readlane(prefix(base, own), 63);
+    const int per_kvh = blocks * p.chunks;               // (fits 32 bits: the host checked the padded count)
+    if (per_kvh == 0) return;
+    int m0;                                              // the first item's number among its KV head's
+    if (p.xcd_split > 1) {
+      // 1 or 2 KV heads: the XCDs that share a KV head take its items in turn (number m goes to XCD m mod split of the
+      // head's group) instead of a contiguous part each, which would be some of the sequences.
+      m0 = xcd % p.xcd_split + p.xcd_split * cuslot;
+      v_kvh = xcd / p.xcd_split;
+      item_step = p.xcd_split * nslots;
+      if (m0 < per_kvh) n_raw = (per_kvh - m0 + item_step - 1) / item_step;
+    } else {
+      const int total = per_kvh * p.hkv, per_xcd = (total + 7) / 8;
+      int lim = total - xcd * per_xcd;
+      if (lim > per_xcd) lim = per_xcd;
+      if (lim > cuslot) n_raw = (lim - cuslot + nslots - 1) / nslots;
+      m0 = xcd * per_xcd + cuslot;
+      v_kvh = m0 / per_kvh;
+      m0 -= v_kvh * per_kvh;
+    }
+    if (n_raw == 0) return;
+    v_r = __builtin_amdgcn_readfirstlane(m0 / p.chunks);
+    v_chunk = m0 - v_r * p.chunks;
+    for (int base = 0; base < p.batch; base += 64) {
+      const int sum = prefix(base, own), all = __builtin_amdgcn_readlane(sum, 63);
+      if (v_r < all) {
+        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(sum > v_r));   // the first lane that reaches beyond it
+        v_b = base + at;
+        v_r -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(own, at);
+        break;
+      }
+      v_r -= all;
+    }
   } else {
     int64_t lim = p.total_wg - (int64_t)xcd * p.per_xcd;
     if (lim > p.per_xcd) lim = p.per_xcd;
@@ -202,26 +262,19 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   static_assert(!PAGED || (CHAIN && !DENSE), "paged caches: explicit lists, chained items");
 
   // Items are numbered L = ((b*hkv + kvh)*nb + r)*chunks + chunk with r counting query blocks from the last one
-  // down (longest rows first, which matters for the dense list); with sequences of different lengths
-  // L = ((kvh*batch + b)*nb + r)*chunks + chunk, so that the contiguous share of an XCD spans all sequences (one KV
-  // head each when there are eight) and the XCDs finish together whatever the mix of lengths.  The first item is decoded by division, the
-  // following ones by adding the stride nslots digit by digit with carries: all scalar, no division in the loop.
-  struct item_t { int chunk, r, kvh, b, i, subs_diag, n, qs; };   // n: keys (= tokens) of the item's sequence; qs: its first query
+  // down (longest rows first, which matters for the dense list); with sequences of different lengths the KV head is
+  // the slowest digit and sequence b has nblk blocks, so that the contiguous share of an XCD spans all sequences (one
+  // KV head each when there are eight) and the XCDs finish together whatever the mix of lengths.  The first item is
+  // decoded by division, the following ones by adding the stride nslots digit by digit with carries: all scalar, no
+  // division in the loop.
+  struct item_t { int chunk, r, kvh, b, i, subs_diag, n, qs, first, nblk; };   // n: keys (= tokens) of the item's sequence; qs:
+                                                                               // its first query, in block `first`
+  auto enter_seq = [&](item_t& it) {   // uniform over the workgroup: scalar loads
+    const seq_t q = seq_of(it.b);
+    it.n = q.n; it.qs = q.qs; it.first = q.first; it.nblk = q.nblk;
+  };
   auto finish_item = [&](item_t& it) {
-    it.i = p.i0 + p.nb - 1 - it.r;
-    if (VARLEN) {                      // uniform over the workgroup: scalar loads; values outside [0, N] are clamped
-      int qs = 0;
-      if (p.q_start_dev) {
-        qs = p.q_start_dev[it.b];
-        qs = qs < 0 ? 0 : (qs > (int)p.N ? (int)p.N : qs);
-        it.i += qs / p.B;              // the launch numbers a sequence's query blocks from its own first one
-      }
-      const int n = p.seq_len[it.b];
-      it.qs = qs;
-      int room = (int)p.N - qs;        // rows that fit the context, and the slab of Q/O
-      if ((int64_t)room > p.q_rows) room = (int)p.q_rows;
-      it.n = qs + (n < 0 ? 0 : (n > room ? room : n));
-    }
+    it.i = (VARLEN ? it.first + it.nblk : p.i0 + p.nb) - 1 - it.r;
     // tiles of the diagonal block needed by any wavefront of the item
     int last_task = it.chunk * NW + NW - 1;
     if (last_task > p.tasks - 1) last_task = p.tasks - 1;
@@ -231,15 +284,13 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   auto digits = [&](uint32_t L) -> item_t {
     item_t it;
     it.chunk = (int)(L % (uint32_t)p.chunks); L /= (uint32_t)p.chunks;
-    it.r = (int)(L % (uint32_t)p.nb); L /= (uint32_t)p.nb;
-    if (VARLEN) {                      // the KV head is the slowest digit: an XCD's share then holds every sequence
-      it.b = (int)(L % (uint32_t)p.batch);
-      it.kvh = (int)(L / (uint32_t)p.batch);
-    } else {
+    if (VARLEN) { it.r = (int)L; it.kvh = it.b = 0; }   // (a stride; the first item is found above)
+    else {
+      it.r = (int)(L % (uint32_t)p.nb); L /= (uint32_t)p.nb;
       it.kvh = (int)(L % (uint32_t)p.hkv);
       it.b = (int)(L / (uint32_t)p.hkv);
     }
-    it.i = 0; it.subs_diag = 0; it.n = 0; it.qs = 0;
+    it.i = 0; it.subs_diag = 0; it.n = 0; it.qs = 0; it.first = 0; it.nblk = 0;
     return it;
   };
   const item_t stride = digits((uint32_t)item_step);
@@ -247,9 +298,16 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     item_t it = cur;
     it.chunk += stride.chunk; if (it.chunk >= p.chunks) { it.chunk -= p.chunks; ++it.r; }
     if (VARLEN) {
-      it.r += stride.r;       if (it.r >= p.nb) { it.r -= p.nb; ++it.b; }
-      it.b += stride.b;       if (it.b >= p.batch) { it.b -= p.batch; ++it.kvh; }
-      it.kvh += stride.kvh;
+      it.r += stride.r;
+      while (it.r >= it.nblk) {        // called for items that exist only: a sequence with the block follows
+        it.r -= it.nblk;
+        if (++it.b >= p.batch) { it.b = 0; ++it.kvh; }
+        enter_seq(it);
+        if (it.kvh >= p.hkv) {         // only if the lengths changed while the kernel ran: stay in bounds, and end
+          it.kvh = p.hkv - 1; it.r = 0;
+          it.nblk = it.nblk > 0 ? it.nblk : 1;
+        }
+      }
     } else {
       it.r += stride.r;       if (it.r >= p.nb) { it.r -= p.nb; ++it.kvh; }
       it.kvh += stride.kvh;   if (it.kvh >= p.hkv) { it.kvh -= p.hkv; ++it.b; }
@@ -259,25 +317,14 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     return it;
   };
   item_t it = stride, it1 = stride, it2 = stride;   // the current item, the next one, the one after (set below)
-  // Sequences of different lengths: an item exists when its query block starts inside its sequence.  raw2 is the
-  // position of it2 among this workgroup's item numbers; next_valid steps to the next existing item (finish_item
-  // is only ever called for item numbers of the launch, so the length look-up stays inside the array).
-  int n_items = n_raw, raw2 = 0;
+  int raw2 = 0;                        // position of it2 among this workgroup's items
+  const int n_items = n_raw;
   // keys of an item's sequence (one value for the whole launch unless the sequences have lengths of their own)
   auto keys_of = [&](const item_t& x) -> int { return VARLEN ? x.n : (int)p.N; };
-  auto exists = [&](const item_t& x) -> bool { return !VARLEN || (x.n > x.qs && (int64_t)x.i * p.B < x.n); };
   // position of the first row of Q/O
   auto qs_of = [&](const item_t& x) -> int64_t { return VARLEN ? (int64_t)x.qs : p.q_start; };
-  auto next_valid = [&](const item_t& cur, int& raw) -> item_t {
-    item_t x = cur;
-    while (raw + 1 < n_raw) {
-      ++raw;
-      x = next_item(x);
-      if (exists(x)) return x;
-    }
-    raw = n_raw;
-    return cur;                        // none left: never used as an item (the loop below counts the existing ones)
-  };
+  // the item after x, if there is one (else x: never used as an item)
+  auto next_valid = [&](const item_t& x, int& raw) -> item_t { return ++raw < n_items ? next_item(x) : x; };
 
   // ---- tile tables (explicit lists only) ----
   // Writes the table of an item from its list row: lane e holds entry e (j), n entries in all; the tiles of the
@@ -518,20 +565,15 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   };
 
   // ---- start of the stream: tables of the first two items, fills 0..NS-2, Q of the first item ----
-  it = digits((uint32_t)first_item);
-  finish_item(it);
   if (VARLEN) {
-    // count this workgroup's existing items, then set out on the first three
-    n_items = exists(it) ? 1 : 0;
-    {
-      item_t x = it;
-      for (int raw = 1; raw < n_raw; ++raw) { x = next_item(x); n_items += exists(x) ? 1 : 0; }
-    }
-    if (n_items == 0) return;
-    if (!exists(it)) it = next_valid(it, raw2);
+    it.chunk = v_chunk; it.r = v_r; it.kvh = v_kvh; it.b = v_b;
+    enter_seq(it);
+    finish_item(it);
     it1 = next_valid(it, raw2);
     it2 = next_valid(it1, raw2);
   } else {
+    it = digits((uint32_t)first_item);
+    finish_item(it);
     it1 = next_item(it);
     it2 = next_item(it1);
   }
@@ -1007,18 +1049,14 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
   int nw = p.tasks > 4 ? 8 : 4;
   if (nw == 8 && few_items_want_four_wavefronts(p, a)) nw = 4;
   p.chunks = (p.tasks + nw - 1) / nw;
-  // Sequences of different lengths: an odd count of block numbers per sequence (the extra one lies behind every
-  // sequence and is passed over), so that the power-of-two stride of a workgroup's item numbers walks through all
-  // block positions instead of returning to the same few, whose rows exist for different shares of the batch.
-  if (a.seq_len_dev && (p.nb & 1) == 0) ++p.nb;
   p.total_wg = (int64_t)a.batch * a.hkv * p.nb * p.chunks;
   int64_t per_xcd = (p.total_wg + 7) / 8;
-  p.xcd_split = 0; p.per_kvh = 0;
+  p.xcd_split = 0;
   if (a.seq_len_dev && a.hkv <= 2) {   // (with four KV heads the contiguous halves measure the same or 1-2 % better)
     p.xcd_split = 8 / a.hkv;
-    p.per_kvh = (int64_t)a.batch * p.nb * p.chunks;
-    per_xcd = (p.per_kvh + p.xcd_split - 1) / p.xcd_split;
+    per_xcd = ((int64_t)a.batch * p.nb * p.chunks + p.xcd_split - 1) / p.xcd_split;
   }
+  p.b_shift = (p.B & (p.B - 1)) == 0 ? __builtin_ctz((unsigned)p.B) : -1;
   if (per_xcd * 8 > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
   p.per_xcd = (int32_t)per_xcd;
   // chaining keeps the list row of the item after next in 63 lanes and two tile tables in LDS

@@ -81,3 +81,29 @@ def test_lengths_outside_the_padding_are_clamped_and_many_sequences_share_one_la
                                  oracle_pattern(pat))
         assert np.abs(o[b:b + 1, :, :n].double().cpu().numpy() - oo).max() <= TOL_O["bf16"]
         assert np.abs(lse[b:b + 1, :, :n].double().cpu().numpy() - olse).max() <= TOL_LSE
+
+
+@pytest.mark.parametrize("B,hq,hkv,d,batch,hi", [
+    (64, 8, 1, 64, 65, 700),        # one KV head: the XCDs take its items in turn; the 65th sequence in a second pass
+    (128, 6, 3, 128, 70, 400),      # an XCD's share crosses from one KV head to the next
+    (192, 8, 8, 128, 9, 900),       # a block size that is no power of two
+    (64, 16, 2, 128, 130, 200),     # mostly empty sequences
+])
+def test_every_block_of_every_mix_of_lengths_is_done_once(B, hq, hkv, d, batch, hi):
+    # only blocks that exist are numbered: lengths around block edges, empty ones first, last and in runs
+    pat = pa.Pattern(B, 2, 1)
+    rng = np.random.default_rng(83)
+    lens = rng.choice([0, 0, 0, 1, B - 1, B, B + 1, 2 * B, hi], size=batch)
+    lens[0] = lens[-1] = 0
+    lens[batch // 2] = hi
+    q, k, v = (t.cuda() for t in synth.qkv(batch, hq, hkv, hi, d, "bf16", seed=84))
+    cnt, idx, _ = pa.mask_build(pat, hi)
+    o = torch.full_like(q, 7.0)
+    lse = torch.full((batch, hq, hi), -3.0, dtype=torch.float32, device="cuda")
+    pa.prefill_varlen(pat, cnt, idx, q, k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"), o=o, lse=lse)
+    o1, l1 = pa.prefill(pat, cnt, idx, q, k, v)          # causal: a row does not depend on the keys after it
+    beyond = torch.arange(hi, device="cuda")[None, :] >= torch.tensor(lens, device="cuda")[:, None]
+    o1.masked_fill_(beyond[:, None, :, None], 7.0)
+    l1.masked_fill_(beyond[:, None, :], -3.0)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o1) and torch.equal(lse, l1)
