@@ -77,8 +77,8 @@ struct bf16_params {
   const int32_t* kv_cnt; const int32_t* kv_idx;
   int32_t max_k, nb, B, hq, hkv, G, dense, batch;
   int32_t subs;      // 64-key tiles per block
-  int32_t tasks;     // G * B / 32
-  int32_t chunks;    // workgroups per (batch, kv head, query block)
+  int32_t chunks;    // work items of a whole query block (of one sequence and KV head)
+  int32_t c_last, n_items;   // ... of the last block, and of all blocks (sequences of one length)
   int32_t per_xcd;   // work items per XCD partition
   int32_t xcd_split; // sequences of different lengths, one or two KV heads: XCDs that share a KV head's items (else 0)
   int32_t b_shift;   // log2 of B, or -1
@@ -133,6 +133,22 @@ __device__ __forceinline__ void wait_vmcnt() {   // s_waitcnt vmcnt(N) only
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// Work items of one sequence and KV head whose queries qs .. n-1 lie in nblk blocks from block `first` on.  A query block
+// has G tasks for each of its 32-query slices that holds a query of the call, nw of them to an item: the first block
+// of a piece that starts inside it and a ragged last one take fewer items than a whole one.  (Counted as whole ones, a
+// piece of 2000 rows from position 30001, 28 query heads on 4, made 264 items on 256 compute units, a second round for
+// eight of them: 48.2 -> 32.1 us.)
+struct seq_items { int c_last, n; };
+__host__ __device__ __forceinline__ seq_items items_of_sequence(int n, int qs, int first, int nblk, int B, int G, int nw) {
+  seq_items s = {0, 0};
+  if (nblk <= 0) return s;
+  const int skipped = (qs - first * B) / QW, last = (n - 1 - (first + nblk - 1) * B) / QW;
+  s.c_last = (G * (last + 1 - (nblk == 1 ? skipped : 0)) + nw - 1) / nw;
+  s.n = s.c_last;
+  if (nblk > 1) s.n += (nblk - 2) * ((G * (B / QW) + nw - 1) / nw) + (G * (B / QW - skipped) + nw - 1) / nw;
+  return s;
+}
+
 // DENSE: the implicit list {0..i} instead of a block list.  CHAIN: the launch chains work items in persistent
 // workgroups (two half-size tile tables, list rows prefetched); otherwise one workgroup per item.  VARLEN: every
 // sequence of the batch has its own length, read from device memory; the work items are numbered as if all had the
@@ -167,13 +183,12 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, and the compiler knows it
   const int ln = lane & 31, hh = lane >> 5;
-  const int slices = p.B / QW;
   // Which task of a work item this wavefront takes.  Wavefronts w and w+4 share a SIMD; the tasks of the lower
   // half of a query block stop one diagonal tile before those of the upper half.  With four 32-query slices per
   // head (blocks of 128 keys) tasks w and w+4 are the same slice of two heads, and whole SIMDs would idle in the
   // item's last step while the others carry two wavefronts; the tasks are dealt so that every SIMD gets one
   // wavefront of either kind (wavefront w: head (w>>1)&1, slice (w&1) + 2(w>>2)).
-  const int wtask = (NW == 8 && slices == 4) ? ((wave & 1) | (((wave >> 2) & 1) << 1) | (((wave >> 1) & 1) << 2)) : wave;
+  const int wave4 = NW == 8 ? ((wave & 1) | (((wave >> 2) & 1) << 1) | (((wave >> 1) & 1) << 2)) : wave;
 
   // ---- this workgroup's work items: item k is number xcd*per_xcd + cuslot + nslots*k of the launch, so that
   // the workgroups of one XCD (one L2) work on neighbouring query blocks at any time ----
@@ -184,7 +199,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   // Sequences of different lengths: keys and first query of sequence b (values outside the context or the slab of Q/O
   // are clamped), and how many query blocks it has, counted from the one of its first query.
   auto block_of = [&](int pos) -> int { return p.b_shift >= 0 ? pos >> p.b_shift : pos / p.B; };
-  struct seq_t { int n, qs, first, nblk; };
+  struct seq_t { int n, qs, first, nblk; seq_items it; };
   auto seq_of = [&](int b) -> seq_t {
     seq_t q;
     q.qs = 0;
@@ -198,16 +213,17 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     q.n = q.qs + (len < 0 ? 0 : (len > room ? room : len));
     q.first = block_of(q.qs);
     q.nblk = q.n > q.qs ? block_of(q.n - 1) - q.first + 1 : 0;
+    q.it = items_of_sequence(q.n, q.qs, q.first, q.nblk, p.B, p.G, NW);
     return q;
   };
-  int v_kvh = 0, v_chunk = 0, v_b = 0, v_r = 0;          // VARLEN: the first item
+  int v_kvh = 0, v_b = 0, v_q = 0;          // VARLEN: the first item
   if (VARLEN) {
     // Only the query blocks that exist are numbered, so that every workgroup gets the same number of items whatever the
     // mix of lengths (numbered as if all sequences had the padded length, the fullest of 256 workgroups got 20 items
     // where 17 were the mean, at 32 pieces of 1 .. 2048 rows: 528 -> 501 us; 32 prompts of 300 .. 8192: 1447 -> 1369 us).  64 sequences at a time, one
-    // per lane: how many blocks they have, and a prefix sum to find the first item's sequence.
-    auto prefix = [&](int base, int& own) -> int {       // blocks of the sequences base .. base + lane
-      own = base + lane < p.batch ? seq_of(base + lane).nblk : 0;
+    // per lane: how many items they have, and a prefix sum to find the first item's sequence.
+    auto prefix = [&](int base, int& own) -> int {       // items of the sequences base .. base + lane
+      own = base + lane < p.batch ? seq_of(base + lane).it.n : 0;
       int sum = own;
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
@@ -216,9 +232,8 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       }
       return sum;
     };
-    int blocks = 0, own = 0;                             // query blocks of all sequences, for one KV head
-    for (int base = 0; base < p.batch; base += 64) blocks += __builtin_amdgcn_readlane(prefix(base, own), 63);
-    const int per_kvh = blocks * p.chunks;               // (fits 32 bits: the host checked the padded count)
+    int per_kvh = 0, own = 0;                            // items of all sequences (fits 32 bits: the host checked the padded count)
+    for (int base = 0; base < p.batch; base += 64) per_kvh += __builtin_amdgcn_readlane(prefix(base, own), 63);
     if (per_kvh == 0) return;
     int m0;                                              // the first item's number among its KV head's
     if (p.xcd_split > 1) {
@@ -238,17 +253,16 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       m0 -= v_kvh * per_kvh;
     }
     if (n_raw == 0) return;
-    v_r = __builtin_amdgcn_readfirstlane(m0 / p.chunks);
-    v_chunk = m0 - v_r * p.chunks;
+    v_q = __builtin_amdgcn_readfirstlane(m0);
     for (int base = 0; base < p.batch; base += 64) {
       const int sum = prefix(base, own), all = __builtin_amdgcn_readlane(sum, 63);
-      if (v_r < all) {
-        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(sum > v_r));   // the first lane that reaches beyond it
+      if (v_q < all) {
+        const int at = __builtin_ctzll(__builtin_amdgcn_ballot_w64(sum > v_q));   // the first lane that reaches beyond it
         v_b = base + at;
-        v_r -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(own, at);
+        v_q -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(own, at);
         break;
       }
-      v_r -= all;
+      v_q -= all;
     }
   } else {
     int64_t lim = p.total_wg - (int64_t)xcd * p.per_xcd;
@@ -261,55 +275,76 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   constexpr int PHYS = TILE_CAP / 2;   // paged: entry e's first pool row sits at s_tile[PHYS + e]
   static_assert(!PAGED || (CHAIN && !DENSE), "paged caches: explicit lists, chained items");
 
-  // Items are numbered L = ((b*hkv + kvh)*nb + r)*chunks + chunk with r counting query blocks from the last one
+  // Items are numbered L = (b*hkv + kvh)*n_items + q with q counting the items of a sequence from the last query block
   // down (longest rows first, which matters for the dense list); with sequences of different lengths the KV head is
-  // the slowest digit and sequence b has nblk blocks, so that the contiguous share of an XCD spans all sequences (one
-  // KV head each when there are eight) and the XCDs finish together whatever the mix of lengths.  The first item is
-  // decoded by division, the following ones by adding the stride nslots digit by digit with carries: all scalar, no
-  // division in the loop.
-  struct item_t { int chunk, r, kvh, b, i, subs_diag, n, qs, first, nblk; };   // n: keys (= tokens) of the item's sequence; qs:
-                                                                               // its first query, in block `first`
+  // the slowest digit and every sequence has a count of its own, so that the contiguous share of an XCD spans all
+  // sequences (one KV head each when there are eight) and the XCDs finish together whatever the mix of lengths.  The
+  // first item is found by division, the following ones by adding the stride nslots digit by digit with carries.
+  struct item_t { int q, kvh, b, chunk, i, sl0, nsl, subs_diag;     // sl0, nsl: the block's slices that hold queries of the call
+                  int n, qs, first, nblk, c_last, n_items; };       // VARLEN: the sequence (keys, first query, its block, blocks, items)
   auto enter_seq = [&](item_t& it) {   // uniform over the workgroup: scalar loads
     const seq_t q = seq_of(it.b);
-    it.n = q.n; it.qs = q.qs; it.first = q.first; it.nblk = q.nblk;
+    it.n = q.n; it.qs = q.qs; it.first = q.first; it.nblk = q.nblk; it.c_last = q.it.c_last; it.n_items = q.it.n;
   };
+  // counts of slices and items are powers of two but for ragged blocks of 128 keys or more and unusual head groups
+  auto quot = [](unsigned x, unsigned y) -> int { return (int)((y & (y - 1)) == 0 ? x >> __builtin_ctz(y) : x / y); };
   auto finish_item = [&](item_t& it) {
-    it.i = (VARLEN ? it.first + it.nblk : p.i0 + p.nb) - 1 - it.r;
+    const int c_last = VARLEN ? it.c_last : p.c_last;
+    int r = 0;                         // query blocks behind the item's
+    it.chunk = it.q;
+    if (it.q >= c_last) {
+      const int rest = it.q - c_last, blocks = quot(rest, p.chunks);
+      r = 1 + blocks;
+      it.chunk = rest - blocks * p.chunks;
+    }
+    it.i = (VARLEN ? it.first + it.nblk : p.i0 + p.nb) - 1 - r;
+    const int before = (VARLEN ? it.qs : (int)p.q_start) - it.i * p.B, keys = (VARLEN ? it.n : (int)p.N) - it.i * p.B;
+    it.sl0 = before > 0 ? before / QW : 0;
+    it.nsl = ((keys < p.B ? keys : p.B) + QW - 1) / QW - it.sl0;
+    if (it.nsl < 1) it.nsl = 1;
     // tiles of the diagonal block needed by any wavefront of the item
     int last_task = it.chunk * NW + NW - 1;
-    if (last_task > p.tasks - 1) last_task = p.tasks - 1;
-    const int max_sl = (last_task / slices > (it.chunk * NW) / slices) ? slices - 1 : last_task % slices;
+    if (last_task > p.G * it.nsl - 1) last_task = p.G * it.nsl - 1;
+    const int g_last = quot(last_task, it.nsl);
+    const int max_sl = it.sl0 + (g_last * it.nsl > it.chunk * NW ? it.nsl - 1 : last_task - g_last * it.nsl);
     it.subs_diag = (max_sl * QW + QW - 1) / KT + 1;
+  };
+  // this wavefront's task of an item: query head of the group and slice; false (and 0, 0): none
+  auto task_of = [&](const item_t& it, int& g, int& sl) -> bool {
+    const int task = it.chunk * NW + (it.nsl == 4 ? wave4 : wave);
+    const bool act = task < p.G * it.nsl;
+    g = act ? quot(task, it.nsl) : 0;
+    sl = act ? it.sl0 + task - g * it.nsl : 0;
+    return act;
   };
   auto digits = [&](uint32_t L) -> item_t {
     item_t it;
-    it.chunk = (int)(L % (uint32_t)p.chunks); L /= (uint32_t)p.chunks;
-    if (VARLEN) { it.r = (int)L; it.kvh = it.b = 0; }   // (a stride; the first item is found above)
+    it.b = it.kvh = 0;
+    if (VARLEN) it.q = (int)L;         // (a stride; the first item is found above)
     else {
-      it.r = (int)(L % (uint32_t)p.nb); L /= (uint32_t)p.nb;
+      it.q = (int)(L % (uint32_t)p.n_items); L /= (uint32_t)p.n_items;
       it.kvh = (int)(L % (uint32_t)p.hkv);
       it.b = (int)(L / (uint32_t)p.hkv);
     }
-    it.i = 0; it.subs_diag = 0; it.n = 0; it.qs = 0; it.first = 0; it.nblk = 0;
+    it.chunk = it.i = it.sl0 = it.nsl = it.subs_diag = it.n = it.qs = it.first = it.nblk = it.c_last = it.n_items = 0;
     return it;
   };
   const item_t stride = digits((uint32_t)item_step);
   auto next_item = [&](const item_t& cur) -> item_t {
     item_t it = cur;
-    it.chunk += stride.chunk; if (it.chunk >= p.chunks) { it.chunk -= p.chunks; ++it.r; }
+    it.q += stride.q;
     if (VARLEN) {
-      it.r += stride.r;
-      while (it.r >= it.nblk) {        // called for items that exist only: a sequence with the block follows
-        it.r -= it.nblk;
+      while (it.q >= it.n_items) {     // called for items that exist only: a sequence with the item follows
+        it.q -= it.n_items;
         if (++it.b >= p.batch) { it.b = 0; ++it.kvh; }
         enter_seq(it);
         if (it.kvh >= p.hkv) {         // only if the lengths changed while the kernel ran: stay in bounds, and end
-          it.kvh = p.hkv - 1; it.r = 0;
-          it.nblk = it.nblk > 0 ? it.nblk : 1;
+          it.kvh = p.hkv - 1; it.q = 0;
+          if (it.nblk < 1) it.nblk = it.c_last = it.n_items = 1;
         }
       }
     } else {
-      it.r += stride.r;       if (it.r >= p.nb) { it.r -= p.nb; ++it.kvh; }
+      if (it.q >= p.n_items) { it.q -= p.n_items; ++it.kvh; }
       it.kvh += stride.kvh;   if (it.kvh >= p.hkv) { it.kvh -= p.hkv; ++it.b; }
       it.b += stride.b;
     }
@@ -520,9 +555,8 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   u32x4 qraw[NC];
   bf16x8 qf[NC];
   auto load_q = [&](const item_t& it) {
-    const int task = it.chunk * NW + wtask;
-    const bool act = task < p.tasks;
-    const int g = act ? task / slices : 0, sl = act ? task % slices : 0;
+    int g, sl;
+    const bool act = task_of(it, g, sl);
     const int64_t tok0 = (int64_t)it.i * p.B + sl * QW + (ln & ~3);          // first row of this lane's quad
     const __bf16* qbase = p.q + (((int64_t)it.b * p.hq + it.kvh * p.G + g) * p.q_rows + (tok0 - qs_of(it))) * D
                           + (D / 2) * hh + 8 * (lane & 3);
@@ -566,17 +600,15 @@ void pa_prefill_bf16_kernel(bf16_params p) {
 
   // ---- start of the stream: tables of the first two items, fills 0..NS-2, Q of the first item ----
   if (VARLEN) {
-    it.chunk = v_chunk; it.r = v_r; it.kvh = v_kvh; it.b = v_b;
+    it.q = v_q; it.kvh = v_kvh; it.b = v_b;
     enter_seq(it);
     finish_item(it);
-    it1 = next_valid(it, raw2);
-    it2 = next_valid(it1, raw2);
   } else {
     it = digits((uint32_t)first_item);
     finish_item(it);
-    it1 = next_item(it);
-    it2 = next_item(it1);
   }
+  it1 = next_valid(it, raw2);
+  it2 = next_valid(it1, raw2);
   if (!DENSE) {
     if (wave == 0) {
       table_from_memory(0, it);
@@ -664,10 +696,8 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   for (int k = 0; k < n_items; ++k) {
     const bool more = k + 1 < n_items;
     // ---- per-item geometry ----
-    const int task = it.chunk * NW + wtask;
-    const bool active = task < p.tasks;
-    const int g = active ? task / slices : 0;
-    const int sl = active ? task % slices : 0;
+    int g, sl;
+    const bool active = task_of(it, g, sl);
     const int h = it.kvh * p.G + g;
     q_in_blk = sl * QW;
     const int64_t q0 = (int64_t)it.i * p.B + q_in_blk;
@@ -978,7 +1008,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       if (active && tok < keys_of(it) && tok >= qs_of(it) && p.lse && hh == 0)
         p.lse[((int64_t)it.b * p.hq + h) * p.q_rows + (tok - qs_of(it))] = (m_run + log2f(ltot)) * 0.69314718055994530942f;
     }
-    it = it1; it1 = it2; it2 = VARLEN ? next_valid(it2, raw2) : next_item(it2);
+    it = it1; it1 = it2; it2 = next_valid(it2, raw2);
   }
   // asynchronous copies must not outlive the workgroup's claim on its LDS
   wait_vmcnt<0>();
@@ -1015,6 +1045,15 @@ int launch(const bf16_params& p, hipStream_t stream) {
   return p.chain ? launch_as<D, NW, NS, false, true, false>(p, stream) : launch_as<D, NW, NS, false, false, false>(p, stream);
 }
 
+// Work items of a sequence and KV head (at most, if only the device knows the lengths) with workgroups of nw wavefronts
+seq_items host_items(const bf16_params& p, int nw) {
+  if (p.seq_len) {
+    const int chunks = (p.G * (p.B / QW) + nw - 1) / nw;
+    return {chunks, p.nb * chunks};
+  }
+  return items_of_sequence((int)p.N, (int)p.q_start, p.i0, p.nb, p.B, p.G, nw);
+}
+
 // Whether a launch of few work items is better cut into workgroups of four wavefronts: when there is a compute unit for
 // every half-size item.  A lone wavefront per SIMD takes about 0.6 of the time for a step that two take each.
 // Eight / four wavefronts, us, 32 query heads on 8, blocks of 64 keys: head_dim 128 N = 200 15.2 / 12.8, N = 1000
@@ -1023,8 +1062,8 @@ int launch(const bf16_params& p, hipStream_t stream) {
 bool few_items_want_four_wavefronts(const bf16_params& p, const pa_prefill_args& a) {
   int n_cu = 0;
   pa_current_device(nullptr, &n_cu);
-  const int64_t per_chunk = (int64_t)a.batch * a.hkv * p.nb, slots = n_cu >= 8 ? n_cu / 8 : 1;
-  return (per_chunk * ((p.tasks + 3) / 4) + 7) / 8 <= slots;      // an eighth of the items per XCD
+  const int64_t items = (int64_t)a.batch * a.hkv * host_items(p, 4).n, slots = n_cu >= 8 ? n_cu / 8 : 1;
+  return (items + 7) / 8 <= slots;                   // an eighth of the items per XCD
 }
 
 }  // namespace
@@ -1045,16 +1084,18 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
   p.block_table = a.block_table; p.table_stride = a.table_stride; p.n_pages = (int32_t)a.n_pages;
   const int64_t tasks = (int64_t)p.G * p.B / QW;
   if (tasks > (1 << 20)) return POWATTN_UNSUPPORTED;
-  p.tasks = (int32_t)tasks;
-  int nw = p.tasks > 4 ? 8 : 4;
+  if ((int64_t)p.nb * tasks > 0x7fffffffLL) return POWATTN_UNSUPPORTED;   // the items of a sequence are counted in 32 bits
+  int nw = tasks > 4 ? 8 : 4;
   if (nw == 8 && few_items_want_four_wavefronts(p, a)) nw = 4;
-  p.chunks = (p.tasks + nw - 1) / nw;
-  p.total_wg = (int64_t)a.batch * a.hkv * p.nb * p.chunks;
+  p.chunks = (int32_t)((tasks + nw - 1) / nw);
+  const seq_items si = host_items(p, nw);
+  p.c_last = si.c_last; p.n_items = si.n;
+  p.total_wg = (int64_t)a.batch * a.hkv * si.n;
   int64_t per_xcd = (p.total_wg + 7) / 8;
   p.xcd_split = 0;
   if (a.seq_len_dev && a.hkv <= 2) {   // (with four KV heads the contiguous halves measure the same or 1-2 % better)
     p.xcd_split = 8 / a.hkv;
-    per_xcd = ((int64_t)a.batch * p.nb * p.chunks + p.xcd_split - 1) / p.xcd_split;
+    per_xcd = ((int64_t)a.batch * si.n + p.xcd_split - 1) / p.xcd_split;
   }
   p.b_shift = (p.B & (p.B - 1)) == 0 ? __builtin_ctz((unsigned)p.B) : -1;
   if (per_xcd * 8 > 0x7fffffffLL) return POWATTN_UNSUPPORTED;

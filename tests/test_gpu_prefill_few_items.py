@@ -30,3 +30,20 @@ def test_same_rows_with_four_and_eight_wavefronts(B, hq, hkv, d, n, many):
     oo, olse = orc.attention(*(synth.to_numpy_storage(t) for t in (q, k, v)), oracle_pattern(pat))
     assert np.abs(o1.double().cpu().numpy() - oo).max() <= TOL_O["bf16"]
     assert np.abs(l1.double().cpu().numpy() - olse).max() <= TOL_LSE
+
+
+@pytest.mark.parametrize("B,hq,hkv,d,q_start,q_len", [
+    (64, 28, 4, 128, 33, 700),      # the first block holds one slice, the last one query
+    (256, 7, 1, 64, 100, 150),      # one block only: slices 3 .. 7, no power of two of them
+    (256, 12, 2, 128, 672, 450),    # first block: 3 slices, last one: 4, the second item of either half empty
+    (128, 32, 8, 128, 127, 2),      # two blocks with one query each
+])
+def test_partial_blocks_take_fewer_items(B, hq, hkv, d, q_start, q_len):
+    pat = pa.Pattern(B, 3, 1)
+    n = q_start + q_len
+    q, k, v = (t.cuda() for t in synth.qkv(5, hq, hkv, n, d, "bf16", seed=80))
+    cnt, idx, _ = pa.mask_build(pat, n)
+    want_o, want_l = pa.prefill(pat, cnt, idx, q, k, v)
+    o, lse = pa.prefill_chunk(pat, cnt, idx, q[:, :, q_start:].contiguous(), k, v, q_start)
+    torch.cuda.synchronize()
+    assert torch.equal(o, want_o[:, :, q_start:]) and torch.equal(lse, want_l[:, :, q_start:])
