@@ -831,7 +831,12 @@ int pa_launch_backward_bf16(const pa_backward_args& a) {
   // eight wavefronts per workgroup when a query block has that many tasks and blocks of 128 keys or more; at
   // blocks of 64 keys four (two workgroups per compute unit that are not in step with each other: 4-7 % faster
   // at configuration 2's shape than one workgroup of eight)
-  const int nwq = (p.tasks > 4 && p.B >= 128) ? 8 : 4;
+  // ... and where there is a compute unit for every workgroup of four (gradients of one sequence, eight / four, us:
+  // block 128, 32 heads on 8, N = 500 88.0 / 79.9, N = 1000 105.2 / 95.9; block 256, 8 on 8, N = 2000 114.9 / 99.8)
+  int n_cu = 1;
+  pa_current_device(nullptr, &n_cu);
+  const bool few = (int64_t)a.batch * a.hkv * a.nb * ((p.tasks + 3) / 4) <= n_cu;
+  const int nwq = (p.tasks > 4 && p.B >= 128 && !few) ? 8 : 4;
   p.chunks = (p.tasks + nwq - 1) / nwq;
   p.sink_blocks = a.pat.sink < a.nb ? a.pat.sink : a.nb;
   // A sink block's column is cut into parts as long as the longest ordinary column, at most PART blocks: on a short
