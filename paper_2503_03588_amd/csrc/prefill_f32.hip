@@ -51,6 +51,7 @@ void pa_prefill_f32_kernel(f32_params p) {
   extern __shared__ __attribute__((aligned(16))) float s_o[];   // [NW][QR][D + 4], then the maxima and sums [NW][QR]
   float* s_m = s_o + NW * QR * o_stride(D);
   float* s_l = s_m + NW * QR;
+  __shared__ int s_some[NW];                // whether the wavefront's part held any key
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -103,11 +104,13 @@ void pa_prefill_f32_kernel(f32_params p) {
   int left = (int)(hi - lo);
   if (ct >= 64) row_e = list_lanes(ct & ~63);
   const int last = (int)(p.N - 1);
+  bool any = false;                                            // a tile to attend: a block's first one holds a key of every query
   auto next_key0 = [&]() -> int {                              // first key of the next tile, or -1: nothing to attend
     const int j = __builtin_amdgcn_readlane(row_e, ct & 63);
     const bool some = left > 0 && j >= 0 && (j < qb || (j == qb && cs < diag_tiles));
     int key0 = some ? j * p.B + 16 * cs : -1;
     if (key0 > last) key0 = -1;                                // (later query tiles of a last block that is not full)
+    any = any || key0 >= 0;
     --left;
     if (++cs == tpb) {
       cs = 0;
@@ -243,6 +246,7 @@ void pa_prefill_f32_kernel(f32_params p) {
   }
 
   // ---- the wavefronts' partials meet in LDS ----
+  if (lane == 0) s_some[wave] = any;
 #pragma unroll
   for (int m = 0; m < MQ; ++m) {
     const int row = wave * QR + 16 * m + ln;
@@ -257,6 +261,9 @@ void pa_prefill_f32_kernel(f32_params p) {
             f32x4{O[m][4 * x][r], O[m][4 * x + 1][r], O[m][4 * x + 2][r], O[m][4 * x + 3][r]};
   }
   __syncthreads();
+  int some = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) some |= s_some[w];
   for (int e = tid; e < QR * (D / 4); e += 64 * NW) {
     const int row = e / (D / 4), d4 = e % (D / 4);
     float M = -INFINITY;
@@ -267,7 +274,7 @@ void pa_prefill_f32_kernel(f32_params p) {
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float lw = s_l[w * QR + row];
-      const float wt = lw > 0.f ? __builtin_amdgcn_exp2f(s_m[w * QR + row] - M) : 0.f;
+      const float wt = lw > 0.f ? __builtin_amdgcn_exp2f(s_m[w * QR + row] - M) : 0.f;   // (0 times a sum that is NaN is NaN)
       L = fmaf(wt, lw, L);
       const f32x4 ow = *reinterpret_cast<const f32x4*>(s_o + (w * QR + row) * o_stride(D) + 4 * d4);
 #pragma unroll
@@ -275,7 +282,8 @@ void pa_prefill_f32_kernel(f32_params p) {
     }
     const int64_t tok = q0 + row;
     if (tok >= p.N) continue;
-    const float inv = L > 0.f ? 1.0f / L : 0.f;                // a row whose list is empty: o = 0, lse = -inf
+    // a row whose list is empty: o = 0, lse = -inf; one whose scores are all -inf: 0 * (1 / 0), no number, as softmax has it
+    const float inv = some ? 1.0f / L : 0.f;
     const int64_t at = ((int64_t)b * p.hq + h) * p.N + tok;
     *reinterpret_cast<f32x4*>(p.o + at * D + 4 * d4) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
     if (p.lse && d4 == 0) p.lse[at] = (M + log2f(L)) * 0.69314718055994530942f;

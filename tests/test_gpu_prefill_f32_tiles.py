@@ -5,8 +5,9 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import powattn_oracle as orc
 from paper_2503_03588_amd import binding as pa
-from gpu_util import check_prefill
+from gpu_util import check_prefill, oracle_pattern
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,28 @@ def test_prefill_f32_list_order_and_empty_row():
     assert float((o[rows] - ref).abs().max()) <= 1e-5
     assert float((lse[rows] - torch.logsumexp(s[rows], -1)).abs().max()) <= 1e-3
     assert float(o[~rows].abs().max()) == 0.0 and bool(torch.isneginf(lse[~rows]).all())
+
+
+@pytest.mark.parametrize("at", [0, 383, 640])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("hq", [1, 16])                      # 16 and 64 queries to a workgroup
+def test_prefill_f32_non_finite_keys_reach_the_rows_that_attend_them(hq, bad, at):
+    """A key that is no number, or so large that its score is one of the infinities: the rows that softmax leaves without
+    a result are the rows that have none here, whichever wavefront held the key (key 0: row 0 attends nothing else)."""
+    pat = pa.Pattern(64, 2, 1)
+    n, d = 641, 64
+    gen = torch.Generator().manual_seed(11)
+    q, k, v = (torch.randn((1, h, n, d), generator=gen) for h in (hq, 1, 1))
+    k[0, 0, at, 3] = bad
+    q[0, 0, -1, 3] = 1.0                                     # (the only row that attends key 640: its score is +inf)
+    cnt, idx, _ = pa.mask_build(pat, n)
+    o, lse = pa.prefill(pat, cnt, idx, q.cuda(), k.cuda(), v.cuda())
+    o, lse = o.cpu().double()[0], lse.cpu().double()[0]
+    keep = torch.from_numpy(orc.token_mask(n, oracle_pattern(pat)))
+    s = (q[0].double() @ k[0, 0].double().T) / d ** 0.5
+    s = s.masked_fill(~keep, -float("inf"))
+    ref = torch.softmax(s, -1) @ v[0, 0].double()
+    none = torch.isnan(ref).all(-1)
+    assert int(none.sum()) > 0 and torch.equal(torch.isnan(o).all(-1), none) and torch.equal(torch.isnan(o).any(-1), none)
+    assert bool(((o - ref).abs() <= 1e-5)[~none].all())
+    assert bool(((lse - torch.logsumexp(s, -1)).abs() <= 1e-3)[~none].all())
