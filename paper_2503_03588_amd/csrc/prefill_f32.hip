@@ -47,6 +47,11 @@ void pa_prefill_f32_kernel(f32_params p) {
   constexpr int NV = D / 64;                // 16-byte pieces of a V row per lane; each feeds four tiles of O^T
   constexpr int QR = 16 * MQ;               // query rows of the workgroup
   constexpr int TS = MQ * D <= 128 ? 4 : 2; // 16-key tiles per step (scores held at a time)
+  // Sums a score is formed in (one for every CH-th head element), added up at the end.  With a single sum of D products the
+  // outputs were up to 1.6 times as far from 64 bits (2-norm; 2.3 times, largest difference) as those of four short ones
+  // per lane in plain multiply-adds; with these 0.44 .. 0.88 times (0.42 .. 0.94).  Four 16-row tiles at head_dim 64 have no
+  // registers for more than two (four spill 40: 52.8 -> 57.3 us at 8 heads, N = 4096), and reach long sequences only.
+  constexpr int CH = MQ == 4 ? 2 : 4;
   constexpr int LA = MQ * D <= 64 ? 4 : MQ * D <= 128 ? 2 : 1;   // tiles loaded ahead
   extern __shared__ __attribute__((aligned(16))) float s_o[];   // [NW][QR][D + 4], then the maxima and sums [NW][QR]
   float* s_m = s_o + NW * QR * o_stride(D);
@@ -175,15 +180,22 @@ void pa_prefill_f32_kernel(f32_params p) {
 #pragma unroll
         for (int m = 0; m < MQ; ++m) S[m][i] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       } else {
+        f32x4 part[CH][MQ];
 #pragma unroll
-        for (int m = 0; m < MQ; ++m) S[m][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < CH * MQ; ++x) part[x / MQ][x % MQ] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NK; ++c)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int m = 0; m < MQ; ++m)
-              S[m][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][c][e], qf[m][c][e], S[m][i], 0, 0, 0);
+              part[e % CH][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][c][e], qf[m][c][e], part[e % CH][m], 0, 0, 0);
+#pragma unroll
+        for (int m = 0; m < MQ; ++m)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            S[m][i][r] = CH == 4 ? (part[0][m][r] + part[1][m][r]) + (part[2 % CH][m][r] + part[3 % CH][m][r])
+                                 : part[0][m][r] + part[1][m][r];
         if ((int64_t)key0[i] + 15 > q0) {                      // causality: a tile that reaches the workgroup's queries
 #pragma unroll
           for (int m = 0; m < MQ; ++m)
