@@ -203,6 +203,8 @@ int powattn_prefill_chunk_paged(const powattn_pattern* pattern,
  *   d_q_start         device int32 [batch], >= 0 (clamped into [0, table_stride*block])
  *   d_q_len           device int32 [batch], 0 <= d_q_len[b] <= q_rows (clamped so that the context
  *                     d_q_start[b] + d_q_len[b] stays inside the table); 0: the sequence is skipped
+ *                     Both arrays are read several times: like the tensors, they must not change
+ *                     until the launch has finished
  *   q_rows            rows per (sequence, head) slab of q/o/lse, 1 <= q_rows <= table_stride*block
  *   k_pages, v_pages, d_block_table, table_stride, n_pages   as for powattn_prefill_chunk_paged;
  *                     positions 0 .. d_q_start[b]+d_q_len[b]-1 of sequence b must be filled in
@@ -237,7 +239,8 @@ int powattn_prefill_batch_paged(const powattn_pattern* pattern,
  *   k, v           device [batch, n_kv_heads, padded_len, head_dim]
  *   lse            device float [batch, n_q_heads, padded_len] or NULL
  *   d_seq_len      device int32 [batch], 0 <= seq_len[b] <= padded_len (0: nothing
- *                  to do; values outside that range are clamped into it by the kernel)
+ *                  to do; values outside that range are clamped into it by the kernel).  Read
+ *                  several times: like the tensors, it must not change until the launch has finished
  *   d_kv_cnt, d_kv_idx, max_k   lists covering ceil(padded_len / block) rows
  *   dtype          POWATTN_BF16 only; head_dim 64 or 128; block a multiple of 64, at most 1024
  * Work is dealt to the compute units by position in the padded batch, not by

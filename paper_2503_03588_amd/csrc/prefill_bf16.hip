@@ -52,6 +52,7 @@
 #include <stdlib.h>
 #include <type_traits>
 #include "common.h"
+#include "items.h"
 
 
 namespace {
@@ -69,7 +70,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 64;          // keys per staged tile
-constexpr int QW = 32;          // query tokens per wavefront
+constexpr int QW = PA_QW;       // query tokens per wavefront
 constexpr float RESCALE_TAU = 8.0f;   // running max is only raised when exceeded by 2^8 (see softmax below)
 
 struct bf16_params {
@@ -82,6 +83,7 @@ struct bf16_params {
   int32_t per_xcd;   // work items per XCD partition
   int32_t xcd_split; // sequences of different lengths, one or two KV heads: XCDs that share a KV head's items (else 0)
   int32_t b_shift;   // log2 of B, or -1
+  int32_t i_max;     // last query block of the context: (N - 1) / B
   int32_t chain;     // items may be chained in persistent workgroups
   int64_t total_wg;
   int64_t N;         // keys in the context: query q_start + r attends keys <= q_start + r, all of them < N
@@ -133,22 +135,6 @@ __device__ __forceinline__ void wait_vmcnt() {   // s_waitcnt vmcnt(N) only
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// Work items of one sequence and KV head whose queries qs .. n-1 lie in nblk blocks from block `first` on.  A query block
-// has G tasks for each of its 32-query slices that holds a query of the call, nw of them to an item: the first block
-// of a piece that starts inside it and a ragged last one take fewer items than a whole one.  (Counted as whole ones, a
-// piece of 2000 rows from position 30001, 28 query heads on 4, made 264 items on 256 compute units, a second round for
-// eight of them: 48.2 -> 32.1 us.)
-struct seq_items { int c_last, n; };
-__host__ __device__ __forceinline__ seq_items items_of_sequence(int n, int qs, int first, int nblk, int B, int G, int nw) {
-  seq_items s = {0, 0};
-  if (nblk <= 0) return s;
-  const int skipped = (qs - first * B) / QW, last = (n - 1 - (first + nblk - 1) * B) / QW;
-  s.c_last = (G * (last + 1 - (nblk == 1 ? skipped : 0)) + nw - 1) / nw;
-  s.n = s.c_last;
-  if (nblk > 1) s.n += (nblk - 2) * ((G * (B / QW) + nw - 1) / nw) + (G * (B / QW - skipped) + nw - 1) / nw;
-  return s;
-}
-
 // DENSE: the implicit list {0..i} instead of a block list.  CHAIN: the launch chains work items in persistent
 // workgroups (two half-size tile tables, list rows prefetched); otherwise one workgroup per item.  VARLEN: every
 // sequence of the batch has its own length, read from device memory; the work items are numbered as if all had the
@@ -198,23 +184,8 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   int item_step = nslots;
   // Sequences of different lengths: keys and first query of sequence b (values outside the context or the slab of Q/O
   // are clamped), and how many query blocks it has, counted from the one of its first query.
-  auto block_of = [&](int pos) -> int { return p.b_shift >= 0 ? pos >> p.b_shift : pos / p.B; };
-  struct seq_t { int n, qs, first, nblk; seq_items it; };
-  auto seq_of = [&](int b) -> seq_t {
-    seq_t q;
-    q.qs = 0;
-    const int len = p.seq_len[b];
-    if (p.q_start_dev) {
-      q.qs = p.q_start_dev[b];
-      q.qs = q.qs < 0 ? 0 : (q.qs > (int)p.N ? (int)p.N : q.qs);
-    }
-    int room = (int)p.N - q.qs;        // rows that fit the context, and the slab of Q/O
-    if ((int64_t)room > p.q_rows) room = (int)p.q_rows;
-    q.n = q.qs + (len < 0 ? 0 : (len > room ? room : len));
-    q.first = block_of(q.qs);
-    q.nblk = q.n > q.qs ? block_of(q.n - 1) - q.first + 1 : 0;
-    q.it = items_of_sequence(q.n, q.qs, q.first, q.nblk, p.B, p.G, NW);
-    return q;
+  auto seq_of = [&](int b) -> pa_seq {
+    return pa_sequence(p.seq_len[b], p.q_start_dev ? p.q_start_dev[b] : 0, p.N, p.q_rows, p.B, p.b_shift, p.G, NW);
   };
   int v_kvh = 0, v_b = 0, v_q = 0;          // VARLEN: the first item
   if (VARLEN) {
@@ -223,7 +194,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     // where 17 were the mean, at 32 pieces of 1 .. 2048 rows: 528 -> 501 us; 32 prompts of 300 .. 8192: 1447 -> 1369 us).  64 sequences at a time, one
     // per lane: how many items they have, and a prefix sum to find the first item's sequence.
     auto prefix = [&](int base, int& own) -> int {       // items of the sequences base .. base + lane
-      own = base + lane < p.batch ? seq_of(base + lane).it.n : 0;
+      own = base + lane < p.batch ? seq_of(base + lane).n_items : 0;
       int sum = own;
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
@@ -280,32 +251,20 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   // the slowest digit and every sequence has a count of its own, so that the contiguous share of an XCD spans all
   // sequences (one KV head each when there are eight) and the XCDs finish together whatever the mix of lengths.  The
   // first item is found by division, the following ones by adding the stride nslots digit by digit with carries.
-  struct item_t { int q, kvh, b, chunk, i, sl0, nsl, subs_diag;     // sl0, nsl: the block's slices that hold queries of the call
-                  int n, qs, first, nblk, c_last, n_items; };       // VARLEN: the sequence (keys, first query, its block, blocks, items)
-  auto enter_seq = [&](item_t& it) {   // uniform over the workgroup: scalar loads
-    const seq_t q = seq_of(it.b);
-    it.n = q.n; it.qs = q.qs; it.first = q.first; it.nblk = q.nblk; it.c_last = q.it.c_last; it.n_items = q.it.n;
+  struct item_t : pa_seq {             // VARLEN: the sequence
+    int q, kvh, b, chunk, i, sl0, nsl, subs_diag;     // sl0, nsl: the block's slices that hold queries of the call
   };
-  // counts of slices and items are powers of two but for ragged blocks of 128 keys or more and unusual head groups
-  auto quot = [](unsigned x, unsigned y) -> int { return (int)((y & (y - 1)) == 0 ? x >> __builtin_ctz(y) : x / y); };
+  auto enter_seq = [&](item_t& it) {   // uniform over the workgroup: scalar loads
+    static_cast<pa_seq&>(it) = seq_of(it.b);
+  };
   auto finish_item = [&](item_t& it) {
-    const int c_last = VARLEN ? it.c_last : p.c_last;
-    int r = 0;                         // query blocks behind the item's
-    it.chunk = it.q;
-    if (it.q >= c_last) {
-      const int rest = it.q - c_last, blocks = quot(rest, p.chunks);
-      r = 1 + blocks;
-      it.chunk = rest - blocks * p.chunks;
-    }
-    it.i = (VARLEN ? it.first + it.nblk : p.i0 + p.nb) - 1 - r;
-    const int before = (VARLEN ? it.qs : (int)p.q_start) - it.i * p.B, keys = (VARLEN ? it.n : (int)p.N) - it.i * p.B;
-    it.sl0 = before > 0 ? before / QW : 0;
-    it.nsl = ((keys < p.B ? keys : p.B) + QW - 1) / QW - it.sl0;
-    if (it.nsl < 1) it.nsl = 1;
+    const pa_seq whole = {(int)p.N, (int)p.q_start, p.i0, p.nb, p.c_last, p.n_items};
+    const pa_item_place at = pa_place_item(it.q, VARLEN ? it : whole, p.chunks, p.B);
+    it.i = at.i; it.chunk = at.chunk; it.sl0 = at.sl0; it.nsl = at.nsl;
     // tiles of the diagonal block needed by any wavefront of the item
     int last_task = it.chunk * NW + NW - 1;
     if (last_task > p.G * it.nsl - 1) last_task = p.G * it.nsl - 1;
-    const int g_last = quot(last_task, it.nsl);
+    const int g_last = pa_quot(last_task, it.nsl);
     const int max_sl = it.sl0 + (g_last * it.nsl > it.chunk * NW ? it.nsl - 1 : last_task - g_last * it.nsl);
     it.subs_diag = (max_sl * QW + QW - 1) / KT + 1;
   };
@@ -313,7 +272,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   auto task_of = [&](const item_t& it, int& g, int& sl) -> bool {
     const int task = it.chunk * NW + (it.nsl == 4 ? wave4 : wave);
     const bool act = task < p.G * it.nsl;
-    g = act ? quot(task, it.nsl) : 0;
+    g = act ? pa_quot(task, it.nsl) : 0;
     sl = act ? it.sl0 + task - g * it.nsl : 0;
     return act;
   };
@@ -338,9 +297,9 @@ void pa_prefill_bf16_kernel(bf16_params p) {
         it.q -= it.n_items;
         if (++it.b >= p.batch) { it.b = 0; ++it.kvh; }
         enter_seq(it);
-        if (it.kvh >= p.hkv) {         // only if the lengths changed while the kernel ran: stay in bounds, and end
-          it.kvh = p.hkv - 1; it.q = 0;
-          if (it.nblk < 1) it.nblk = it.c_last = it.n_items = 1;
+        if (it.kvh >= p.hkv) {         // only if the lengths changed while the kernel ran: end with an item that exists
+          it.kvh = p.hkv - 1;
+          it.q = pa_existing_item(it, it.q, p.B, p.i_max);
         }
       }
     } else {
@@ -602,6 +561,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   if (VARLEN) {
     it.q = v_q; it.kvh = v_kvh; it.b = v_b;
     enter_seq(it);
+    it.q = pa_existing_item(it, it.q, p.B, p.i_max);
     finish_item(it);
   } else {
     it = digits((uint32_t)first_item);
@@ -1046,12 +1006,12 @@ int launch(const bf16_params& p, hipStream_t stream) {
 }
 
 // Work items of a sequence and KV head (at most, if only the device knows the lengths) with workgroups of nw wavefronts
-seq_items host_items(const bf16_params& p, int nw) {
+pa_seq_items host_items(const bf16_params& p, int nw) {
   if (p.seq_len) {
     const int chunks = (p.G * (p.B / QW) + nw - 1) / nw;
     return {chunks, p.nb * chunks};
   }
-  return items_of_sequence((int)p.N, (int)p.q_start, p.i0, p.nb, p.B, p.G, nw);
+  return pa_items_of_sequence((int)p.N, (int)p.q_start, p.i0, p.nb, p.B, p.G, nw);
 }
 
 // Whether a launch of few work items is better cut into workgroups of four wavefronts: when there is a compute unit for
@@ -1088,7 +1048,7 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
   int nw = tasks > 4 ? 8 : 4;
   if (nw == 8 && few_items_want_four_wavefronts(p, a)) nw = 4;
   p.chunks = (int32_t)((tasks + nw - 1) / nw);
-  const seq_items si = host_items(p, nw);
+  const pa_seq_items si = host_items(p, nw);
   p.c_last = si.c_last; p.n_items = si.n;
   p.total_wg = (int64_t)a.batch * a.hkv * si.n;
   int64_t per_xcd = (p.total_wg + 7) / 8;
@@ -1098,6 +1058,7 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
     per_xcd = ((int64_t)a.batch * si.n + p.xcd_split - 1) / p.xcd_split;
   }
   p.b_shift = (p.B & (p.B - 1)) == 0 ? __builtin_ctz((unsigned)p.B) : -1;
+  p.i_max = (int32_t)((a.seq_len - 1) / p.B);
   if (per_xcd * 8 > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
   p.per_xcd = (int32_t)per_xcd;
   // chaining keeps the list row of the item after next in 63 lanes and two tile tables in LDS
