@@ -577,9 +577,9 @@ void pa_bwd_dkv_kernel(bwd_params p) {
   };
   static_assert(TR == 32 || TR == 64, "a tile's vectors are one or two copy instructions");
   static_assert((TR / G::RPI) % NW == 0 || EITHER, "tile copies must divide over the wavefronts");
-  // The mask matters on the diagonal block and where queries or keys run past the sequence: tiles whose first query
-  // lies outside [m_lo, m_lo + m_span].
-  int m_lo = (int)(((int64_t)j + 1) * p.B < n32 ? ((int64_t)j + 1) * p.B : n32);
+  // The mask matters where queries lie before the slab's last key, and where queries or keys run past the sequence: tiles
+  // whose first query lies outside [m_lo, m_lo + m_span].
+  int m_lo = (int)(slab0 + 32 * NSL < n32 ? slab0 + 32 * NSL : n32);
   uint32_t m_span = n32 - TR - m_lo > 0 ? (uint32_t)(n32 - TR - m_lo) : 0u;
   if (n32 - TR < m_lo || slab0 + 32 * NSL > p.N) { m_lo = 0x7fffffff; m_span = 0; }     // every tile
   const uint32_t pbase = lds0 + NST * STAGEB + (slice * QW + qg) * (QI * W::PPIECE) + lane * 16;
@@ -588,8 +588,9 @@ void pa_bwd_dkv_kernel(bwd_params p) {
   // (after the first tile's copies: they would queue behind these row-per-lane loads)
   reg_rows<D>((krole ? p.v : p.k) + krow * D, kok, lane, xf);
 
+  auto attended = [&](int qi) -> bool { return kok && qi >= key32 && qi < n32; };      // by query qi, in a tile with a mask
   // One tile's products: piece by piece, S or dP, the elements, dV^T or dK^T.
-  auto products = [&](auto role, int q0, uint32_t stage, uint32_t pbuf) {
+  auto products = [&](auto role, auto masked_side, int q0, uint32_t stage, uint32_t pbuf) {
     constexpr bool KR = decltype(role)::value;
     const uint32_t qt = lds0 + stage, dot = qt + TILEB;
     const uint32_t vec = qt + 2 * TILEB;
@@ -629,10 +630,7 @@ void pa_bwd_dkv_kernel(bwd_params p) {
             for (int e = 0; e < 4; ++e) {
               // computed for every element and selected afterwards: a conditional exponential becomes a branch
               x[e] = __builtin_amdgcn_exp2f(fmaf(X[4 * r4 + e], p.c2, -l4[e]));
-              if (decltype(masked)::value) {
-                const int qi = q0 + 32 * half + 8 * r4 + 4 * hh + e;
-                x[e] = (kok && qi >= key32 && qi < n32) ? x[e] : 0.f;
-              }
+              if (decltype(masked)::value) x[e] = attended(q0 + 32 * half + 8 * r4 + 4 * hh + e) ? x[e] : 0.f;
             }
             const int r = 4 * r4;
             w[r >> 3][(r & 7) >> 1] = pack2(x[0], x[1]);
@@ -646,6 +644,11 @@ void pa_bwd_dkv_kernel(bwd_params p) {
           slot[64] = w[1];
         }
       } else {
+        // (P is masked by its producer; 0 times a dP that is no number, where a query's row of O or dO is none, would not be 0)
+        if (decltype(masked_side)::value) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) X[r] = attended(q0 + 32 * half + acc_row(r, hh)) ? X[r] : 0.f;
+        }
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
           float y[4];
@@ -686,17 +689,30 @@ void pa_bwd_dkv_kernel(bwd_params p) {
     for (int it = 0; it < n_tiles; ++it) {
       const int q0 = q_next;
       top(it);
-      products(std::false_type{}, q0, stage, pbuf);
+      products(std::false_type{}, std::false_type{}, q0, stage, pbuf);
       moved_on();
     }
     top(n_tiles);
   } else {
+    // The tiles that need the mask are among those of the diagonal block, which comes first, and of the sequence's last
+    // block; each range has a loop of its own (a test in every tile: +2 % at the 128K workload).
+    int n_diag = part == 0 ? p.G * (tpb - u_diag) : 0;
+    int n_last = n32 % TR != 0 && entry(n_ent - 1) == p.nb - 1 ? p.G * tpb : 0;
+    if (n_diag + n_last > n_tiles || slab0 + 32 * NSL > p.N) { n_diag = n_tiles; n_last = 0; }
+    int q0 = q_next, it = 1;
     top(0);
-    for (int it = 1; it <= n_tiles; ++it) {
-      top(it);
-      products(std::true_type{}, 0, stage, pbuf);
-      moved_on();
-    }
+    auto run = [&](auto masked_side, int to) {
+      for (; it <= to; ++it) {
+        const int q1 = q_next;
+        top(it);
+        products(std::true_type{}, masked_side, q0, stage, pbuf);
+        q0 = q1;
+        moved_on();
+      }
+    };
+    run(std::true_type{}, n_diag);
+    run(std::false_type{}, n_tiles - n_last);
+    run(std::true_type{}, n_tiles);
   }
   wait_vmcnt<0>();
 

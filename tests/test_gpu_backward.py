@@ -201,3 +201,29 @@ def test_degenerate_shapes(B, W, S, flags, hq, hkv, n, d):
 ])
 def test_more_slabs_than_compute_units(B, W, S, flags, batch, hq, hkv, n, d):
     run_backward(pa.Pattern(B, W, S, flags), batch, hq, hkv, n, d, seed=58)
+
+
+@pytest.mark.parametrize("B,hq,hkv,n,d", [
+    (64, 2, 1, 400, 128),                         # 64-key slabs, two query groups
+    (64, 16, 8, 2100, 128),                       # tiles of 32 queries
+    (128, 8, 8, 2177, 128),                       # P between the wavefronts in bf16
+    (256, 8, 8, 2305, 128),                       # 128-key slabs
+    (256, 8, 8, 2305, 64),                        # sixteen wavefronts
+])
+def test_a_row_without_a_number_stays_with_the_keys_it_attends(B, hq, hkv, n, d):
+    # one query row of dO is NaN: dK of the keys it attends is, dK of all others (later keys of its own tile among them)
+    # is what it is with that row at zero.  (No sink: its columns add up with atomics, in any order.)
+    pat = pa.Pattern(B, 2, 0)
+    q, k, v = (t.cuda() for t in synth.qkv(1, hq, hkv, n, d, "bf16", 66))
+    do = synth.gaussian((1, hq, n, d), "bf16", 67).cuda()
+    cnt, idx, _ = pa.mask_build(pat, n)
+    o, lse = pa.prefill(pat, cnt, idx, q, k, v)
+    row = B + 17
+    do[:, 0, row] = 0
+    want = pa.backward(pat, cnt, idx, q, k, v, o, lse, do)[1]
+    do[:, 0, row] = float("nan")
+    got = pa.backward(pat, cnt, idx, q, k, v, o, lse, do)[1]
+    torch.cuda.synchronize()
+    hit = torch.from_numpy(orc.token_mask_rows([row], n, oracle_pattern(pat))[0]).cuda()
+    assert bool(torch.isnan(got[:, 0, hit]).all())
+    assert torch.equal(got[:, 0, ~hit], want[:, 0, ~hit]) and torch.equal(got[:, 1:], want[:, 1:])
