@@ -42,7 +42,6 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
 constexpr int KT = 64;            // rows per staged tile
 constexpr int TILE_CAP = 2048;    // tiles per query block in the dq kernel
-constexpr int PART = 16;          // query blocks per part of a sink block's column, at most
 constexpr int PFD = 2;            // matrix instructions per group of LDS fragment reads
 constexpr float LOG2E = 1.44269504088896340736f;
 constexpr int dq_stages(int) { return 2; }   // LDS stages of the dQ kernel's tile stream (see there)
@@ -855,12 +854,7 @@ int pa_launch_backward_bf16(const pa_backward_args& a) {
   const int nwq = (p.tasks > 4 && p.B >= 128 && !few) ? 8 : 4;
   p.chunks = (p.tasks + nwq - 1) / nwq;
   p.sink_blocks = a.pat.sink < a.nb ? a.pat.sink : a.nb;
-  // A sink block's column is cut into parts as long as the longest ordinary column, at most PART blocks: on a short
-  // sequence longer ones would be all that is still running at the end.
-  int32_t longest = (a.pat.flags & POWATTN_POWER) ? (p.W > 1 ? p.W : 1) : p.W;
-  if (a.pat.flags & POWATTN_POWER)
-    for (int64_t pw = 1; pw < a.nb; pw <<= 1) longest += pw >= p.W ? 1 : 0;
-  p.part = longest < PART ? longest : PART;
+  p.part = pa_sink_part(a.nb, p.sink_blocks, p.W, p.flags, (int64_t)a.hkv * a.batch, p.G, p.B);
   p.max_parts = p.sink_blocks > 0 ? (a.nb + p.part - 1) / p.part : 1;
   if (p.max_parts < 2) p.max_parts = 2;                            // keeps the part arithmetic of the kernel defined
 

@@ -78,3 +78,25 @@ PA_HD bool pa_block_attended(int32_t W, int32_t S, uint32_t flags, int64_t i, in
   if (d < W || j < S) return true;
   return (flags & POWATTN_POWER) && ((d & (d - 1)) == 0);
 }
+
+// Backward pass: the column of a sink block (every later query block attends it) is cut into parts of this many query
+// blocks; kv_heads counts those of all sequences, G the query heads of each.
+//
+// Short parts end early: a workgroup takes about 1.1 us for 64 queries of a head, and on a short sequence the longest part
+// is all that is still running at the end; parts no longer than the longest ordinary column cost nothing there.  But
+// every part adds B x head_dim sums of dK and of dV to the same addresses, at about 50 additions a ns on the whole card.
+// Both times together are least at part^2 = 0.3 nb sinks kv_heads / G (block size and head_dim cancel); beyond 16 blocks
+// nothing is gained.  Gradient pass, head_dim 128, one sink, window only, 32 heads on 8, us, parts as long as an
+// ordinary column / of 16 blocks / by this rule: block 64, W = 1, N = 131072 8490 / 2300 / 2340, N = 4096 287 / 167 / 129;
+// W = 4, N = 131072 4490 / 3620 / 3630, N = 1000 64 / 114 / 63; block 256, W = 5, 28 on 4, N = 32768 2460 / 2800 / 2470.
+PA_HD int32_t pa_sink_part(int64_t nb, int32_t sinks, int32_t W, uint32_t flags, int64_t kv_heads, int32_t G, int32_t B) {
+  int64_t longest = (flags & POWATTN_POWER) ? (W > 1 ? W : 1) : W;
+  if (flags & POWATTN_POWER)
+    for (int64_t pw = 1; pw < nb; pw <<= 1) longest += pw >= W ? 1 : 0;
+  int64_t part = longest < 16 ? longest : 16;
+  while (part < 16 && 10.0 * part * part * G < 3.0 * nb * sinks * kv_heads) ++part;
+  // very many sink blocks of a very long sequence: longer parts, so that the launch has fewer than 2^32 threads (at most
+  // 512 for 64 keys)
+  while ((nb + sinks * ((nb + part - 1) / part)) * (B / 64) * 512 > 0xffffffffLL && part < nb) part *= 2;
+  return (int32_t)part;
+}
