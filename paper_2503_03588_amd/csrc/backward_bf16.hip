@@ -471,7 +471,7 @@ void pa_bwd_dkv_kernel(bwd_params p) {
     n_win = weff < p.nb - j ? weff : p.nb - j;
     n_ent = n_win;
     if (p.flags & POWATTN_POWER) {
-      while (first_pow < weff) first_pow <<= 1;
+      while (first_pow < weff && first_pow < p.nb) first_pow <<= 1;      // (a window above 2^30 has no power of two in 32 bits)
       for (int64_t pw = first_pow; j + pw < p.nb; pw <<= 1) ++n_ent;
     }
   }

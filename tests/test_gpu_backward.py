@@ -182,6 +182,7 @@ def test_long_prefill_configuration_size_with_a_row_sparse_upstream_gradient():
     (128, 1, 1, 0, 16, 1, 700, 64),               # GQA 16, window of the diagonal block only
     (256, 2, 1, pa.POWER, 1, 1, 2100, 128),       # one head, block 256, ragged
     (64, 1, 2, 0, 2, 2, 2113, 128),               # window of one block: the sink columns in many parts
+    (64, 2 ** 31 - 1, 0, pa.POWER, 2, 1, 300, 64),   # a window beyond every power of two in 32 bits
 ])
 def test_degenerate_shapes(B, W, S, flags, hq, hkv, n, d):
     run_backward(pa.Pattern(B, W, S, flags), 1, hq, hkv, n, d, seed=57)
