@@ -587,7 +587,9 @@ void pa_bwd_dkv_kernel(bwd_params p) {
   // (after the first tile's copies: they would queue behind these row-per-lane loads)
   reg_rows<D>((krole ? p.v : p.k) + krow * D, kok, lane, xf);
 
-  auto attended = [&](int qi) -> bool { return kok && qi >= key32 && qi < n32; };      // by query qi, in a tile with a mask
+  // in a tile with a mask: whether query qi attends this lane's key (key32 <= qi < n32, in one comparison)
+  const uint32_t q_span = kok ? (uint32_t)(n32 - key32) : 0u;
+  auto attended = [&](int qi) -> bool { return (uint32_t)(qi - key32) < q_span; };
   // One tile's products: piece by piece, S or dP, the elements, dV^T or dK^T.
   auto products = [&](auto role, auto masked_side, int q0, uint32_t stage, uint32_t pbuf) {
     constexpr bool KR = decltype(role)::value;
@@ -709,9 +711,12 @@ void pa_bwd_dkv_kernel(bwd_params p) {
         moved_on();
       }
     };
-    run(std::true_type{}, n_diag);
-    run(std::false_type{}, n_tiles - n_last);
-    run(std::true_type{}, n_tiles);
+    int stop = n_diag;
+    while (it <= n_tiles) {                      // (one copy of either loop, left at one place only: the sums stay in their registers)
+      run(std::true_type{}, stop);
+      run(std::false_type{}, n_tiles - n_last);
+      stop = n_tiles;
+    }
   }
   wait_vmcnt<0>();
 
