@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import operator
 import os
 from dataclasses import dataclass
 
@@ -48,13 +49,23 @@ class Pattern:
     sink: int = 1
     flags: int = POWER
 
+    def __post_init__(self):
+        # plain integers, whatever integer type they came as (arrays and tensors of one element among them): the values are
+        # the key under which a pattern's C struct is kept (below), so they have to be hashable and must not change
+        for name in ("block", "window", "sink", "flags"):
+            object.__setattr__(self, name, operator.index(getattr(self, name)))
+        object.__setattr__(self, "_values", (self.block, self.window, self.sink, self.flags))
+
+    def __setstate__(self, state):       # (a pattern that was pickled with its four fields alone)
+        self.__init__(state["block"], state["window"], state["sink"], state["flags"])
+
     def c(self) -> _CPattern:
-        return _CPattern(self.block, self.window, self.sink, self.flags)
+        return _CPattern(*self._values)
 
 
 # The C struct of a pattern is built once per set of values (a call only reads it) instead of on every call: 1.3 us of
-# the 8 to 10 us of host time that bound the smallest calls.  typed: 64 and 64.0 stay different arguments.
-@functools.lru_cache(maxsize=256, typed=True)
+# the 8 to 10 us of host time that bound the smallest calls.
+@functools.lru_cache(maxsize=256)
 def _pattern_ref(block, window, sink, flags):
     return ctypes.byref(_CPattern(block, window, sink, flags))
 
@@ -160,14 +171,14 @@ def strerror(status: int) -> str:
 
 
 def num_blocks(pattern: Pattern, seq_len: int) -> int:
-    n = lib().powattn_num_blocks(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len)
+    n = lib().powattn_num_blocks(_pattern_ref(*pattern._values), seq_len)
     if n < 0:
         raise PowattnError(-n, "powattn_num_blocks")
     return n
 
 
 def max_k(pattern: Pattern, seq_len: int) -> int:
-    n = lib().powattn_max_k(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len)
+    n = lib().powattn_max_k(_pattern_ref(*pattern._values), seq_len)
     if n < 0:
         raise PowattnError(-n, "powattn_max_k")
     return n
@@ -187,7 +198,7 @@ def row_host(pattern: Pattern, q_block: int):
 
 
 def decode_workspace_bytes(pattern: Pattern, batch, n_q_heads, n_kv_heads, head_dim, cache_capacity) -> int:
-    return lib().powattn_decode_workspace_bytes(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), batch, n_q_heads, n_kv_heads,
+    return lib().powattn_decode_workspace_bytes(_pattern_ref(*pattern._values), batch, n_q_heads, n_kv_heads,
                                                 head_dim, cache_capacity)
 
 
@@ -212,7 +223,7 @@ def mask_build(pattern: Pattern, seq_len: int, kv_cnt=None, kv_idx=None, block_m
         kv_cnt = torch.empty((nb,), dtype=torch.int32, device=device)
     if block_mask is None and want_block_mask:
         block_mask = torch.empty((nb, nb), dtype=torch.uint8, device=device)
-    st = lib().powattn_mask_build(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), seq_len, _ptr(kv_cnt), _ptr(kv_idx),
+    st = lib().powattn_mask_build(_pattern_ref(*pattern._values), seq_len, _ptr(kv_cnt), _ptr(kv_idx),
                                   kv_idx.shape[1], _ptr(block_mask), _stream(stream))
     _check(st, "powattn_mask_build")
     return kv_cnt, kv_idx, block_mask
@@ -234,7 +245,7 @@ def prefill(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o=None, lse=None, softmax
     mk = kv_idx.shape[1] if kv_idx is not None else 0
     if kv_idx is not None and kv_cnt.shape[0] * pattern.block < n:
         raise ValueError("block lists shorter than the sequence")
-    st = lib().powattn_prefill(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
                                batch, hq, hkv, n, d, _dtype_code(q), float(softmax_scale), _stream(stream))
     _check(st, "powattn_prefill")
@@ -258,7 +269,7 @@ def prefill_chunk(pattern: Pattern, kv_cnt, kv_idx, q, k_cache, v_cache, q_start
     mk = kv_idx.shape[1] if kv_idx is not None else 0
     if kv_idx is not None and kv_cnt.shape[0] * pattern.block < q_start + q_len:
         raise ValueError("block lists shorter than the context")
-    st = lib().powattn_prefill_chunk(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill_chunk(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                      _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(o), _ptr(lse),
                                      batch, hq, hkv, int(q_start), q_len, cap, d, _dtype_code(q),
                                      float(softmax_scale), _stream(stream))
@@ -290,7 +301,7 @@ def prefill_chunk_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
         o = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((batch, hq, q_len), dtype=torch.float32, device=q.device)
-    st = lib().powattn_prefill_chunk_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_prefill_chunk_paged(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                            _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
                                            block_table.shape[1], n_pages, _ptr(o), _ptr(lse),
                                            batch, hq, hkv, int(q_start), q_len, d, _dtype_code(q),
@@ -327,7 +338,7 @@ def prefill_batch_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
         o = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((batch, hq, q_rows), dtype=torch.float32, device=q.device)
-    st = lib().powattn_prefill_batch_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_prefill_batch_paged(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                            _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
                                            block_table.shape[1], n_pages, _ptr(q_start), _ptr(q_len), q_rows,
                                            _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
@@ -351,7 +362,7 @@ def decode(pattern: Pattern, q, k_cache, v_cache, kv_len, o=None, lse=None, soft
         lse = torch.empty((batch, hq), dtype=torch.float32, device=q.device)
     if workspace is None:
         workspace = decode_workspace(pattern, batch, hq, hkv, d, cap, q.device)
-    st = lib().powattn_decode(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
+    st = lib().powattn_decode(_pattern_ref(*pattern._values), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
                               cap, _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
                               float(softmax_scale), _ptr(workspace), workspace.numel() * workspace.element_size(),
                               _stream(stream))
@@ -370,7 +381,7 @@ def decode_static(pattern: Pattern, q, k_cache, v_cache, kv_len, o, lse=None, so
         raise ValueError("kv_len must be int32 [batch]")
     if o.shape != q.shape or o.dtype != q.dtype:
         raise ValueError("o must have the shape and dtype of q")
-    st = lib().powattn_decode_static(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
+    st = lib().powattn_decode_static(_pattern_ref(*pattern._values), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(kv_len),
                                      cap, _ptr(o), _ptr(lse), batch, hq, hkv, d, _dtype_code(q),
                                      float(softmax_scale), _stream(stream))
     _check(st, "powattn_decode_static")
@@ -400,7 +411,7 @@ def decode_paged(pattern: Pattern, q, k_pages, v_pages, block_table, kv_len, o=N
         lse = torch.empty((batch, hq), dtype=torch.float32, device=q.device)
     if workspace is None:
         workspace = decode_workspace(pattern, batch, hq, hkv, d, stride * blk, q.device)
-    st = lib().powattn_decode_paged(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(q), _ptr(k_pages), _ptr(v_pages), n_pages,
+    st = lib().powattn_decode_paged(_pattern_ref(*pattern._values), _ptr(q), _ptr(k_pages), _ptr(v_pages), n_pages,
                                     _ptr(block_table), stride, _ptr(kv_len), _ptr(o), _ptr(lse),
                                     batch, hq, hkv, d, _dtype_code(q), float(softmax_scale),
                                     _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
@@ -409,7 +420,7 @@ def decode_paged(pattern: Pattern, q, k_pages, v_pages, block_table, kv_len, o=N
 
 
 def backward_workspace_bytes(pattern: Pattern, batch, n_q_heads, n_kv_heads, seq_len, head_dim) -> int:
-    return lib().powattn_backward_workspace_bytes(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), batch, n_q_heads, n_kv_heads,
+    return lib().powattn_backward_workspace_bytes(_pattern_ref(*pattern._values), batch, n_q_heads, n_kv_heads,
                                                   seq_len, head_dim)
 
 
@@ -439,7 +450,7 @@ def backward(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o, lse, d_o, dq=None, dk
         if need == 0:
             raise PowattnError(INVALID_ARG, "powattn_backward_workspace_bytes")
         workspace = torch.empty((need,), dtype=torch.uint8, device=q.device)
-    st = lib().powattn_backward(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
+    st = lib().powattn_backward(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), kv_idx.shape[1],
                                 _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
                                 batch, hq, hkv, n, d, _dtype_code(q), float(softmax_scale),
                                 _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
@@ -466,7 +477,7 @@ def prefill_varlen(pattern: Pattern, kv_cnt, kv_idx, q, k, v, seq_lens, o=None, 
     if lse is None and want_lse:
         lse = torch.zeros((batch, hq, npad), dtype=torch.float32, device=q.device)
     mk = kv_idx.shape[1] if kv_idx is not None else 0
-    st = lib().powattn_prefill_varlen(_pattern_ref(pattern.block, pattern.window, pattern.sink, pattern.flags), _ptr(kv_cnt), _ptr(kv_idx), mk,
+    st = lib().powattn_prefill_varlen(_pattern_ref(*pattern._values), _ptr(kv_cnt), _ptr(kv_idx), mk,
                                       _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), batch, hq, hkv, _ptr(seq_lens),
                                       npad, d, _dtype_code(q), float(softmax_scale), _stream(stream))
     _check(st, "powattn_prefill_varlen")

@@ -4,6 +4,7 @@ bad arguments into status codes before anything could be launched (CPU only:
 no call here reaches a kernel launch)."""
 import ctypes
 import os
+import pickle
 import re
 
 import numpy as np
@@ -325,3 +326,20 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(pa, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(RuntimeError, match="no fallback"):
         pa.version()
+
+
+def test_pattern_values_of_any_integer_type(L):
+    # one-element arrays and tensors count as integers; a pattern keeps their value, not the object
+    import torch
+    cell = torch.tensor(64)
+    pats = [pa.Pattern(64, 4, 1), pa.Pattern(np.int64(64), np.array(4), np.int32(1), np.uint8(1)), pa.Pattern(cell, torch.tensor(4))]
+    assert pats[0] == pats[1] == pats[2] and len({hash(p) for p in pats}) == 1
+    assert [pa.num_blocks(p, 1000) for p in pats] == [16, 16, 16]
+    cell.fill_(128)
+    assert pa.num_blocks(pats[2], 1000) == 16 and pa.num_blocks(pa.Pattern(cell, 4), 1000) == 8
+    old = pa.Pattern.__new__(pa.Pattern)
+    old.__setstate__({"block": 64, "window": 4, "sink": 1, "flags": 1})      # as pickled before the values were kept together
+    assert old == pats[0] == pickle.loads(pickle.dumps(pats[0])) and pa.num_blocks(old, 1000) == 16
+    for bad in (64.0, "64", None, torch.tensor(64.0)):
+        with pytest.raises(TypeError):
+            pa.num_blocks(pa.Pattern(bad, 4), 1000)
