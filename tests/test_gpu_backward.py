@@ -132,7 +132,7 @@ def test_prefill_configuration_size_on_sampled_rows_and_keys():
 
 def test_long_prefill_configuration_size_with_a_row_sparse_upstream_gradient():
     # configuration 3 at its full size (batch 1, 32/8 heads, N = 131072, block 128, W = 4, S = 1): what the bench
-    # times as `backward_128k`, i.e. the split-wavefront dK/dV kernel with the sink block's column cut into 64 parts
+    # times as `backward_128k`, with the sink block's column cut into 64 parts of 16 blocks (test_sink_parts_host.py)
     # that add up in fp32.  The dense oracle is out of reach and so is the sampled one for sink keys (every query
     # attends them).  Instead dO is zero outside 200 query rows that are spread over all 64 parts: then only those rows
     # contribute to dK and dV (a row with dO = 0 has dS = 0), and the oracle's row-sparse form gives dK and dV of
@@ -200,8 +200,14 @@ def test_degenerate_shapes(B, W, S, flags, hq, hkv, n, d):
     (256, 1, 0, pa.POWER, 3, 12, 4, 1471, 128),   # GQA 3, no sink
     (128, 3, 1, pa.POWER, 3, 8, 8, 1409, 64),
     (256, 2, 1, pa.POWER, 2, 8, 8, 1665, 64),
+    (256, 2, 1, pa.POWER, 3, 8, 8, 1665, 64),
+    (128, 2, 1, pa.POWER, 1, 16, 8, 2177, 64),
+    (128, 2, 1, pa.POWER, 1, 16, 8, 2177, 128),
 ])
 def test_more_slabs_than_compute_units(B, W, S, flags, batch, hq, hkv, n, d):
+    # the last three: dQ in workgroups of eight wavefronts, which takes more work items of four than there are compute units
+    if (B, batch, hq) in ((256, 3, 8), (128, 1, 16)):
+        assert batch * hkv * -(-n // B) * -(-(hq // hkv * B // 32) // 4) > torch.cuda.get_device_properties(0).multi_processor_count
     run_backward(pa.Pattern(B, W, S, flags), batch, hq, hkv, n, d, seed=58)
 
 

@@ -19,10 +19,24 @@ CASES = [
     (2, 2, 401, 128, 80, 1, 1, pa.POWER),        # five
     (16, 2, 1041, 64, 64, 3, 1, pa.POWER),       # 64 queries per workgroup, ragged end
     (16, 4, 530, 128, 32, 2, 1, pa.POWER),       # 32 queries per workgroup
-    (9, 3, 499, 64, 32, 2, 0, pa.POWER),         # 32 queries of a possible 64
+    (9, 3, 499, 64, 32, 2, 0, pa.POWER),         # too few tiles for more than 16 queries per workgroup
     (2, 1, 1100, 64, 16, 1, 0, pa.DENSE),        # implicit rows of up to 69 entries
     (1, 1, 1100, 128, 16, 69, 1, pa.POWER),      # listed rows of up to 69 entries
 ]
+
+
+# query tiles of 16 rows per workgroup: as many as the registers hold while every compute unit gets a workgroup
+@pytest.mark.parametrize("hq,hkv,n,d,block,tiles", [
+    (2, 2, 1024, 64, 64, 1), (9, 3, 999, 64, 32, 2), (8, 2, 1041, 64, 64, 2), (8, 2, 2100, 64, 64, 4), (16, 4, 2100, 64, 48, 1),
+    (2, 1, 1000, 128, 64, 1), (8, 2, 1100, 128, 64, 2), (8, 2, 2100, 128, 32, 2), (8, 2, 2100, 128, 16, 1),
+])
+def test_prefill_f32_every_form(hq, hkv, n, d, block, tiles):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    total, mq = -(-n // block) * (block // 16) * hq, 1
+    while mq < 256 // d and block % (32 * mq) == 0 and total // (2 * mq) >= cus:
+        mq *= 2
+    assert mq == tiles
+    check_prefill(pa.Pattern(block, 2, 1), 1, hq, hkv, n, d, "f32", 400 + n)
 
 
 @pytest.mark.parametrize("hq,hkv,n,d,block,window,sink,flags", CASES)
