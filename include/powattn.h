@@ -117,8 +117,9 @@ int powattn_mask_build(const powattn_pattern* pattern, int64_t seq_len,
  *   lse            device float [batch, n_q_heads, seq_len] or NULL:
  *                  natural-log sum of exp(scaled logits) over the attended keys
  *   dtype          POWATTN_BF16 (MFMA path, fp32 accumulation; head_dim 64 or 128,
- *                  block a multiple of 64, at most 1024) or POWATTN_F32 (plain FMA path;
- *                  head_dim 64 or 128, block 16..256 and a multiple of 16)
+ *                  block a multiple of 64, at most 1024) or POWATTN_F32 (fp32 matrix
+ *                  instructions, products and sums in fp32; head_dim 64 or 128,
+ *                  block 16..256 and a multiple of 16)
  *   softmax_scale  logit scale; <= 0 selects 1/sqrt(head_dim) (Equation 1)
  * seq_len need not be a multiple of the block size.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP_ERROR.
@@ -211,8 +212,9 @@ int powattn_prefill_chunk_paged(const powattn_pattern* pattern,
  *   d_kv_cnt, d_kv_idx, max_k   the block lists, built for at least table_stride*block tokens
  *                     (or for the longest context of the batch)
  * Limits as for powattn_prefill_chunk_paged.  The lengths are read by the kernel: no
- * host synchronisation, one launch whatever the mix of lengths; work is dealt by
- * position in the padded batch, so q_rows should not be much larger than the longest piece.
+ * host synchronisation, one launch whatever the mix of lengths.  Only query blocks that
+ * exist are dealt; a q_rows larger than the longest piece counts only in the choice
+ * between smaller and larger workgroups.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP_ERROR.
  */
 int powattn_prefill_batch_paged(const powattn_pattern* pattern,
@@ -243,12 +245,9 @@ int powattn_prefill_batch_paged(const powattn_pattern* pattern,
  *                  several times: like the tensors, it must not change until the launch has finished
  *   d_kv_cnt, d_kv_idx, max_k   lists covering ceil(padded_len / block) rows
  *   dtype          POWATTN_BF16 only; head_dim 64 or 128; block a multiple of 64, at most 1024
- * Work is dealt to the compute units by position in the padded batch, not by
- * length, in an order that keeps them level for any mix of lengths when there
- * are 1, 2 or a multiple of 8 KV heads (every part of the chip then sees every
- * sequence); with other head counts a part sees some of the sequences, and a
- * batch whose long sequences sit next to one another is balanced less well
- * than a shuffled one.
+ * Only query blocks that exist are dealt to the compute units, the same amount (give
+ * or take one block's work item) to each, whatever the mix of lengths, their order in
+ * the batch and the number of heads.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP_ERROR.
  */
 int powattn_prefill_varlen(const powattn_pattern* pattern,

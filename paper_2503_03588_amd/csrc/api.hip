@@ -268,9 +268,8 @@ extern "C" int powattn_prefill_varlen(const powattn_pattern* pattern,
   if (pattern->block % 64 != 0 || pattern->block > 1024) return POWATTN_UNSUPPORTED;
   if ((int64_t)batch * n_q_heads > 65535 * 16) return POWATTN_UNSUPPORTED;
 
-  // One launch for the whole batch: the work items are numbered as if every sequence had padded_len tokens, and
-  // the kernel, which reads the lengths from device memory, passes over the query blocks a sequence does not have
-  // (the rows of the lists do not depend on the sequence length, so all sequences walk the same lists).
+  // One launch for the whole batch: the kernel reads the lengths from device memory and numbers the query blocks that
+  // exist (the rows of the lists do not depend on the sequence length, so all sequences walk the same lists).
   pa_prefill_args a;
   a.pat = *pattern;
   a.kv_cnt = d_kv_cnt; a.kv_idx = d_kv_idx; a.max_k = max_k;

@@ -67,10 +67,7 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
-__device__ __forceinline__ void async_copy16(const void* sbase, uint32_t voff, uint32_t lds_off) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_off) : "memory", "m0");
-}
-// the same with the LDS offset given as a scalar base plus a constant
+// 16 bytes per lane: lane l's land at lds_base + OFF + 16*l
 template <int OFF>
 __device__ __forceinline__ void async_copy16_at(const void* sbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF) : "memory", "scc", "m0");
@@ -125,19 +122,9 @@ __device__ __forceinline__ void copy_tile(const __bf16* base, int64_t row0, int6
   int64_t r0 = row0 < last_row ? row0 : last_row;
   const int lim = (int)(last_row - r0);
   const __bf16* sb = uniform_ptr(base + r0 * D);
-  if constexpr (G::IPT % NWV == 0) {
-    // a known number of copy instructions per wavefront: straight-line code, LDS offsets as constants
-    const uint32_t wdst = __builtin_amdgcn_readfirstlane(dst + wave * G::SRB);
-    const int row0w = G::RPI * wave + cp_row;
-    copy_tile_unrolled<D, NWV, 0>(sb, row0w, lim, (uint32_t)(cp_chunk << 4), wdst);
-  } else {
-    for (int inst = wave; inst < G::IPT; inst += NWV) {
-      int row = G::RPI * inst + cp_row;
-      row = row < lim ? row : lim;
-      const uint32_t voff = (uint32_t)row * G::ROWB + (cp_chunk << 4);
-      async_copy16(sb, voff, __builtin_amdgcn_readfirstlane(dst + inst * G::SRB));
-    }
-  }
+  static_assert(G::IPT % NWV == 0, "tile copies must divide over the wavefronts");
+  const uint32_t wdst = __builtin_amdgcn_readfirstlane(dst + wave * G::SRB);
+  copy_tile_unrolled<D, NWV, 0>(sb, G::RPI * wave + cp_row, lim, (uint32_t)(cp_chunk << 4), wdst);
 }
 // A operand "rows of the tile": rows 32rt + (lane%32), elements 16c + 8(lane/32) .. +7
 template <int D>

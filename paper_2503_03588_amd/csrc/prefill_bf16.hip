@@ -108,14 +108,10 @@ struct bf16_params {
 // have to be waited for together with every asynchronous tile copy in flight.
 constexpr int TILE_CAP = 4096;   // tiles per query block with an explicit list (16 KB of LDS)
 
-// Asynchronous 16-byte-per-lane copy global -> LDS: lane l's data lands at lds_off + 16*l.
+// Asynchronous 16-byte-per-lane copy global -> LDS: lane l's data lands at lds_base + OFF + 16*l.
 // Written as inline assembly on purpose: the compiler then does not pair every later LDS read
 // with a full vmcnt(0) wait, and the waits are placed by hand (wait_vmcnt below).  M0 carries
 // the LDS offset and is declared as clobbered.
-__device__ __forceinline__ void async_copy16(const void* sbase, uint32_t voff, uint32_t lds_off) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_off) : "memory", "m0");
-}
-// the same with the LDS offset given as a scalar base plus a constant
 template <int OFF>
 __device__ __forceinline__ void async_copy16_at(const void* sbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF) : "memory", "scc", "m0");
@@ -137,8 +133,8 @@ __device__ __forceinline__ void wait_vmcnt() {   // s_waitcnt vmcnt(N) only
 
 // DENSE: the implicit list {0..i} instead of a block list.  CHAIN: the launch chains work items in persistent
 // workgroups (two half-size tile tables, list rows prefetched); otherwise one workgroup per item.  VARLEN: every
-// sequence of the batch has its own length, read from device memory; the work items are numbered as if all had the
-// padded length, and a workgroup passes over the items of query blocks that a sequence does not have.  PAGED: K and V
+// sequence of the batch has its own length (and first query position), read from device memory; only the query blocks
+// that exist are numbered, by a prefix sum over the lengths that every workgroup forms for itself.  PAGED: K and V
 // are pools of pages of one block each; the tile table then also holds every tile's first row in the pool, looked up
 // in the sequence's block table when the table is written (explicit lists, chained items only).
 template <int D, int NW, int NS, bool DENSE, bool CHAIN, bool VARLEN, bool PAGED>
