@@ -384,8 +384,9 @@ void pa_bwd_dq_kernel(bwd_params p) {
 // LDS at the end.
 //
 // Bound: instruction issue (a SIMD issues about one instruction per 4 to 5 cycles, a matrix instruction lasts 32).  Per
-// matrix instruction the loops take 9.0 instructions at 128-key slabs and head_dim 128; 13.0 with a cursor each
-// for copies and products, Delta subtracted element by element and a wait per matrix instruction.  Training steps with
+// matrix instruction the kernel executes 7.9 instructions at blocks of 128 keys and head_dim 128, 8.7 at 256, 9.5 at 64
+// (counters; 10.0 at 128 with a cursor each for copies and products, Delta subtracted element by element and a wait per
+// matrix instruction).  Training steps with
 // 32 query heads on 8 (28 on 4 at block 256), N = 32768: block 64 2.19 -> 1.98 ms, block 256 6.29 -> 4.65 ms (of which
 // the kernel 3.9 -> 2.3); N = 2000, block 64: 232 -> 144 us, block 256: 766 -> 254 us.
 template <int NSL, int QW, int QI, bool P32>

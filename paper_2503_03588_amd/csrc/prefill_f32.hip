@@ -12,8 +12,8 @@
 // of a K row feeds four steps, and the rows of O^T so that one 16-byte load of a V row feeds four tiles of it.
 //
 // Bound by the fp32 matrix rate (153 TFLOP/s in a large matrix product on the same card): 84 TFLOP/s at 8 heads,
-// head_dim 64, N = 8192, blocks of 64 keys, 79 at head_dim 128; a kernel of plain multiply-adds with K/V staged in LDS,
-// which this replaced, 4.  Short prompts are bound by latency (2 heads, N = 1024: 74 us before, 10.7 now).
+// head_dim 64, N = 8192, blocks of 64 keys, 80 at head_dim 128; a kernel of plain multiply-adds with K/V staged in LDS,
+// which this replaced, 4.  Short prompts are bound by latency (2 heads, N = 1024: 74 us before, 10.5 now).
 //
 // Loads run LA tiles ahead of the products (the K tiles of a step of TS tiles, then its V tiles, then the next step's).
 #include <math.h>
