@@ -686,7 +686,7 @@ void pa_bwd_dkv_kernel(bwd_params p) {
     // The tiles that need the mask are among those of the diagonal block, which comes first, and of the sequence's last
     // block; each range has a loop of its own (a test in every tile: +2 % at the 128K workload).
     int n_diag = part == 0 ? p.G * (tpb - u_diag) : 0;
-    int n_last = n32 % TR != 0 && entry(n_ent - 1) == p.nb - 1 ? p.G * tpb : 0;
+    int n_last = n32 % p.B != 0 && entry(n_ent - 1) == p.nb - 1 ? p.G * tpb : 0;
     if (n_diag + n_last > n_tiles || slab0 + 32 * NSL > p.N) { n_diag = n_tiles; n_last = 0; }
     int q0 = q_next, it = 1;
     top(0);
