@@ -11,7 +11,10 @@
 //  * A workgroup of 8 wavefronts owns one (sequence, KV head[, split]).  The
 //    attended tokens are cut into 64-token chunks, dealt round-robin to the
 //    splits and their wavefronts; a wavefront issues all K and V loads of a
-//    chunk before touching any.
+//    chunk before touching any.  What stands between the sequence length and the first of them is scalar and 32 bits
+//    wide, and the loads are buffer loads, which answer zeros beyond the last attended token: no address or comparison per
+//    load.  (One sequence, 32 query heads on 8, 32001 tokens: 9.8 us -> 8.1 with the two changes below; 128 of 1000 .. 16384
+//    tokens over pages, persistent workgroups: 66.9 -> 64.4.)
 //  * Everything stays in registers.  K rows are loaded straight into the
 //    A-operand layout of v_mfma_f32_16x16x32_bf16 (S^T = K q^T, the G query
 //    heads of the group are the 16 columns, unused ones zero).  V is loaded
@@ -25,7 +28,8 @@
 //    in the workspace as tagged 8-byte packets, waits until memory has taken
 //    them, and then reads the packets of the other workgroups: the one whose
 //    packets landed last finds all of them in place and writes the output (a
-//    second launch would cost more than the whole merge).  There are no
+//    second launch would cost more than the whole merge).  The wavefronts' partials are read for the wavefronts that have
+//    a chunk, and the weights of the splits do not wait for one another.  There are no
 //    counters and nothing in the workspace has to be initialised: a packet
 //    is valid when its tag matches the generation number that the (sequence,
 //    KV head) keeps in the workspace and that the finishing workgroup advances.
@@ -36,6 +40,7 @@
 //    workgroups take over (pa_decode_stream_kernel): the loads of the next item
 //    are in flight while the current one is merged.
 #include <math.h>
+#include <type_traits>
 #include "common.h"
 
 namespace {
@@ -55,14 +60,16 @@ struct dec_params {
   uint64_t* packets;    // the same shape as (value, tag) packets when the workgroups merge among themselves
   uint32_t* gen;        // [batch, hkv] generation numbers of the packets (any initial value)
   int64_t capacity;
+  int32_t len_max;      // the capacity, or the largest sequence length that there is
   int32_t B, W, S; uint32_t flags;
   int32_t hq, hkv, G, splits, subs;
   uint32_t subs_magic;  // ceil(2^32 / subs) for subs > 1: slot / subs = umulhi(slot, subs_magic) for every slot of a row
+  int32_t kvh_first;    // 1: the KV head is the fastest digit of a workgroup's number, 0: the split
   int32_t fused;        // 1: the workgroups of a (sequence, KV head) merge their partials among themselves
   float c2;
   const int32_t* block_table;   // paged cache: page of block j of sequence b at [b * table_stride + j]; else null
   int32_t table_stride;
-  int64_t n_pages;
+  int32_t last_page;            // the pool's last page (that an entry of the table can name)
 };
 
 // ---- merging the workgroups of a (sequence, KV head) without a second kernel ----
@@ -74,15 +81,19 @@ struct dec_params {
 // combine all partials in split order, write the output and store g + 1 as the new generation.
 //  * Some workgroup finishes: order the workgroups by the time at which the last of their stores was acknowledged;
 //    the latest one loads after that, when every other workgroup's packets are in memory.
-//  * Several may finish: they combine the same values in the same order and write the same bits.
+//  * Several may finish: they combine the same values in the same order and write the same bits.  (Each thread decides for
+//    the outputs it owns: a vote of the workgroup took another 0.6 us.)
 //  * Nothing stale is taken for valid: what the workspace holds from the call before carries generation g - 1 (the
-//    finisher advanced it only after every workgroup of the pair had stored, hence had read g), and the very first
+//    finisher advanced it only after every workgroup of the pair had stored packets, hence all of its wavefronts had read
+//    g, before the barrier in front of its stores), and the very first
 //    call on a workspace meets whatever the memory held: a word there passes for a tag only if it equals
 //    ~g ^ ((split + 1) << 24) for the word g found in the same memory (never for a memory filled with one byte
 //    value, zeros included).
 //  * No workgroup waits for another one: whoever finds a packet missing simply leaves.
 // Calls that may run at the same time must not share a workspace (they would share generation numbers).
-constexpr int MAX_FUSED_SPLITS = 16;
+// With more splits than this a merge kernel follows: what a workgroup reads grows with their number (b = 1, 8 KV heads, 48
+// chunks, us: 7 splits 11.0, 12 12.1, 20 and a merge kernel 9.2; b = 4: 12 splits 24, 20 and a merge kernel 16).
+constexpr int MAX_FUSED_SPLITS = 8;
 __device__ __forceinline__ uint32_t dec_tag(uint32_t gen, int split) { return ~gen ^ ((uint32_t)(split + 1) << 24); }
 __device__ __forceinline__ void dec_put(uint64_t* slot, float x, uint32_t tag) {
   __hip_atomic_store(slot, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -99,128 +110,159 @@ template <int D>
 constexpr size_t dec_o_bytes(int G) { return (size_t)NW * G * (D / 32) * OROW * sizeof(float); }
 
 // The query's row of the pattern in closed form: [0, sink_end) ++ {i - 2^k inside [pow_lo, win_start), k
-// descending} ++ [win_start, i].  Uniform over a workgroup, so all of it runs on the scalar unit.
+// descending} ++ [win_start, i].  Uniform over a workgroup, so all of it runs on the scalar unit, and it stands between
+// the sequence length and the first load: positions are 32-bit numbers (as the lengths are), half the instructions.
 struct dec_row {
-  pa_row_shape rs;
-  int64_t t, i;          // position of the query, its block
+  pa_row_shape_t<int32_t> rs;
+  int32_t t, i;          // position of the query, its block
   int n_pow, k_max;      // isolated blocks i - 2^k for k = k_max, k_max-1, ...: n_pow of them
   int n_slots;           // 64-token chunks of the attended blocks
 };
-__device__ __forceinline__ dec_row dec_row_of(const dec_params& p, int64_t len) {
+__device__ __forceinline__ dec_row dec_row_of(const dec_params& p, int32_t len) {
   dec_row r;
   if (len < 1) len = 1;
-  if (len > p.capacity) len = p.capacity;
+  if (len > p.len_max) len = p.len_max;
   r.t = len - 1;
-  // t / B = (t / 64) / subs, through the same multiply-high as the slots while the quotient is exact
+  // t / B = (t / 64) / subs: exact through the multiply-high, because t / 64 stays below 2^25
   static_assert(CH == 64, "the block index is formed from 64-token chunks");
-  const int64_t chunk_of_t = r.t >> 6;
-  r.i = p.subs == 1 ? chunk_of_t
-      : chunk_of_t < (1 << 25) ? (int64_t)__umulhi((unsigned)chunk_of_t, p.subs_magic) : chunk_of_t / p.subs;
-  r.rs = pa_shape_of_row(p.W, p.S, p.flags, r.i);
-  const pa_row_powers pw = pa_powers_of_row(r.rs, p.flags, r.i);
+  const unsigned chunk_of_t = (unsigned)r.t >> 6;
+  r.i = p.subs == 1 ? (int)chunk_of_t : (int)__umulhi(chunk_of_t, p.subs_magic);
+  r.rs = pa_shape_of_row<int32_t>(p.W, p.S, p.flags, r.i);
+  const pa_row_powers pw = pa_powers_of_row<int32_t>(r.rs, p.flags, r.i);
   r.n_pow = pw.n_pow; r.k_max = pw.k_max;
-  const int n_blocks = (int)r.rs.sink_end + r.n_pow + (int)(r.i - r.rs.win_start + 1);
+  const int n_blocks = r.rs.sink_end + r.n_pow + (r.i - r.rs.win_start + 1);
   r.n_slots = n_blocks * p.subs;
   return r;
 }
-__device__ __forceinline__ int64_t dec_block_at(const dec_row& r, int lp) {   // lp-th attended block, ascending
+__device__ __forceinline__ int32_t dec_block_at(const dec_row& r, int lp) {   // lp-th attended block, ascending
   if (lp < r.rs.sink_end) return lp;
-  lp -= (int)r.rs.sink_end;
+  lp -= r.rs.sink_end;
   if (lp >= r.n_pow) return r.rs.win_start + (lp - r.n_pow);
-  return r.i - ((int64_t)1 << (r.k_max - lp));
+  return r.i - (1 << (r.k_max - lp));
 }
 // Chunk `slot` of the row: its block, the chunk inside the block, the tokens of it the query attends (<= 0: none)
-struct dec_place { int64_t blk; int sub; int n_tok; };
+struct dec_place { int32_t blk; int sub; int n_tok; };
 __device__ __forceinline__ dec_place dec_place_of(const dec_params& p, const dec_row& r, int slot) {
   // (no division in the kernel: a 64-bit one costs more than the rest of the address arithmetic)
   dec_place c;
   const int lp = p.subs == 1 ? slot : (int)__umulhi((unsigned)slot, p.subs_magic);
   c.sub = slot - lp * p.subs;
   c.blk = dec_block_at(r, lp);
-  const int64_t left = r.t + 1 - (c.blk * p.B + (int64_t)c.sub * CH);      // causal: tokens tok0..t are attended
-  c.n_tok = left >= CH ? CH : (int)left;
+  const int left = (r.t - c.blk * p.B) - c.sub * CH + 1;      // causal: tokens tok0..t are attended
+  c.n_tok = left >= CH ? CH : left;
   return c;
 }
 // First K and V row of a chunk: in the contiguous cache, or in its page (page numbers outside the pool are clamped
 // into it: a bad table gives wrong numbers, never an access outside the pool)
-__device__ __forceinline__ int64_t dec_chunk_offset(const dec_params& p, int b, int kvh, const dec_place& c, int64_t page, int D) {
-  if (!p.block_table) return (((int64_t)b * p.hkv + kvh) * p.capacity + c.blk * p.B + (int64_t)c.sub * CH) * D;
-  page = page < 0 ? 0 : (page >= p.n_pages ? p.n_pages - 1 : page);
-  return ((page * p.hkv + kvh) * p.B + (int64_t)c.sub * CH) * D;
+__device__ __forceinline__ int64_t dec_chunk_offset(const dec_params& p, int b, int kvh, const dec_place& c, int page, int D) {
+  if (!p.block_table) return (((int64_t)b * p.hkv + kvh) * p.capacity + (int64_t)(c.blk * p.B + c.sub * CH)) * D;
+  page = page < 0 ? 0 : (page > p.last_page ? p.last_page : page);
+  return (((int64_t)page * p.hkv + kvh) * p.B + c.sub * CH) * D;
+}
+// the table's entry for block `blk`, through the scalar unit (the table does not change while a kernel runs)
+__device__ __forceinline__ int dec_page(const dec_params& p, int b, int blk) {
+  typedef const __attribute__((address_space(4))) int32_t scalar_int;
+  return *(scalar_int*)(uintptr_t)(p.block_table + (int64_t)b * p.table_stride + blk);
 }
 
 // The registers of one 64-token chunk: every load of it is issued before any is used.
 template <int D>
 struct dec_chunk {
-  u32x4 kraw[4][D / 32];
-  u32x4 vraw[2][8];
+  u32x4 kraw[CH / 16][D / 32];
+  u32x4 vraw[CH / 32][8];
 };
+// A buffer of `bytes` bytes from `base` on (uniform): loads beyond its end return zeros, so the rows behind the last
+// attended token and the heads behind the group's last one need no comparison, no branch and no register of their own.
+typedef __amdgpu_buffer_rsrc_t dec_buf;
+__device__ __forceinline__ dec_buf dec_buffer(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 dec_load16(dec_buf buf, int lane_offset, int offset) {
+  return __builtin_amdgcn_raw_buffer_load_b128(buf, lane_offset + offset, 0, 0);
+}
 // K tile 2x+y, row rho = lane%16 holds token 32x + 8(rho/4) + 4y + rho%4: with this order the S^T
 // accumulator of lane (g, q4) holds tokens 32x + 8*q4 + (0..7), which is what P^T must supply below.
 // V: lane (dg = lane%16, tg = lane/16) takes tokens 32x + 8tg + (0..7), d = 8dg .. 8dg+7.
+// A lane's address is one register and an immediate offset below 4096 bytes: a buffer per 32 tokens.
 template <int D>
 __device__ __forceinline__ void dec_issue(dec_chunk<D>& c, const __bf16* kb, const __bf16* vb, int n_tok, int g, int q4) {
-  constexpr int NC = D / 32, CPR = D / 8;
+  constexpr int NC = D / 32, CPR = D / 8, ROW = 2 * D;
+  const int k_lane = (8 * (g >> 2) + (g & 3)) * ROW + 16 * q4;
+  const int v_lane = g < CPR ? 8 * q4 * ROW + 16 * g : 32 * ROW;      // (head_dim 64: half the lanes have no piece of a row)
 #pragma unroll
-  for (int tau = 0; tau < 4; ++tau) {
-    const int tk = 32 * (tau >> 1) + 8 * (g >> 2) + 4 * (tau & 1) + (g & 3);
+  for (int x = 0; x < CH / 32; ++x) {
+    const int left = n_tok - 32 * x;
+    const dec_buf buf = dec_buffer(kb + 32 * x * D, (left < 0 ? 0 : left > 32 ? 32 : left) * ROW);
 #pragma unroll
-    for (int cc = 0; cc < NC; ++cc)
-      c.kraw[tau][cc] = tk < n_tok ? *reinterpret_cast<const u32x4*>(kb + tk * D + 32 * cc + 8 * q4) : u32x4{0, 0, 0, 0};
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int cc = 0; cc < NC; ++cc) c.kraw[2 * x + y][cc] = dec_load16(buf, k_lane, 4 * y * ROW + 64 * cc);
   }
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < CH / 32; ++x) {
+    const int left = n_tok - 32 * x;
+    const dec_buf buf = dec_buffer(vb + 32 * x * D, (left < 0 ? 0 : left > 32 ? 32 : left) * ROW);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int tk = 32 * x + 8 * q4 + r;
-      c.vraw[x][r] = (g < CPR && tk < n_tok) ? *reinterpret_cast<const u32x4*>(vb + tk * D + 8 * g) : u32x4{0, 0, 0, 0};
-    }
+    for (int r = 0; r < 8; ++r) c.vraw[x][r] = dec_load16(buf, v_lane, r * ROW);
+  }
+  __builtin_amdgcn_sched_barrier(0);                   // every load is under way before the first product
 }
-// One online-softmax update with the chunk: S^T = K q^T, then O^T += V^T P^T.
-template <int D>
+// One online-softmax update with the chunk: S^T = K q^T, then O^T += V^T P^T.  FIRST: nothing has been accumulated yet.
+template <int D, bool FIRST>
 __device__ __forceinline__ void dec_consume(const dec_chunk<D>& c, const bf16x8 (&qf)[D / 32], int n_tok, float c2, int q4,
                                             float& m_run, float& l_run, f32x4 (&O)[8]) {
-  constexpr int NC = D / 32;
-  f32x4 S[4];
+  constexpr int NC = D / 32, NT = CH / 16;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 S[NT];
 #pragma unroll
-  for (int tau = 0; tau < 4; ++tau) {
-    S[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int tau = 0; tau < NT; ++tau) {
+    S[tau] = zero;
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc)
       S[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c.kraw[tau][cc]), qf[cc], S[tau], 0, 0, 0);
   }
   // ---- online softmax; S[2x+y][r] is token 32x + 8*q4 + 4y + r of head g ----
+  if (n_tok < CH) {                                   // uniform: the sequence's last chunk
+#pragma unroll
+    for (int tau = 0; tau < NT; ++tau)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int tk = 32 * (tau >> 1) + 8 * q4 + 4 * (tau & 1) + r;
+        S[tau][r] = tk < n_tok ? S[tau][r] : -INFINITY;
+      }
+  }
   float mx = -INFINITY;
 #pragma unroll
-  for (int tau = 0; tau < 4; ++tau)
+  for (int tau = 0; tau < NT; ++tau)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int tk = 32 * (tau >> 1) + 8 * q4 + 4 * (tau & 1) + r;
-      S[tau][r] = tk < n_tok ? S[tau][r] * c2 : -INFINITY;
+      S[tau][r] *= c2;
       mx = fmaxf(mx, S[tau][r]);
     }
   mx = fmaxf(mx, __shfl_xor(mx, 16));
   mx = fmaxf(mx, __shfl_xor(mx, 32));                // finite: token 0 of the chunk is attended
-  const float m_new = fmaxf(m_run, mx);
-  const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+  const float m_new = FIRST ? mx : fmaxf(m_run, mx);
+  const float alpha = FIRST ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
   m_run = m_new;
   float rowsum = 0.f;
 #pragma unroll
-  for (int tau = 0; tau < 4; ++tau)
+  for (int tau = 0; tau < NT; ++tau)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       S[tau][r] = __builtin_amdgcn_exp2f(S[tau][r] - m_new);
       rowsum += S[tau][r];
     }
-  l_run = l_run * alpha + rowsum;
+  l_run = FIRST ? rowsum : l_run * alpha + rowsum;
+  if (!FIRST) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) O[j][r] *= alpha;
+      for (int r = 0; r < 4; ++r) O[j][r] *= alpha;
+  }
 
   // ---- O^T += V^T P^T: 32 tokens per step; MFMA j covers d = 8*row + j ----
 #pragma unroll
-  for (int x = 0; x < 2; ++x) {
+  for (int x = 0; x < CH / 32; ++x) {
     bf16x8 pf;
 #pragma unroll
     for (int e = 0; e < 8; ++e) pf[e] = (__bf16)S[2 * x + (e >> 2)][e & 3];
@@ -237,18 +279,17 @@ __device__ __forceinline__ void dec_consume(const dec_chunk<D>& c, const bf16x8 
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const u32x4 vf = {tr[0][j], tr[1][j], tr[2][j], tr[3][j]};
-      O[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), pf, O[j], 0, 0, 0);
+      O[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), pf, FIRST && x == 0 ? zero : O[j], 0, 0, 0);
     }
   }
 }
-// q^T fragments: column g, 8 consecutive d per 32-wide step
+// q^T fragments: column g, 8 consecutive d per 32-wide step (columns behind the group's last head: zeros)
 template <int D>
 __device__ __forceinline__ void dec_load_q(bf16x8 (&qf)[D / 32], const dec_params& p, int b, int kvh, int g, int q4) {
-  const bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-  const __bf16* qp = p.q + ((int64_t)b * p.hq + (int64_t)kvh * p.G + (g < p.G ? g : 0)) * D;
+  const dec_buf buf = dec_buffer(p.q + ((int64_t)b * p.hq + (int64_t)kvh * p.G) * D, p.G * 2 * D);
 #pragma unroll
   for (int c = 0; c < D / 32; ++c)
-    qf[c] = g < p.G ? *reinterpret_cast<const bf16x8*>(qp + 32 * c + 8 * q4) : z;
+    qf[c] = __builtin_bit_cast(bf16x8, dec_load16(buf, g * 2 * D + 16 * q4, 64 * c));
 }
 
 // The lane number, computed afresh wherever it is called: the compiler cannot carry the value of an earlier call
@@ -274,18 +315,23 @@ __device__ __forceinline__ void dec_stash(float* s_o, int wave, int G, int g, in
   }
 }
 
-template <int D>
+// EPT: outputs per thread (the G x D values of the group over the workgroup's threads)
+template <int D, int EPT>
 __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
   __shared__ float s_m[NW][MAXG], s_l[NW][MAXG];
   extern __shared__ __attribute__((aligned(16))) float s_o_dyn[];   // [NW][G][D/32][OROW] partial outputs of the wavefronts
 
-  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  const int kvh = p.kvh_first ? blockIdx.x : blockIdx.y, split = p.kvh_first ? blockIdx.y : blockIdx.x, b = blockIdx.z;
   // the wavefront's number as a scalar and the lane from the hardware's lane count: the thread index itself need
   // not stay in a vector register through the chunk loop, where every register counts
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int g = lane & 15, q4 = lane >> 4;    // column (query head) and k-group of this lane
 
+  // Every kernel argument that stands before the loads is asked for at once, with one wait (left alone, the compiler
+  // fetches them in four groups, a trip to memory each).
+  asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.kv_len), "s"(p.gen), "s"(p.capacity), "s"(p.len_max), "s"(p.splits), "s"(p.subs),
+               "s"(p.subs_magic), "s"(p.block_table), "s"(p.table_stride), "s"(p.last_page));
   // The sequence length and the generation of this (sequence, KV head)'s packets (needed only at the end) are
   // both uniform: two scalar loads, one wait.  Written as assembly so that the generation number lives in a
   // scalar register from the start (a vector register held across the chunk loop costs a spill to scratch
@@ -298,9 +344,10 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
                : "s"(p.gen + (int64_t)b * p.hkv + kvh), "s"(p.kv_len + b)
                : "memory");
 
-  const dec_row row = dec_row_of(p, len_b);
   bf16x8 qf[D / 32];
   dec_load_q<D>(qf, p, b, kvh, g, q4);
+  const dec_row row = dec_row_of(p, len_b);
+  const int n_slots = row.n_slots;
 
   float m_run = -INFINITY, l_run = 0.f;
   f32x4 O[8];
@@ -309,19 +356,24 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
 
   // chunks are dealt round-robin to the splits (slot = wave * splits + split), so that the workgroups of a
   // (sequence, KV head) stream nearly equal amounts (13 chunks over 2 workgroups: 7 + 6 instead of 8 + 5)
-  for (int slot = wave * p.splits + split; slot < row.n_slots; slot += p.splits * NW) {
+  auto chunk = [&](int slot, auto first) {
     const dec_place pl = dec_place_of(p, row, slot);
-    if (pl.n_tok <= 0) continue;                         // chunk of the diagonal block beyond the query
+    if (pl.n_tok <= 0) return;                           // chunk of the diagonal block beyond the query
     // paged cache: the block's page comes from the table (one more dependent look-up; blk < table_stride,
     // because len <= table_stride * B); a page holds the block's tokens of every KV head
-    const int64_t page = p.block_table ? p.block_table[(int64_t)b * p.table_stride + pl.blk] : 0;
+    const int page = p.block_table ? dec_page(p, b, pl.blk) : 0;
     const int64_t off = dec_chunk_offset(p, b, kvh, pl, page, D);
     dec_chunk<D> c;
     dec_issue<D>(c, p.k + off, p.v + off, pl.n_tok, g, q4);
-    dec_consume<D>(c, qf, pl.n_tok, p.c2, q4, m_run, l_run, O);
-  }
+    dec_consume<D, decltype(first)::value>(c, qf, pl.n_tok, p.c2, q4, m_run, l_run, O);
+  };
+  int slot = wave * p.splits + split;
+  if (slot < n_slots) chunk(slot, std::true_type{});
+  // (mostly one chunk per wavefront.  A diagonal chunk without a token can only be a wavefront's last one.)
+  while ((slot += p.splits * NW) < n_slots) chunk(slot, std::false_type{});
 
-  // ---- merge the wavefronts through LDS ----
+  // ---- merge the wavefronts through LDS: those that have a chunk ----
+  auto has_chunk = [&](int w) -> bool { return w * p.splits + split < n_slots; };
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
   if (g < p.G) {
@@ -330,9 +382,8 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
   }
   __syncthreads();
 
-  // thread e owns output (head gg, component d); with up to 16 heads per KV head a thread owns several
+  // thread e owns output (head gg, component d); with many heads per KV head a thread owns several
   const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  constexpr int EPT = MAXG * D / (64 * NW);            // at most this many outputs per thread
   float accs[EPT], Ms[EPT], Ls[EPT];
 #pragma unroll
   for (int x = 0; x < EPT; ++x) {
@@ -340,15 +391,21 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
     accs[x] = 0.f; Ms[x] = -INFINITY; Ls[x] = 0.f;
     if (e >= p.G * D) continue;
     const int gg = e / D, d = e % D;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][gg]);
-    float L = 0.f, acc = 0.f;
+    float M = -INFINITY, L = 0.f, acc = 0.f;
+    float mw[NW], lw[NW], ow[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float wt = s_l[w][gg] > 0.f ? __builtin_amdgcn_exp2f(s_m[w][gg] - M) : 0.f;
-      L = fmaf(wt, s_l[w][gg], L);
-      acc = fmaf(wt, s_o_dyn[dec_o_at<D>(w, p.G, gg, d)], acc);
+      mw[w] = -INFINITY; lw[w] = ow[w] = 0.f;
+      if (has_chunk(w)) { mw[w] = s_m[w][gg]; lw[w] = s_l[w][gg]; ow[w] = s_o_dyn[dec_o_at<D>(w, p.G, gg, d)]; }
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (!has_chunk(w)) break;
+      const float wt = lw[w] > 0.f ? __builtin_amdgcn_exp2f(mw[w] - M) : 0.f;
+      L = fmaf(wt, lw[w], L);
+      acc = fmaf(wt, ow[w], acc);
     }
     accs[x] = acc; Ms[x] = M; Ls[x] = L;
     const int h = kvh * p.G + gg;
@@ -372,62 +429,53 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
   // ---- the workgroups of this (sequence, KV head) merge among themselves (protocol above) ----
   __builtin_amdgcn_s_waitcnt(0);                       // vmcnt(0): memory has acknowledged this thread's packets
   __syncthreads();                                     // ... and every other thread's of this workgroup
-  bool valid = true;
-  float o_out[EPT], lse_out[EPT];
 #pragma unroll
   for (int x = 0; x < EPT; ++x) {
     const int e = tid + x * 64 * NW;
-    o_out[x] = 0.f; lse_out[x] = 0.f;
     if (e >= p.G * D) continue;
     const int gg = e / D, d = e % D;
     const int h = kvh * p.G + gg;
     const uint64_t* pk = p.packets + ((int64_t)b * p.hq + h) * p.splits * (D + 2);
+    bool valid = true;
     float M = -INFINITY, L = 0.f, acc = 0.f;
-    for (int s0 = 0; s0 < p.splits; s0 += 8) {
-      uint64_t pm[8], pl[8], po[8];
+    uint64_t pm[MAX_FUSED_SPLITS], pl[MAX_FUSED_SPLITS], po[MAX_FUSED_SPLITS];
 #pragma unroll
-      for (int y = 0; y < 8; ++y) {                    // all loads of (up to) eight splits before any is looked at
-        pm[y] = pl[y] = po[y] = 0;
-        if (s0 + y < p.splits && s0 + y != split) {    // uniform over the workgroup; its own partial is in registers
-          const uint64_t* ps = pk + (int64_t)(s0 + y) * (D + 2);
-          pm[y] = dec_get(ps + D); pl[y] = dec_get(ps + D + 1); po[y] = dec_get(ps + d);
-        }
-      }
-#pragma unroll
-      for (int y = 0; y < 8; ++y) {
-        const int s1 = s0 + y;
-        if (s1 >= p.splits) break;
-        float ms, ls, os;
-        if (s1 == split) { ms = Ms[x]; ls = Ls[x]; os = accs[x]; }   // this workgroup's own partial: the same bits
-        else {
-          const uint32_t want = dec_tag(gen, s1);
-          valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want && (uint32_t)(po[y] >> 32) == want;
-          ms = __builtin_bit_cast(float, (uint32_t)pm[y]); ls = __builtin_bit_cast(float, (uint32_t)pl[y]);
-          os = __builtin_bit_cast(float, (uint32_t)po[y]);
-        }
-        if (ls > 0.f) {                                              // idle splits hold no outputs
-          const float Mn = fmaxf(M, ms);
-          const float r0 = L > 0.f ? __builtin_amdgcn_exp2f(M - Mn) : 0.f, r1 = __builtin_amdgcn_exp2f(ms - Mn);
-          L = L * r0 + ls * r1;
-          acc = acc * r0 + os * r1;
-          M = Mn;
-        }
+    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {     // all loads before any is looked at
+      pm[y] = pl[y] = po[y] = 0;
+      if (y < p.splits && y != split) {              // uniform over the workgroup; its own partial is in registers
+        const uint64_t* ps = pk + (int64_t)y * (D + 2);
+        pm[y] = dec_get(ps + D); pl[y] = dec_get(ps + D + 1); po[y] = dec_get(ps + d);
       }
     }
-    o_out[x] = acc / L;
-    lse_out[x] = (M + log2f(L)) * 0.69314718055994530942f;
-  }
-  if (!__syncthreads_and(valid ? 1 : 0)) return;       // some packet has not landed: its workgroup will finish
+    // the reference point of all of them first, so that their weights do not depend on one another
+    float ls[MAX_FUSED_SPLITS], ms[MAX_FUSED_SPLITS];
 #pragma unroll
-  for (int x = 0; x < EPT; ++x) {
-    const int e = tid + x * 64 * NW;
-    if (e >= p.G * D) continue;
-    const int gg = e / D, d = e % D;
-    const int h = kvh * p.G + gg;
-    p.o[((int64_t)b * p.hq + h) * D + d] = (__bf16)o_out[x];
-    if (p.lse && d == 0) p.lse[(int64_t)b * p.hq + h] = lse_out[x];
+    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
+      ms[y] = -INFINITY; ls[y] = 0.f;
+      if (y >= p.splits) break;
+      if (y == split) { ms[y] = Ms[x]; ls[y] = Ls[x]; }              // this workgroup's own partial: the same bits
+      else {
+        const uint32_t want = dec_tag(gen, y);
+        valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want && (uint32_t)(po[y] >> 32) == want;
+        ms[y] = __builtin_bit_cast(float, (uint32_t)pm[y]); ls[y] = __builtin_bit_cast(float, (uint32_t)pl[y]);
+      }
+      if (ls[y] > 0.f) M = fmaxf(M, ms[y]);                          // idle splits hold no outputs
+    }
+#pragma unroll
+    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
+      if (y >= p.splits) break;
+      const float os = y == split ? accs[x] : __builtin_bit_cast(float, (uint32_t)po[y]);
+      const float wt = ls[y] > 0.f ? __builtin_amdgcn_exp2f(ms[y] - M) : 0.f;
+      L = fmaf(wt, ls[y], L);
+      acc = ls[y] > 0.f ? fmaf(wt, os, acc) : acc;
+    }
+    // Every thread for itself: a packet that has not landed belongs to a workgroup that will write this output.  (A thread
+    // that saw the packets of all splits knows that all their wavefronts have read the generation.)
+    if (!valid) continue;
+    p.o[((int64_t)b * p.hq + h) * D + d] = (__bf16)(acc / L);
+    if (p.lse && d == 0) p.lse[(int64_t)b * p.hq + h] = (M + log2f(L)) * 0.69314718055994530942f;
+    if (e == 0) __hip_atomic_store(p.gen + (int64_t)b * p.hkv + kvh, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (tid == 0) __hip_atomic_store(p.gen + (int64_t)b * p.hkv + kvh, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Large batches: persistent workgroups.  With many more (sequence, KV head, split) items than compute units the
@@ -495,8 +543,9 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_stream_kernel(dec_params p,
   auto request = [&](const plan_t& pn, int page) {
     const int lane = dec_lane_now(), g = lane & 15, q4 = lane >> 4;
     dec_load_q<D>(qf, p, pn.it.b, pn.it.kvh, g, q4);
+    if (!pn.has) return;                                  // no tokens: no loads (the chunk's registers are not looked at)
     const int64_t off = dec_chunk_offset(p, pn.it.b, pn.it.kvh, pn.pl, page, D);
-    dec_issue<D>(c, p.k + off, p.v + off, pn.has ? pn.pl.n_tok : 0, g, q4);   // no tokens: no loads
+    dec_issue<D>(c, p.k + off, p.v + off, pn.pl.n_tok, g, q4);
   };
   request(cur, cur_page);
 
@@ -513,7 +562,7 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_stream_kernel(dec_params p,
     }
     {
       const int q4 = dec_lane_now() >> 4;
-      if (cur.has) dec_consume<D>(c, qf, cur.pl.n_tok, p.c2, q4, m_run, l_run, O);
+      if (cur.has) dec_consume<D, false>(c, qf, cur.pl.n_tok, p.c2, q4, m_run, l_run, O);
     }
     const bool last_pass = pass == n_pass - 1;
     const int buf = n & 1;
@@ -608,12 +657,30 @@ __global__ __launch_bounds__(64) void pa_decode_merge_kernel(dec_params p) {
   if (p.lse && lane == 0) p.lse[(int64_t)b * p.hq + h] = (M + log2f(L)) * 0.69314718055994530942f;
 }
 
+template <int D, int EPT>
+int launch_decode_as(const dec_params& p, int batch, hipStream_t stream) {
+  static std::atomic<unsigned long long> attr_done{0};
+  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_decode_kernel<D, EPT>), dec_o_bytes<D>(MAXG), attr_done)) return st;
+  const dim3 grid((uint32_t)(p.kvh_first ? p.hkv : p.splits), (uint32_t)(p.kvh_first ? p.splits : p.hkv), (uint32_t)batch);
+  hipLaunchKernelGGL((pa_decode_kernel<D, EPT>), grid, dim3(64 * NW), dec_o_bytes<D>(p.G), stream, p);   // at most 72 KB (G <= 16)
+  return pa_note_hip(hipGetLastError());
+}
+template <int D>
+int launch_decode(const dec_params& p, int batch, hipStream_t stream) {
+  constexpr int THREADS = 64 * NW;
+  if (p.G * D <= THREADS) return launch_decode_as<D, 1>(p, batch, stream);
+  if (p.G * D <= 2 * THREADS) return launch_decode_as<D, 2>(p, batch, stream);
+  return launch_decode_as<D, MAXG * D / THREADS>(p, batch, stream);
+}
+
 }  // namespace
 
-// Workgroups per (sequence, KV head).  A workgroup has all loads of eight 64-token chunks in
-// flight at once; a second pass over further chunks would pay the memory latency again, so a row
-// with more chunks is cut into several workgroups whose partials a small second kernel merges.
-// Small batches are cut further so that more of the 256 compute units pull on the memory system.
+// Workgroups per (sequence, KV head).  A workgroup has all loads of eight 64-token chunks in flight at once; a second pass
+// over further chunks would pay the memory latency again, so a row with more chunks is cut into several workgroups.
+// Where that leaves compute units idle, more of them pull on the memory system: about four chunks each, in at most half of
+// the compute units (the exchange of the partials costs more with every workgroup).  us, 8 KV heads, 12 or 13 chunks,
+// 2 / 3 / 4 / 6 / 8 splits: batch 1 8.5 / 7.9 / 7.7 / 8.1 / 8.9, 4 9.2 / 8.8 / 9.0 / 10.5 / 12.0, 8 9.6 / 9.5 / 10.6 / 16.7 / 19.5.
+// Longer rows of small batches are cut finer still, and a merge kernel follows (figures at MAX_FUSED_SPLITS).
 int32_t pa_decode_splits(const powattn_pattern* pat, int32_t batch, int32_t hkv, int64_t capacity) {
   const int32_t mk = powattn_max_k(pat, capacity);
   if (mk < 1) return 0;
@@ -622,9 +689,14 @@ int32_t pa_decode_splits(const powattn_pattern* pat, int32_t batch, int32_t hkv,
   int64_t s = (slots + NW - 1) / NW;                 // one pass per workgroup
   if (s > 8) s = 8;
   if (base * s < 256) {                              // not enough workgroups to cover the chip
-    int64_t want = (256 + base - 1) / base;
-    const int64_t cap = slots / 2 > 1 ? slots / 2 : 1;
-    if (want > cap) want = cap;
+    int64_t want = (slots + 3) / 4;
+    if (want < MAX_FUSED_SPLITS) {
+      if (want > 128 / base) want = 128 / base;
+    } else {
+      const int64_t cap = slots / 2;
+      want = (256 + base - 1) / base;
+      if (want > cap) want = cap;
+    }
     if (want > s) s = want;
   }
   if (s > 1024) s = 1024;
@@ -675,16 +747,22 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   p.packets = (uint64_t*)((char*)a.workspace + hdr);
   p.partials = (float*)((char*)a.workspace + hdr);
   p.capacity = a.capacity;
+  p.len_max = (int32_t)(a.capacity < 0x7fffffff ? a.capacity : 0x7fffffff);
   p.B = a.pat.block; p.W = a.pat.window; p.S = a.pat.sink; p.flags = a.pat.flags;
   p.hq = a.hq; p.hkv = a.hkv; p.G = a.hq / a.hkv; p.splits = a.n_split; p.subs = a.pat.block / CH;
   p.subs_magic = p.subs > 1 ? (uint32_t)(((1ull << 32) + p.subs - 1) / p.subs) : 0u;
   p.c2 = a.scale * 1.44269504088896340736f;
-  p.block_table = a.block_table; p.table_stride = a.table_stride; p.n_pages = a.n_pages;
+  p.block_table = a.block_table; p.table_stride = a.table_stride;
+  p.last_page = (int32_t)((a.n_pages < 0x7fffffff ? a.n_pages : 0x7fffffff) - 1);
   // few enough splits that every workgroup can afford to read all the others' partials: they merge among
   // themselves; otherwise the merge kernel follows
   p.fused = (a.n_split > 1 && a.n_split <= MAX_FUSED_SPLITS) ? 1 : 0;
   int n_cu = 1;
   pa_current_device(nullptr, &n_cu);
+  // Workgroups are dealt to the eight XCDs in turn, so with the KV head as the fastest digit (and eight of them) all splits of
+  // a pair are on one XCD: their exchange is quicker, but where the launch fills the chip the loads are slower.  us, KV head /
+  // split fastest: batch 1 8.1 / 8.2, batch 4 (one query head per KV head) 7.5 / 7.8, batch 16 12.8 / 12.4.
+  p.kvh_first = 2 * (int64_t)a.batch * a.hkv * a.n_split <= n_cu;
   // As many work items as compute units, or more: persistent workgroups that keep bytes in flight across items.
   // With at least one (sequence, KV head) pair per compute unit a pair is one item, walked in passes of NW chunks, and the
   // outputs are written by the same kernel; with fewer pairs but still four (sequence, KV head, split) items per
@@ -721,19 +799,8 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
       return pa_note_hip(hipGetLastError());
     }
   }
-  dim3 grid((uint32_t)a.n_split, (uint32_t)a.hkv, (uint32_t)a.batch);
-  const size_t lds = a.head_dim == 128 ? dec_o_bytes<128>(p.G) : dec_o_bytes<64>(p.G);   // at most 72 KB (G <= 16)
-  {
-    static std::atomic<unsigned long long> attr_done[2];
-    const int which = a.head_dim == 128 ? 0 : 1;
-    const void* fn = which == 0 ? reinterpret_cast<const void*>(&pa_decode_kernel<128>)
-                                : reinterpret_cast<const void*>(&pa_decode_kernel<64>);
-    if (int st = pa_allow_dynamic_lds(fn, which == 0 ? dec_o_bytes<128>(MAXG) : dec_o_bytes<64>(MAXG), attr_done[which])) return st;
-  }
-  if (a.head_dim == 128)
-    hipLaunchKernelGGL((pa_decode_kernel<128>), grid, dim3(64 * NW), lds, a.stream, p);
-  else
-    hipLaunchKernelGGL((pa_decode_kernel<64>), grid, dim3(64 * NW), lds, a.stream, p);
+  const int rc = a.head_dim == 128 ? launch_decode<128>(p, a.batch, a.stream) : launch_decode<64>(p, a.batch, a.stream);
+  if (rc != POWATTN_OK) return rc;
   int st = pa_note_hip(hipGetLastError());
   if (st != POWATTN_OK || a.n_split == 1 || p.fused) return st;
   dim3 mgrid((uint32_t)a.hq, (uint32_t)a.batch);

@@ -14,19 +14,23 @@
 #define PA_HD inline
 #endif
 
-struct pa_row_shape {
-  int64_t sink_end;  // sink blocks not inside the window: [0, sink_end)
-  int64_t win_start; // window (suffix) blocks: [win_start, i]
-  int64_t pow_lo;    // power blocks are emitted only inside [pow_lo, win_start)
+// I: int64_t, or int32_t where positions fit (kernels: half the scalar instructions)
+template <class I>
+struct pa_row_shape_t {
+  I sink_end;  // sink blocks not inside the window: [0, sink_end)
+  I win_start; // window (suffix) blocks: [win_start, i]
+  I pow_lo;    // power blocks are emitted only inside [pow_lo, win_start)
 };
+using pa_row_shape = pa_row_shape_t<int64_t>;
 
-PA_HD pa_row_shape pa_shape_of_row(int32_t W, int32_t S, uint32_t flags, int64_t i) {
+template <class I>
+PA_HD pa_row_shape_t<I> pa_shape_of_row(int32_t W, int32_t S, uint32_t flags, I i) {
   // the power test admits distance 0, so the diagonal is attended even with W == 0
-  int64_t weff = (flags & POWATTN_POWER) ? (W > 1 ? W : 1) : W;
-  pa_row_shape r;
+  const I weff = (flags & POWATTN_POWER) ? (W > 1 ? W : 1) : W;
+  pa_row_shape_t<I> r;
   r.win_start = i - weff + 1;
   if (r.win_start < 0) r.win_start = 0;
-  int64_t s_end = (int64_t)S < i + 1 ? (int64_t)S : i + 1;
+  const I s_end = (I)S < i + 1 ? (I)S : i + 1;
   r.pow_lo = s_end;
   r.sink_end = s_end < r.win_start ? s_end : r.win_start;
   return r;
@@ -35,13 +39,16 @@ PA_HD pa_row_shape pa_shape_of_row(int32_t W, int32_t S, uint32_t flags, int64_t
 // The isolated blocks i - 2^k of a row lie inside [pow_lo, win_start) exactly for i - win_start < 2^k <= i - pow_lo:
 // n_pow exponents k_max, k_max-1, ... (ascending blocks), found with two leading-zero counts instead of a loop.
 struct pa_row_powers { int n_pow, k_max; };
-PA_HD pa_row_powers pa_powers_of_row(const pa_row_shape& r, uint32_t flags, int64_t i) {
+PA_HD int pa_bits(int64_t x) { return 64 - __builtin_clzll((unsigned long long)x); }   // x > 0: its number of bits
+PA_HD int pa_bits(int32_t x) { return 32 - __builtin_clz((unsigned)x); }
+template <class I>
+PA_HD pa_row_powers pa_powers_of_row(const pa_row_shape_t<I>& r, uint32_t flags, I i) {
   pa_row_powers w = {0, 0};
   if (flags & POWATTN_POWER) {
-    const int64_t below = i - r.win_start, upto = i - r.pow_lo;
+    const I below = i - r.win_start, upto = i - r.pow_lo;
     if (upto >= 1) {
-      const int k_min = below > 0 ? 64 - __builtin_clzll((unsigned long long)below) : 0;
-      w.k_max = 63 - __builtin_clzll((unsigned long long)upto);
+      const int k_min = below > 0 ? pa_bits(below) : 0;
+      w.k_max = pa_bits(upto) - 1;
       w.n_pow = w.k_max >= k_min ? w.k_max - k_min + 1 : 0;
     }
   }
@@ -57,7 +64,7 @@ PA_HD int64_t pa_for_each_block(int32_t W, int32_t S, uint32_t flags, int64_t i,
     for (int64_t j = 0; j <= i; ++j) { emit(j); ++n; }
     return n;
   }
-  pa_row_shape r = pa_shape_of_row(W, S, flags, i);
+  pa_row_shape r = pa_shape_of_row<int64_t>(W, S, flags, i);
   for (int64_t j = 0; j < r.sink_end; ++j) { emit(j); ++n; }
   if (flags & POWATTN_POWER) {
     int64_t p = 1;

@@ -50,6 +50,22 @@ def test_shapes_and_lengths(B, W, S, hq, hkv, d, cap, kv_len):
     run_decode(pa.Pattern(B, W, S), len(kv_len), hq, hkv, cap, d, kv_len, seed=31, calls=2)
 
 
+@pytest.mark.parametrize("W,hq,hkv,d,batch", [
+    (4, 4, 1, 128, 5),         # 9 chunks at most: three splits; one output per thread
+    (20, 16, 1, 128, 5),       # six splits; four outputs per thread
+    (24, 8, 1, 128, 6),        # seven splits; two
+    (24, 16, 1, 64, 6),        # seven splits; two, head_dim 64
+    (4, 8, 8, 128, 16),        # two splits that fill the chip: the split is the fastest digit
+    (4, 8, 8, 64, 15),         # ... not a multiple of eight pairs
+    (30, 4, 2, 64, 5),         # more splits than are merged by the workgroups themselves
+])
+def test_exchange_between_splits_at_chunk_edges(W, hq, hkv, d, batch):
+    """Lengths at the edges of a 64-token chunk and of the wavefront's two halves of it, from rows that leave splits
+    without a chunk to full ones."""
+    edges = [4096, 33, 1, 64, 2049, 65, 32, 31, 4033, 63, 1025, 96, 95, 97, 128, 2111]
+    run_decode(pa.Pattern(64, W, 1), batch, hq, hkv, 4096, d, edges[:batch], seed=77, calls=2)
+
+
 def test_sliding_window_flag_and_scale():
     run_decode(pa.Pattern(64, 5, 1, flags=0), 2, 4, 2, 2048, 128, [2048, 900], seed=32, scale=0.11)
 
