@@ -64,7 +64,7 @@ class Pattern:
 
 
 # The C struct of a pattern is built once per set of values (a call only reads it) instead of on every call: 1.3 us of
-# the 8 to 10 us of host time that bound the smallest calls.
+# the host time of the smallest calls.
 @functools.lru_cache(maxsize=256)
 def _pattern_ref(block, window, sink, flags):
     return ctypes.byref(_CPattern(block, window, sink, flags))
@@ -72,10 +72,31 @@ def _pattern_ref(block, window, sink, flags):
 
 _lib = None
 
+# The ordinary calls marshalled natively (csrc/host.cpp): tried first by the functions below once the GPU is in use, and
+# answered with NotImplemented, nothing done, for everything out of the ordinary, which then goes through Python as ever.
+_native = None
+_native_tried = False
+_NATIVE_ENTRY_POINTS = ("num_blocks", "max_k", "mask_build", "prefill", "prefill_chunk", "prefill_chunk_paged",
+                        "prefill_batch_paged", "prefill_varlen", "decode", "decode_paged", "backward_workspace_bytes",
+                        "backward")
+
+
+def _enable_native():
+    global _native, _native_tried
+    _native_tried = True
+    try:
+        from . import _host
+    except ImportError:                  # not built: the Python marshalling below does the same
+        return
+    L = lib()
+    _host.bind(*(ctypes.cast(getattr(L, "powattn_" + name), ctypes.c_void_p).value for name in _NATIVE_ENTRY_POINTS),
+               torch.Tensor, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    _native = _host
+
 
 def lib() -> ctypes.CDLL:
     """Loads the built library (never builds it, never falls back)."""
-    global _lib
+    global _lib, _native, _native_tried
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -126,6 +147,7 @@ def lib() -> ctypes.CDLL:
     L.powattn_backward.argtypes = [P, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i64, i32, i32,
                                    f32, vp, ctypes.c_size_t, vp]
     _lib = L
+    _native, _native_tried = None, False     # (the entry points' addresses are this library's)
     return L
 
 
@@ -144,6 +166,8 @@ def _stream(stream=None):
         # the handle itself: building a torch.cuda.Stream object for it takes longer than the look-up
         if not torch.cuda.is_initialized():
             torch.cuda.init()
+        if not _native_tried:
+            _enable_native()
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -215,6 +239,11 @@ def mask_build(pattern: Pattern, seq_len: int, kv_cnt=None, kv_idx=None, block_m
                want_block_mask=False, device="cuda", stream=None):
     """powattn_mask_build.  Allocates the outputs when they are not given.
     Returns (kv_cnt int32 [nb], kv_idx int32 [nb, max_k], block_mask uint8 [nb, nb] or None)."""
+    if (_native is not None and stream is None and kv_cnt is None and kv_idx is None and block_mask is None
+            and not want_block_mask and isinstance(device, str) and device == "cuda"):
+        r = _native.mask_build(pattern._values, seq_len)
+        if r is not NotImplemented:
+            return r
     nb = num_blocks(pattern, seq_len)
     if kv_idx is None:
         mk = max_k(pattern, seq_len)
@@ -232,6 +261,10 @@ def mask_build(pattern: Pattern, seq_len: int, kv_cnt=None, kv_idx=None, block_m
 def prefill(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o=None, lse=None, softmax_scale=0.0,
             want_lse=True, stream=None):
     """powattn_prefill.  q/o: [b,Hq,N,D]; k/v: [b,Hkv,N,D].  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.prefill(pattern._values, kv_cnt, kv_idx, q, k, v, o, lse, softmax_scale, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, n, d = q.shape
     hkv = k.shape[1]
     if k.shape != (batch, hkv, n, d) or v.shape != k.shape:
@@ -256,6 +289,11 @@ def prefill_chunk(pattern: Pattern, kv_cnt, kv_idx, q, k_cache, v_cache, q_start
                   softmax_scale=0.0, want_lse=True, stream=None):
     """powattn_prefill_chunk.  q/o: [b,Hq,q_len,D] at positions q_start..; caches: [b,Hkv,capacity,D] holding
     positions 0..q_start+q_len-1.  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.prefill_chunk(pattern._values, kv_cnt, kv_idx, q, k_cache, v_cache, q_start, o, lse, softmax_scale,
+                                  want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, q_len, d = q.shape
     hkv, cap = k_cache.shape[1], k_cache.shape[2]
     if k_cache.shape != (batch, hkv, cap, d) or v_cache.shape != k_cache.shape:
@@ -281,6 +319,11 @@ def prefill_chunk_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
                         softmax_scale=0.0, want_lse=True, stream=None):
     """powattn_prefill_chunk_paged.  q/o: [b,Hq,q_len,D] at positions q_start..; pages: [n_pages,Hkv,block,D];
     block_table int32 [b, table_stride].  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.prefill_chunk_paged(pattern._values, kv_cnt, kv_idx, q, k_pages, v_pages, block_table, q_start, o, lse,
+                                        softmax_scale, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, q_len, d = q.shape
     n_pages, hkv, blk = k_pages.shape[0], k_pages.shape[1], k_pages.shape[2]
     if k_pages.shape != (n_pages, hkv, blk, d) or v_pages.shape != k_pages.shape:
@@ -315,6 +358,11 @@ def prefill_batch_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
     """powattn_prefill_batch_paged.  q/o: [b,Hq,q_rows,D]; pages: [n_pages,Hkv,block,D]; block_table int32
     [b, table_stride]; q_start, q_len int32 [b] on the device.  Returns (o, lse); rows at or beyond a sequence's
     q_len are left as they were."""
+    if _native is not None and stream is None:
+        r = _native.prefill_batch_paged(pattern._values, kv_cnt, kv_idx, q, k_pages, v_pages, block_table, q_start, q_len,
+                                        o, lse, softmax_scale, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, q_rows, d = q.shape
     n_pages, hkv, blk = k_pages.shape[0], k_pages.shape[1], k_pages.shape[2]
     if k_pages.shape != (n_pages, hkv, blk, d) or v_pages.shape != k_pages.shape:
@@ -350,6 +398,10 @@ def prefill_batch_paged(pattern: Pattern, kv_cnt, kv_idx, q, k_pages, v_pages, b
 def decode(pattern: Pattern, q, k_cache, v_cache, kv_len, o=None, lse=None, softmax_scale=0.0,
            workspace=None, want_lse=True, stream=None):
     """powattn_decode.  q/o: [b,Hq,D]; caches: [b,Hkv,capacity,D]; kv_len int32 [b].  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.decode(pattern._values, q, k_cache, v_cache, kv_len, o, lse, softmax_scale, workspace, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, d = q.shape
     hkv, cap = k_cache.shape[1], k_cache.shape[2]
     if k_cache.shape != (batch, hkv, cap, d) or v_cache.shape != k_cache.shape:
@@ -392,6 +444,11 @@ def decode_paged(pattern: Pattern, q, k_pages, v_pages, block_table, kv_len, o=N
                  workspace=None, want_lse=True, stream=None):
     """powattn_decode_paged.  q/o: [b,Hq,D]; pages: [n_pages,Hkv,block,D]; block_table int32 [b, table_stride];
     kv_len int32 [b].  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.decode_paged(pattern._values, q, k_pages, v_pages, block_table, kv_len, o, lse, softmax_scale,
+                                 workspace, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, d = q.shape
     n_pages, hkv, blk = k_pages.shape[0], k_pages.shape[1], k_pages.shape[2]
     if k_pages.shape != (n_pages, hkv, blk, d) or v_pages.shape != k_pages.shape:
@@ -428,6 +485,10 @@ def backward(pattern: Pattern, kv_cnt, kv_idx, q, k, v, o, lse, d_o, dq=None, dk
              workspace=None, stream=None):
     """powattn_backward.  q/o/d_o/dq: [b,Hq,N,D]; k/v/dk/dv: [b,Hkv,N,D]; lse float32 [b,Hq,N].
     Returns (dq, dk, dv)."""
+    if _native is not None and stream is None:
+        r = _native.backward(pattern._values, kv_cnt, kv_idx, q, k, v, o, lse, d_o, dq, dk, dv, softmax_scale, workspace)
+        if r is not NotImplemented:
+            return r
     batch, hq, n, d = q.shape
     hkv = k.shape[1]
     if k.shape != (batch, hkv, n, d) or v.shape != k.shape:
@@ -462,6 +523,10 @@ def prefill_varlen(pattern: Pattern, kv_cnt, kv_idx, q, k, v, seq_lens, o=None, 
                    want_lse=True, stream=None):
     """powattn_prefill_varlen.  q/o: [b,Hq,Np,D]; k/v: [b,Hkv,Np,D] padded to Np rows; seq_lens: int32 device
     tensor [b].  Rows beyond a sequence's length keep whatever o/lse held.  Returns (o, lse)."""
+    if _native is not None and stream is None:
+        r = _native.prefill_varlen(pattern._values, kv_cnt, kv_idx, q, k, v, seq_lens, o, lse, softmax_scale, want_lse)
+        if r is not NotImplemented:
+            return r
     batch, hq, npad, d = q.shape
     hkv = k.shape[1]
     if k.shape != (batch, hkv, npad, d) or v.shape != k.shape:

@@ -1,4 +1,5 @@
-"""Builds libpowattn.so (the C-ABI library) for gfx950 with hipcc, in-tree.
+"""Builds libpowattn.so (the C-ABI library) for gfx950 with hipcc, in-tree, and the binding's host module _host.so with the
+host compiler.
 
 Run as `python -m paper_2503_03588_amd.build`.  Every .hip file under csrc/ is
 compiled to an object in csrc/_build/ and the objects are linked into
@@ -15,6 +16,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libpowattn.so")
+HOST_OUT = os.path.join(HERE, "_host.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -71,7 +73,29 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     os.replace(tmp, OUT)
     if verbose:
         print(f"built {OUT} from {len(srcs)} sources")
+    build_host(verbose)
     return OUT
+
+
+def build_host(verbose: bool = True) -> str:
+    """csrc/host.cpp -> _host.so: the binding's ordinary calls marshalled natively (host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = HOST_OUT + ".tmp"
+    cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"), "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "host.cpp"), "-o", tmp,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"the host module failed to build:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, HOST_OUT)
+    if verbose:
+        print(f"built {HOST_OUT}")
+    return HOST_OUT
 
 
 def build_microbench(verbose: bool = True):

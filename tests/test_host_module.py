@@ -1,0 +1,137 @@
+"""The native marshalling of the binding's ordinary calls (csrc/host.cpp) against the Python marshalling: the same results
+for the calls it takes, nothing done for the ones it leaves alone, the same errors."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2503_03588_amd import binding as pa
+
+PAT = pa.Pattern(64, 3, 1)
+
+
+def bound_host():
+    from paper_2503_03588_amd import _host
+    L = pa.lib()
+    _host.bind(*(ctypes.cast(getattr(L, "powattn_" + n), ctypes.c_void_p).value for n in pa._NATIVE_ENTRY_POINTS), torch.Tensor,
+               torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    return _host
+
+
+def test_out_of_the_ordinary_is_left_alone():
+    if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        pytest.skip("this torch has no GPU support")
+    host = bound_host()
+
+    class Sub(torch.Tensor):
+        pass
+
+    x = torch.zeros(1, 2, 64, 64)
+    for q in (x, x.as_subclass(Sub), torch.nn.Parameter(x), x.transpose(1, 2), x.data_ptr(), None):
+        assert host.prefill(PAT._values, None, None, q, x, x, None, None, 0.0, True) is NotImplemented
+        assert host.decode(PAT._values, q, x, x, x, None, None, 0.0, x, True) is NotImplemented
+    assert host.mask_build(PAT._values, -1) is NotImplemented
+    assert host.mask_build((64, 3, 1), 128) is NotImplemented
+    assert host.mask_build(PAT._values, 128.0) is NotImplemented
+    with pytest.raises(TypeError):
+        host.prefill(PAT._values)
+
+
+def calls():
+    """(name, function of no arguments) of every entry point that is marshalled natively; fresh outputs each time."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    n, hq, hkv, d, b = 200, 4, 2, 64, 2
+    q, k, v = normal(b, hq, n, d), normal(b, hkv, n, d), normal(b, hkv, n, d)
+    cnt, idx, _ = pa.mask_build(PAT, 256)
+    pk, pv = normal(9, hkv, 64, d), normal(9, hkv, 64, d)
+    table = torch.arange(8, dtype=torch.int32, device="cuda").reshape(b, 4)
+    lens = torch.tensor([n, 77], dtype=torch.int32, device="cuda")
+    start = torch.tensor([30, 0], dtype=torch.int32, device="cuda")
+    rows = torch.tensor([100, 3], dtype=torch.int32, device="cuda")
+    ws = pa.decode_workspace(PAT, b, hq, hkv, d, 256)
+    q1, o1 = q[:, :, 0].contiguous(), torch.empty_like(q[:, :, 0].contiguous())
+    nosink = pa.Pattern(64, 3, 0)                # (sums over a sink block's column depend on the order of arrival)
+    cnt0, idx0, _ = pa.mask_build(nosink, 256)
+    saved = pa.prefill(nosink, cnt0, idx0, q, k, v)
+    zo, zl = torch.zeros_like(q), torch.zeros(q.shape[:3], device="cuda")
+    return [
+        ("mask_build", lambda: pa.mask_build(PAT, 1000)[:2]),
+        ("prefill", lambda: pa.prefill(PAT, cnt, idx, q, k, v)),
+        ("prefill without lse, scale given", lambda: pa.prefill(PAT, cnt, idx, q, k, v, softmax_scale=0.3, want_lse=False)[:1]),
+        ("prefill fp32", lambda: pa.prefill(PAT, cnt, idx, q.float(), k.float(), v.float())),
+        ("prefill dense", lambda: pa.prefill(pa.Pattern(64, 1, 0, pa.DENSE | pa.POWER), None, None, q, k, v)),
+        ("chunk", lambda: pa.prefill_chunk(PAT, cnt, idx, q[:, :, :50].contiguous(), k, v, 31)),
+        ("chunk paged", lambda: pa.prefill_chunk_paged(PAT, cnt, idx, q[:, :, :50].contiguous(), pk, pv, table, 31)),
+        ("batch paged", lambda: pa.prefill_batch_paged(PAT, cnt, idx, q, pk, pv, table, start, rows, o=zo.clone(), lse=zl.clone())),
+        ("varlen", lambda: pa.prefill_varlen(PAT, cnt, idx, q, k, v, lens)),
+        ("decode", lambda: pa.decode(PAT, q1, k, v, lens, workspace=ws)),
+        ("decode, outputs given", lambda: pa.decode(PAT, q1, k, v, lens, o=o1, workspace=ws)),
+        ("decode paged", lambda: pa.decode_paged(PAT, q1, pk, pv, table, lens, workspace=ws)),
+        ("backward", lambda: pa.backward(nosink, cnt0, idx0, q, k, v, *saved, q)),
+        ("backward, outputs given", lambda: pa.backward(nosink, cnt0, idx0, q, k, v, *saved, q, dq=zo.clone(), dv=v.clone(), softmax_scale=0.2)),
+    ]
+
+
+@pytest.mark.gpu
+def test_the_same_results_as_through_python(monkeypatch):
+    pa.mask_build(PAT, 64)                       # (the first call enables the native ones)
+    host = pa._native
+    assert host is not None, "the host module is not built"
+    for name, call in calls():
+        results = []
+        for native in (host, None):
+            monkeypatch.setattr(pa, "_native", native)
+            side = torch.cuda.Stream()           # the current stream is the one that counts
+            side.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(side):
+                out = call()
+            side.synchronize()
+            results.append([t.clone() for t in out])
+        for a, b in zip(*results):
+            assert a.dtype == b.dtype and a.shape == b.shape and torch.equal(a, b), name
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_every_ordinary_call_goes_the_native_way(monkeypatch):
+    pa.mask_build(PAT, 64)
+    host, seen = pa._native, []
+
+    class Spy:
+        def __getattr__(self, name):
+            def f(*a):
+                r = getattr(host, name)(*a)
+                seen.append((name, r is not NotImplemented))
+                return r
+            return f
+
+    todo = calls()
+    monkeypatch.setattr(pa, "_native", Spy())
+    for name, call in todo:
+        call()
+    torch.cuda.synchronize()
+    assert len(seen) == len(todo) and all(ok for _, ok in seen), seen
+
+
+@pytest.mark.gpu
+def test_errors_are_the_python_ways_own():
+    pa.mask_build(PAT, 64)
+    q = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16, device="cuda")
+    cnt, idx, _ = pa.mask_build(PAT, 64)
+    with pytest.raises(ValueError, match="dtype"):
+        pa.prefill(PAT, cnt, idx, q, q.float(), q)
+    with pytest.raises(ValueError, match="shape"):
+        pa.prefill(PAT, cnt, idx, q, q[:, :, :32].contiguous(), q)
+    with pytest.raises(ValueError, match="contiguous"):
+        pa.prefill(PAT, cnt, idx, q.transpose(1, 2), q.transpose(1, 2), q.transpose(1, 2))
+    with pytest.raises(pa.PowattnError):
+        pa.prefill(pa.Pattern(72, 3, 1), cnt, idx, q, q, q)
+    with pytest.raises(pa.PowattnError):
+        pa.mask_build(PAT, -3)
+    with pytest.raises(pa.PowattnError):
+        pa.decode(PAT, q[:, :, 0].contiguous(), q, q, cnt, workspace=torch.empty(1, dtype=torch.uint8, device="cuda"))
