@@ -22,11 +22,16 @@
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <int N> struct f32_vec { typedef f32x4 type; };
+template <> struct f32_vec<2> { typedef f32x2 type; };
 
 struct f32_params {
   const float* q; const float* k; const float* v; float* o; float* lse;
   const int32_t* kv_cnt; const int32_t* kv_idx;
-  int32_t max_k, nb, B, hq, hkv, dense;
+  int32_t max_k, nb, B, hq, hkv, G, dense;
+  int32_t q_tiles;               // workgroups per head and part of the head dimension: nb * per_block
+  uint32_t per_block_magic, tpb_magic, G_magic;   // reciprocals of B / query rows of a workgroup, B / 16 and G (see quot)
   int64_t N;
   float c2;   // softmax scale * log2(e)
 };
@@ -36,15 +41,25 @@ constexpr int NW = 4;              // wavefronts per workgroup (eight share the 
 constexpr float RAISE_BY = 8.0f;   // the exponentials' reference point is raised when exceeded by 2^8: any reference
                                    // gives the same result, and raising it costs a multiplication of all of O
 
-constexpr int o_stride(int D) { return D + 4; }   // floats per query row of a wavefront's partial output in LDS
-template <int D, int MQ>
-constexpr size_t merge_lds() { return sizeof(float) * NW * 16 * MQ * (o_stride(D) + 2); }
+constexpr int o_stride(int DV) { return DV + 4; }   // floats per query row of a wavefront's partial output in LDS
+template <int DV, int MQ>
+constexpr size_t merge_lds() { return sizeof(float) * NW * 16 * MQ * (o_stride(DV) + 2); }
 
-template <int D, int MQ>
+// x / y through ceil(2^32 / y), which the host passes where it is exact for every x (else 0): divisions stand in front of the
+// first load, forty instructions each in 32 bits and a hundred in 64.
+__device__ __forceinline__ int quot(int x, int y, uint32_t magic) {
+  return y == 1 ? x : magic ? (int)__umulhi((uint32_t)x, magic) : x / y;
+}
+
+// DS: the output's columns are dealt to DS workgroups, which all form the scores (launches that leave compute units idle)
+template <int D, int MQ, int DS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void pa_prefill_f32_kernel(f32_params p) {
   constexpr int NK = D / 16;                // 16-byte pieces of a K row per lane; each feeds four steps
-  constexpr int NV = D / 64;                // 16-byte pieces of a V row per lane; each feeds four tiles of O^T
+  constexpr int DV = D / DS;                // columns of V and O of this workgroup
+  constexpr int VW = DV >= 64 ? 4 : 2;      // floats in a lane's piece of a V row; each feeds a tile of O^T
+  constexpr int NV = DV / (16 * VW);        // pieces per lane
+  typedef typename f32_vec<VW>::type v_piece;
   constexpr int QR = 16 * MQ;               // query rows of the workgroup
   constexpr int TS = MQ * D <= 128 ? 4 : 2; // 16-key tiles per step (scores held at a time)
   // Sums a score is formed in (one for every CH-th head element), added up at the end.  With a single sum of D products the
@@ -53,25 +68,26 @@ void pa_prefill_f32_kernel(f32_params p) {
   // registers for more than two (four spill 40: 52.8 -> 57.3 us at 8 heads, N = 4096), and reach long sequences only.
   constexpr int CH = MQ == 4 ? 2 : 4;
   constexpr int LA = MQ * D <= 64 ? 4 : MQ * D <= 128 ? 2 : 1;   // tiles loaded ahead
-  extern __shared__ __attribute__((aligned(16))) float s_o[];   // [NW][QR][D + 4], then the maxima and sums [NW][QR]
-  float* s_m = s_o + NW * QR * o_stride(D);
+  extern __shared__ __attribute__((aligned(16))) float s_o[];   // [NW][QR][DV + 4], then the maxima and sums [NW][QR]
+  float* s_m = s_o + NW * QR * o_stride(DV);
   float* s_l = s_m + NW * QR;
   __shared__ int s_some[NW];                // whether the wavefront's part held any key
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 15, kg = lane >> 4;
-  const int per_block = p.B / QR;
-  const int qb = p.nb - 1 - (int)blockIdx.x / per_block;       // longest rows first
-  const int q_in_blk = ((int)blockIdx.x % per_block) * QR;
+  const int dpart = DS == 1 ? 0 : (int)blockIdx.x / p.q_tiles;             // (at most four: a compare each)
+  const int qx = (int)blockIdx.x - dpart * p.q_tiles, qblk = quot(qx, p.B / QR, p.per_block_magic);
+  const int qb = p.nb - 1 - qblk;                              // longest rows first
+  const int q_in_blk = (qx - qblk * (p.B / QR)) * QR;
   const int h = blockIdx.y, b = blockIdx.z;
-  const int kvh = h / (p.hq / p.hkv);
+  const int kvh = quot(h, p.G, p.G_magic);
   const int64_t q0 = (int64_t)qb * p.B + q_in_blk;
   if (q0 >= p.N) return;                                       // uniform over the workgroup
 
   const float* qbase = p.q + ((int64_t)b * p.hq + h) * p.N * D;
   const float* kbase = p.k + ((int64_t)b * p.hkv + kvh) * p.N * D;
-  const float* vbase = p.v + ((int64_t)b * p.hkv + kvh) * p.N * D;
+  const float* vbase = p.v + ((int64_t)b * p.hkv + kvh) * p.N * D + dpart * DV;
 
   // ---- the row's list, 64 entries at a time: lane e keeps entry list_base + e ----
   const int32_t* list = p.kv_idx + (int64_t)qb * p.max_k;
@@ -99,14 +115,15 @@ void pa_prefill_f32_kernel(f32_params p) {
   // ---- this wavefront's 16-key tiles: tile tau is piece tau % tpb of list entry tau / tpb ----
   const int tpb = p.B / 16;
   const int diag_tiles = q_in_blk / 16 + MQ;                   // tiles of the diagonal block that any query reaches
-  int64_t tiles = (int64_t)n_list * tpb;
+  int tiles = n_list * tpb;                                    // (fewer than 2^27: positions are 32-bit numbers)
   int last_row = row_e;
   if (n_list > 64) last_row = list_lanes((n_list - 1) & ~63);
   if (n_list > 0 && __builtin_amdgcn_readlane(last_row, (n_list - 1) & 63) == qb) tiles -= tpb - diag_tiles;
-  const int64_t lo = tiles * wave / NW, hi = tiles * (wave + 1) / NW;
-  const int n_steps = (int)((hi - lo + TS - 1) / TS);
-  int ct = (int)(lo / tpb), cs = (int)(lo % tpb);              // cursor of the loads: list entry, piece
-  int left = (int)(hi - lo);
+  static_assert(NW == 4, "the parts of the row are formed with shifts");
+  const int lo = (tiles >> 2) * wave + (((tiles & 3) * wave) >> 2), hi = (tiles >> 2) * (wave + 1) + (((tiles & 3) * (wave + 1)) >> 2);
+  const int n_steps = (hi - lo + TS - 1) / TS;
+  int ct = quot(lo, tpb, p.tpb_magic), cs = lo - ct * tpb;     // cursor of the loads: list entry, piece
+  int left = hi - lo;
   if (ct >= 64) row_e = list_lanes(ct & ~63);
   const int last = (int)(p.N - 1);
   bool any = false;                                            // a tile to attend: a block's first one holds a key of every query
@@ -124,7 +141,8 @@ void pa_prefill_f32_kernel(f32_params p) {
     return key0;
   };
 
-  f32x4 kf[TS][NK], vf[TS][4][NV];
+  f32x4 kf[TS][NK];
+  v_piece vf[TS][4][NV];
   // A tile's address is scalar, a lane adds its row and piece; rows beyond the sequence repeat its last one (masked).
   // "No tile" reads the start of the slab and its products are left out, so that nothing unattended reaches the sums.
   auto load_k = [&](int i, int key0) {
@@ -140,19 +158,19 @@ void pa_prefill_f32_kernel(f32_params p) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = 4 * kg + r;
-      const uint32_t off = (uint32_t)(row < lim ? row : lim) * D + 4 * ln;
+      const uint32_t off = (uint32_t)(row < lim ? row : lim) * D + VW * ln;
 #pragma unroll
-      for (int x = 0; x < NV; ++x) vf[i][r][x] = *reinterpret_cast<const f32x4*>(src + off + 64 * x);
+      for (int x = 0; x < NV; ++x) vf[i][r][x] = *reinterpret_cast<const v_piece*>(src + off + 16 * VW * x);
     }
   };
 
-  f32x4 O[MQ][4 * NV];
+  f32x4 O[MQ][VW * NV];
   float m_run[MQ], l_run[MQ];
 #pragma unroll
   for (int m = 0; m < MQ; ++m) {
     m_run[m] = -INFINITY; l_run[m] = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4 * NV; ++j) O[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < VW * NV; ++j) O[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
   int key0[TS], nkey0[TS];
@@ -221,7 +239,7 @@ void pa_prefill_f32_kernel(f32_params p) {
         m_run[m] = m_new;
         l_run[m] *= alpha;
 #pragma unroll
-        for (int j = 0; j < 4 * NV; ++j)
+        for (int j = 0; j < VW * NV; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) O[m][j][r] *= alpha;
       }
@@ -235,7 +253,7 @@ void pa_prefill_f32_kernel(f32_params p) {
       }
       l_run[m] += sum;
     }
-    // ---- O^T += V^T P^T: row R of tile 4x+j is d = 64x + 4R + j ----
+    // ---- O^T += V^T P^T: row R of tile VW x + j is column VW (16x + R) + j of the workgroup's ----
 #pragma unroll
     for (int i = 0; i < TS; ++i) {
       load_ahead(TS + i);
@@ -246,10 +264,10 @@ void pa_prefill_f32_kernel(f32_params p) {
 #pragma unroll
           for (int x = 0; x < NV; ++x)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < VW; ++j)
 #pragma unroll
               for (int m = 0; m < MQ; ++m)
-                O[m][4 * x + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][x][j], S[m][i][r], O[m][4 * x + j], 0, 0, 0);
+                O[m][VW * x + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][x][j], S[m][i][r], O[m][VW * x + j], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -268,16 +286,19 @@ void pa_prefill_f32_kernel(f32_params p) {
 #pragma unroll
     for (int x = 0; x < NV; ++x)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<f32x4*>(s_o + row * o_stride(D) + 64 * x + 16 * kg + 4 * r) =
-            f32x4{O[m][4 * x][r], O[m][4 * x + 1][r], O[m][4 * x + 2][r], O[m][4 * x + 3][r]};
+      for (int r = 0; r < 4; ++r) {
+        v_piece piece;
+#pragma unroll
+        for (int j = 0; j < VW; ++j) piece[j] = O[m][VW * x + j][r];
+        *reinterpret_cast<v_piece*>(s_o + row * o_stride(DV) + VW * (16 * x + 4 * kg + r)) = piece;
+      }
   }
   __syncthreads();
   int some = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) some |= s_some[w];
-  for (int e = tid; e < QR * (D / 4); e += 64 * NW) {
-    const int row = e / (D / 4), d4 = e % (D / 4);
+  for (int e = tid; e < QR * (DV / 4); e += 64 * NW) {
+    const int row = e / (DV / 4), d4 = e % (DV / 4);
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w * QR + row]);
@@ -288,7 +309,7 @@ void pa_prefill_f32_kernel(f32_params p) {
       const float lw = s_l[w * QR + row];
       const float wt = lw > 0.f ? __builtin_amdgcn_exp2f(s_m[w * QR + row] - M) : 0.f;   // (0 times a sum that is NaN is NaN)
       L = fmaf(wt, lw, L);
-      const f32x4 ow = *reinterpret_cast<const f32x4*>(s_o + (w * QR + row) * o_stride(D) + 4 * d4);
+      const f32x4 ow = *reinterpret_cast<const f32x4*>(s_o + (w * QR + row) * o_stride(DV) + 4 * d4);
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] = fmaf(wt, ow[x], acc[x]);
     }
@@ -297,18 +318,25 @@ void pa_prefill_f32_kernel(f32_params p) {
     // a row whose list is empty: o = 0, lse = -inf; one whose scores are all -inf: 0 * (1 / 0), no number, as softmax has it
     const float inv = some ? 1.0f / L : 0.f;
     const int64_t at = ((int64_t)b * p.hq + h) * p.N + tok;
-    *reinterpret_cast<f32x4*>(p.o + at * D + 4 * d4) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-    if (p.lse && d4 == 0) p.lse[at] = (M + log2f(L)) * 0.69314718055994530942f;
+    *reinterpret_cast<f32x4*>(p.o + at * D + dpart * DV + 4 * d4) = f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+    if (p.lse && d4 == 0 && dpart == 0) p.lse[at] = (M + log2f(L)) * 0.69314718055994530942f;
   }
 }
 
-template <int D, int MQ>
-int launch(const f32_params& p, int32_t batch, hipStream_t stream) {
-  constexpr size_t lds = merge_lds<D, MQ>();
+template <int D, int MQ, int DS>
+int launch(f32_params p, int32_t batch, hipStream_t stream) {
+  constexpr size_t lds = merge_lds<D / DS, MQ>();
   static std::atomic<unsigned long long> done{0};
-  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_prefill_f32_kernel<D, MQ>), lds, done)) return st;
-  dim3 grid((uint32_t)p.nb * (uint32_t)(p.B / (16 * MQ)), (uint32_t)p.hq, (uint32_t)batch);
-  hipLaunchKernelGGL((pa_prefill_f32_kernel<D, MQ>), grid, dim3(64 * NW), lds, stream, p);
+  if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_prefill_f32_kernel<D, MQ, DS>), lds, done)) return st;
+  const int per_block = p.B / (16 * MQ), tpb = p.B / 16;
+  // exact for x < n if n * y <= 2^32
+  auto magic = [](int64_t n, int64_t y) -> uint32_t { return y > 1 && n * y <= 0xffffffffLL ? (uint32_t)(((1ull << 32) + y - 1) / y) : 0u; };
+  p.q_tiles = p.nb * per_block;
+  p.per_block_magic = magic((int64_t)p.nb * per_block, per_block);
+  p.tpb_magic = magic((int64_t)(p.max_k > p.nb ? p.max_k : p.nb) * tpb, tpb);
+  p.G_magic = magic(p.hq, p.G);
+  dim3 grid((uint32_t)p.q_tiles * DS, (uint32_t)p.hq, (uint32_t)batch);
+  hipLaunchKernelGGL((pa_prefill_f32_kernel<D, MQ, DS>), grid, dim3(64 * NW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
 }
 
@@ -316,6 +344,10 @@ int launch(const f32_params& p, int32_t batch, hipStream_t stream) {
 // N = 8192: 59 / 70 / 84 TFLOP/s at 1 / 2 / 4) as long as every compute unit gets a workgroup: at 8 heads and N = 1024
 // 1 / 2 / 4 tiles (512 / 256 / 128 workgroups) take 19.8 / 16.3 / 26.1 us, at 2 heads 11.6 / 15.1 / 25.4.
 // At most 64 queries at head_dim 64 and 32 at 128, which is what the 256 registers of a wavefront hold.
+// Where even workgroups of 16 queries leave half of the compute units idle, the output's columns are dealt to two or four
+// workgroups: half of a workgroup's products are those of the output, and the scores are
+// formed anew.  us with the list, one / more workgroups: head_dim 128, 2 heads, N = 1000 17.8 / 16.0, N = 130 (four) 12.1 / 11.0;
+// head_dim 64, 2 heads, N = 1024 12.15 / 11.9.  (Steps of six or eight key tiles instead of four at head_dim 64: 12.5, 13.2.)
 template <int D>
 int launch_d(const f32_params& p, int32_t batch, hipStream_t stream) {
   constexpr int MQ_MAX = 256 / D;
@@ -325,8 +357,11 @@ int launch_d(const f32_params& p, int32_t batch, hipStream_t stream) {
   int mq = 1;
   while (mq < MQ_MAX && p.B % (32 * mq) == 0 && tiles / (2 * mq) >= n_cu) mq *= 2;
   if constexpr (MQ_MAX == 4)
-    if (mq == 4) return launch<D, 4>(p, batch, stream);
-  return mq == 2 ? launch<D, 2>(p, batch, stream) : launch<D, 1>(p, batch, stream);
+    if (mq == 4) return launch<D, 4, 1>(p, batch, stream);
+  if (mq == 2) return launch<D, 2, 1>(p, batch, stream);
+  if constexpr (D == 128)
+    if (4 * tiles <= n_cu) return launch<D, 1, 4>(p, batch, stream);
+  return 2 * tiles <= n_cu ? launch<D, 1, 2>(p, batch, stream) : launch<D, 1, 1>(p, batch, stream);
 }
 
 }  // namespace
@@ -335,7 +370,7 @@ int pa_launch_prefill_f32(const pa_prefill_args& a) {
   f32_params p;
   p.q = (const float*)a.q; p.k = (const float*)a.k; p.v = (const float*)a.v; p.o = (float*)a.o; p.lse = a.lse;
   p.kv_cnt = a.kv_cnt; p.kv_idx = a.kv_idx; p.max_k = a.max_k; p.nb = a.nb; p.B = a.pat.block;
-  p.hq = a.hq; p.hkv = a.hkv; p.dense = (a.pat.flags & POWATTN_DENSE) ? 1 : 0;
+  p.hq = a.hq; p.hkv = a.hkv; p.G = a.hq / a.hkv; p.dense = (a.pat.flags & POWATTN_DENSE) ? 1 : 0;
   p.N = a.seq_len;
   p.c2 = a.scale * 1.44269504088896340736f;
   if (a.hq > 65535 || a.batch > 65535) return POWATTN_UNSUPPORTED;

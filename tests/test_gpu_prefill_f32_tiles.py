@@ -39,6 +39,19 @@ def test_prefill_f32_every_form(hq, hkv, n, d, block, tiles):
     check_prefill(pa.Pattern(block, 2, 1), 1, hq, hkv, n, d, "f32", 400 + n)
 
 
+# few query tiles: the output's columns are dealt to two workgroups, or four at head_dim 128
+@pytest.mark.parametrize("hq,hkv,n,d,block,parts", [
+    (2, 2, 1024, 64, 64, 2), (1, 1, 2033, 64, 16, 2), (2, 1, 1041, 64, 64, 1),          # (272 tiles: one)
+    (1, 1, 1000, 128, 16, 4), (3, 1, 300, 128, 48, 4), (2, 1, 1001, 128, 64, 2), (4, 2, 1100, 128, 64, 1),
+])
+def test_prefill_f32_columns_dealt_to_workgroups(hq, hkv, n, d, block, parts):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = -(-n // block) * (block // 16) * hq
+    want = 4 if d == 128 and 4 * tiles <= cus else 2 if 2 * tiles <= cus else 1
+    assert want == parts
+    check_prefill(pa.Pattern(block, 2, 1), 1, hq, hkv, n, d, "f32", 500 + n)
+
+
 @pytest.mark.parametrize("hq,hkv,n,d,block,window,sink,flags", CASES)
 def test_prefill_f32_tiles(hq, hkv, n, d, block, window, sink, flags):
     check_prefill(pa.Pattern(block, window, sink, flags), 1, hq, hkv, n, d, "f32", 300 + n)
