@@ -81,6 +81,7 @@ struct bf16_params {
   int32_t chunks;    // work items of a whole query block (of one sequence and KV head)
   int32_t c_last, n_items;   // ... of the last block, and of all blocks (sequences of one length)
   int32_t per_xcd;   // work items per XCD partition
+  uint32_t items_magic, hkv_magic;   // ceil(2^32 / n_items), ceil(2^32 / hkv) where that replaces the division of any item's number (else 0)
   int32_t xcd_split; // sequences of different lengths, one or two KV heads: XCDs that share a KV head's items (else 0)
   int32_t b_shift;   // log2 of B, or -1
   int32_t i_max;     // last query block of the context: (N - 1) / B
@@ -132,11 +133,12 @@ __device__ __forceinline__ void wait_vmcnt() {   // s_waitcnt vmcnt(N) only
 }
 
 // DENSE: the implicit list {0..i} instead of a block list.  CHAIN: the launch chains work items in persistent
-// workgroups (two half-size tile tables, list rows prefetched); otherwise one workgroup per item.  VARLEN: every
+// workgroups (two half-size tile tables, list rows and Q rows prefetched); otherwise one workgroup per item, and nothing is
+// looked ahead for: the launches of few items, and lists that are too long for the look-ahead.  VARLEN: every
 // sequence of the batch has its own length (and first query position), read from device memory; only the query blocks
 // that exist are numbered, by a prefix sum over the lengths that every workgroup forms for itself.  PAGED: K and V
 // are pools of pages of one block each; the tile table then also holds every tile's first row in the pool, looked up
-// in the sequence's block table when the table is written (explicit lists, chained items only).
+// in the sequence's block table when the table is written (explicit lists only).
 template <int D, int NW, int NS, bool DENSE, bool CHAIN, bool VARLEN, bool PAGED>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void pa_prefill_bf16_kernel(bf16_params p) {
@@ -234,13 +236,13 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   } else {
     int64_t lim = p.total_wg - (int64_t)xcd * p.per_xcd;
     if (lim > p.per_xcd) lim = p.per_xcd;
-    if (lim > cuslot) n_raw = (int)((lim - cuslot + nslots - 1) / nslots);
+    if (lim > cuslot) n_raw = CHAIN ? (int)((lim - cuslot + nslots - 1) / nslots) : 1;
   }
   if (n_raw == 0) return;
   constexpr bool chained = CHAIN;      // tables in halves, list rows prefetched
   constexpr int tab_half = CHAIN ? (PAGED ? TILE_CAP / 4 : TILE_CAP / 2) : 0;
   constexpr int PHYS = TILE_CAP / 2;   // paged: entry e's first pool row sits at s_tile[PHYS + e]
-  static_assert(!PAGED || (CHAIN && !DENSE), "paged caches: explicit lists, chained items");
+  static_assert(!PAGED || !DENSE, "paged caches: explicit lists");
 
   // Items are numbered L = (b*hkv + kvh)*n_items + q with q counting the items of a sequence from the last query block
   // down (longest rows first, which matters for the dense list); with sequences of different lengths the KV head is
@@ -276,10 +278,16 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     item_t it;
     it.b = it.kvh = 0;
     if (VARLEN) it.q = (int)L;         // (a stride; the first item is found above)
-    else {
+    else if (CHAIN) {
       it.q = (int)(L % (uint32_t)p.n_items); L /= (uint32_t)p.n_items;
       it.kvh = (int)(L % (uint32_t)p.hkv);
       it.b = (int)(L / (uint32_t)p.hkv);
+    } else {
+      auto quot = [](uint32_t x, uint32_t y, uint32_t magic) -> uint32_t { return y == 1 ? x : magic ? __umulhi(x, magic) : x / y; };
+      const uint32_t head = quot(L, (uint32_t)p.n_items, p.items_magic), seq = quot(head, (uint32_t)p.hkv, p.hkv_magic);
+      it.q = (int)(L - head * (uint32_t)p.n_items);
+      it.kvh = (int)(head - seq * (uint32_t)p.hkv);
+      it.b = (int)seq;
     }
     it.chunk = it.i = it.sl0 = it.nsl = it.subs_diag = it.n = it.qs = it.first = it.nblk = it.c_last = it.n_items = 0;
     return it;
@@ -308,7 +316,7 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   };
   item_t it = stride, it1 = stride, it2 = stride;   // the current item, the next one, the one after (set below)
   int raw2 = 0;                        // position of it2 among this workgroup's items
-  const int n_items = n_raw;
+  const int n_items = CHAIN ? n_raw : 1;
   // keys of an item's sequence (one value for the whole launch unless the sequences have lengths of their own)
   auto keys_of = [&](const item_t& x) -> int { return VARLEN ? x.n : (int)p.N; };
   // position of the first row of Q/O
@@ -371,6 +379,25 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       table_rows(tab, it, j, page_of(it, j), blocks, has_diag);
     }
     table_finish(tab, it, page_of(it, it.i), blocks, has_diag);
+  };
+  // ... of a workgroup's only item: the row is read without waiting for its length first (trips to memory that depend on one
+  // another are what a short launch waits for)
+  auto only_table = [&](const item_t& it) {
+    const int e = lane < p.max_k ? lane : p.max_k - 1;
+    int n = p.kv_cnt[it.i];
+    int j = p.kv_idx[(int64_t)it.i * p.max_k + e];
+    const int page_i = page_of(it, it.i);
+    if (n > p.max_k) n = p.max_k;
+    n = __builtin_amdgcn_readfirstlane(n);
+    j = lane < n ? j : -1;
+    int blocks = 0;
+    bool has_diag = false;
+    table_rows(0, it, j, page_of(it, j), blocks, has_diag);
+    for (int base = 64; base < n; base += 64) {
+      j = base + lane < n ? p.kv_idx[(int64_t)it.i * p.max_k + base + lane] : -1;
+      table_rows(0, it, j, page_of(it, j), blocks, has_diag);
+    }
+    table_finish(0, it, page_i, blocks, has_diag);
   };
   // first wavefront; the row was copied earlier into s_raw[0].  Paged: the pages of the row's blocks are requested by
   // row_pages at the start of an item and used here, after the Q fragments have been arranged.
@@ -553,6 +580,36 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     }
   };
 
+  // The Q rows of a workgroup with one item come through LDS instead, through the ring stages that no tile needs yet: copied
+  // row by row as the tiles are, each wavefront its own rows, and read in the order of the fragments (nothing to
+  // arrange).  They are asked for before the tiles, and the first product waits for them and the first tile only.
+  constexpr int QC = QW / RPI;               // copy instructions of a wavefront's rows
+  constexpr int QSTAGES = NW * QC * SRB / STAGEB;
+  static_assert(QSTAGES * STAGEB == NW * QC * SRB && QSTAGES < NS, "Q rows fill whole stages");
+  const uint32_t q_lds = __builtin_amdgcn_readfirstlane(lds0 + (NS - QSTAGES) * STAGEB + wave * QC * SRB);
+  auto copy_only_q = [&](const item_t& it) {
+    int g, sl;
+    if (!task_of(it, g, sl)) return;                       // (the fragments are not used then)
+    const int64_t tok0 = (int64_t)it.i * p.B + sl * QW, qs = qs_of(it);
+    const int64_t from = tok0 > qs ? tok0 : qs;            // rows outside the call repeat its first or last one; not stored
+    const int skip = (int)(from - tok0), last = keys_of(it) - 1 - (int)from;
+    const __bf16* base = uniform_ptr(p.q + (((int64_t)it.b * p.hq + it.kvh * p.G + g) * p.q_rows + (from - qs)) * D);
+    auto one = [&](auto xc) {
+      constexpr int x = decltype(xc)::value;
+      if constexpr (x < QC) {
+        int row = RPI * x + cp_row - skip;
+        row = row > last ? last : row;
+        row = row < 0 ? 0 : row;
+        async_copy16_at<x * SRB>(base, (uint32_t)row * ROWB | f_chunk, q_lds);
+      }
+    };
+    one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{});
+    one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{});
+    static_assert(QC <= 8, "copy_only_q lists the copies");
+  };
+
   // ---- start of the stream: tables of the first two items, fills 0..NS-2, Q of the first item ----
   if (VARLEN) {
     it.q = v_q; it.kvh = v_kvh; it.b = v_b;
@@ -565,17 +622,27 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   }
   it1 = next_valid(it, raw2);
   it2 = next_valid(it1, raw2);
-  if (!DENSE) {
-    if (wave == 0) {
-      table_from_memory(0, it);
-      if (chained && n_items > 1) table_from_memory(1, it1);
+  constexpr int EARLY = CHAIN || QSTAGES == 1 ? NS - 1 : NS - QSTAGES;     // fills before the first product
+  if constexpr (CHAIN) {
+    if (!DENSE) {
+      if (wave == 0) {
+        table_from_memory(0, it);
+        if (n_items > 1) table_from_memory(1, it1);
+      }
+      __syncthreads();
     }
-    __syncthreads();
+  } else {
+    if (!DENSE) {
+      if (wave == 0) only_table(it);
+      else copy_only_q(it);
+      __syncthreads();
+    }
+    if (DENSE || wave == 0) copy_only_q(it);
   }
   cursor_enter(0, it);
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s) { next_fill(); fill_all(); }
-  load_q(it);
+  for (int s = 0; s < EARLY; ++s) { next_fill(); fill_all(); }
+  if (CHAIN) load_q(it);
 
   // Per-lane LDS base addresses of the fragment reads: ka inside the stage whose K tile is multiplied next,
   // va inside the stage whose V tile is multiplied next; they are advanced in place from stage to stage.
@@ -646,11 +713,17 @@ void pa_prefill_bf16_kernel(bf16_params p) {
   // Q fragments and the first tiles must have arrived before the first item; waiting here, once, also tells
   // the compiler that none of its own loads is outstanding inside the loops, so that it does not add
   // full vmcnt(0) waits there (they would drain the asynchronous copies as well).
-  wait_vmcnt<0>();
+  // (One item: its Q rows and the first tile; nothing of the compiler's own is outstanding.)
+  wait_vmcnt<CHAIN ? 0 : (EARLY - 1) * LPT>();
   __syncthreads();
+  if constexpr (!CHAIN) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      qf[c] = *reinterpret_cast<const lds_bf16x8*>((uintptr_t)(q_lds + (ln / RPI) * SRB + ((hh * NC * RPI + ln % RPI) << 4) + c * K_C));
+  }
 
   for (int k = 0; k < n_items; ++k) {
-    const bool more = k + 1 < n_items;
+    const bool more = CHAIN && k + 1 < n_items;
     // ---- per-item geometry ----
     int g, sl;
     const bool active = task_of(it, g, sl);
@@ -680,15 +753,17 @@ void pa_prefill_bf16_kernel(bf16_params p) {
     // The Q rows requested during the previous item are needed from here on.  Touching them on every path
     // makes the compiler wait for them here, once, instead of guarding each later use inside the loops
     // with a wait that would also drain the asynchronous copies.
+    if constexpr (CHAIN) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qraw[c]));
+      for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qraw[c]));
+    }
     // paged: the pages of the next item's blocks are requested here and used below, behind the arranging of Q
     int nx_page = 0, nx_page_i = 0;
     if (PAGED && wave == 0 && k >= 1 && more) {
       nx_page = page_of(it1, row_entry());
       nx_page_i = page_of(it1, it1.i);
     }
-    q_arrange();
+    if constexpr (CHAIN) q_arrange();
 
     // ---- look-ahead: the table of the next item from its prefetched list row (the first two tables were
     // built above), and the copy of the row of the item after it ----
@@ -716,6 +791,15 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       for (int sl2 = 0; sl2 < 2 * NC; ++sl2)
         Sc[sl2 & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_frag(sl2), qf[sl2 >> 1],
                                                               sl2 < 2 ? zero16 : Sc[sl2 & 1], 0, 0, 0);
+    }
+    if constexpr (EARLY < NS - 1) {          // the third fill goes where the first Q rows were
+#pragma unroll
+      for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qf[c]));
+      __syncthreads();
+      next_fill();
+      fill_all();
+    }
+    if (n_my > 0) {
       if (n_before == 0) mask(Sc, 0);        // the first tile is already a diagonal one
       float mx = Sc[0][0];
 #pragma unroll
@@ -929,8 +1013,10 @@ void pa_prefill_bf16_kernel(bf16_params p) {
       auto quad_xor2 = [](uint32_t x) -> uint32_t { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true); };
       // The next item's Q rows are waited for here, before the output stores go out: after them the same wait
       // would also wait for the stores to be acknowledged (loads and stores share one counter).
+      if constexpr (CHAIN) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qraw[c]));
+        for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qraw[c]));
+      }
       const int li = lane & 3;
       const int64_t tok0 = tok - li;                   // first row of the quad
       __bf16* obase = p.o + (((int64_t)it.b * p.hq + h) * p.q_rows + (tok0 - qs_of(it))) * D + hh * (D / 2) + 8 * li;
@@ -976,8 +1062,8 @@ int launch_as(const bf16_params& p, hipStream_t stream) {
   static std::atomic<unsigned long long> attr_done{0};
   if (int st = pa_allow_dynamic_lds(reinterpret_cast<const void*>(&pa_prefill_bf16_kernel<D, NW, NS, DENSE, CHAIN, VARLEN, PAGED>), lds, attr_done))
     return st;
-  // One workgroup per work item, or, when the items can be chained (the block lists are short enough for the
-  // look-ahead tables and registers), one persistent workgroup per compute unit that walks through its share.
+  // One workgroup per work item, or, when there are more of them and they can be chained (the block lists are short enough
+  // for the look-ahead tables and registers), one persistent workgroup per compute unit that walks through its share.
   int64_t grid = (int64_t)p.per_xcd * 8;
   if (CHAIN) {
     int n_cu = 0;
@@ -992,12 +1078,15 @@ int launch_as(const bf16_params& p, hipStream_t stream) {
 
 template <int D, int NW, int NS>
 int launch(const bf16_params& p, hipStream_t stream) {
-  if (p.block_table) return p.seq_len ? launch_as<D, NW, NS, false, true, true, true>(p, stream) : launch_as<D, NW, NS, false, true, false, true>(p, stream);
+  if (p.block_table) {
+    if (p.chain) return p.seq_len ? launch_as<D, NW, NS, false, true, true, true>(p, stream) : launch_as<D, NW, NS, false, true, false, true>(p, stream);
+    return p.seq_len ? launch_as<D, NW, NS, false, false, true, true>(p, stream) : launch_as<D, NW, NS, false, false, false, true>(p, stream);
+  }
   if (p.seq_len) {
-    if (p.dense) return launch_as<D, NW, NS, true, true, true>(p, stream);
+    if (p.dense) return p.chain ? launch_as<D, NW, NS, true, true, true>(p, stream) : launch_as<D, NW, NS, true, false, true>(p, stream);
     return p.chain ? launch_as<D, NW, NS, false, true, true>(p, stream) : launch_as<D, NW, NS, false, false, true>(p, stream);
   }
-  if (p.dense) return launch_as<D, NW, NS, true, true, false>(p, stream);     // the implicit list is always chained
+  if (p.dense) return p.chain ? launch_as<D, NW, NS, true, true, false>(p, stream) : launch_as<D, NW, NS, true, false, false>(p, stream);
   return p.chain ? launch_as<D, NW, NS, false, true, false>(p, stream) : launch_as<D, NW, NS, false, false, false>(p, stream);
 }
 
@@ -1014,7 +1103,8 @@ pa_seq_items host_items(const bf16_params& p, int nw) {
 // every half-size item.  A lone wavefront per SIMD takes about 0.6 of the time for a step that two take each.
 // Eight / four wavefronts, us, 32 query heads on 8, blocks of 64 keys: head_dim 128 N = 200 15.2 / 12.8, N = 1000
 // 21.0 / 17.8; head_dim 64 N = 1000 14.9 / 12.0; 16 heads on 2, N = 2000 21.2 / 18.2; 8 on 8, blocks of 256, N = 4000
-// 45.2 / 36.1.  With three rounds of half-size items against two of whole ones (264 items) the two are level: 47.7 / 47.8.
+// 45.2 / 36.1 (before such launches had a variant of their own, below).  With three rounds of half-size items against two of
+// whole ones (264 items) the two are level: 47.7 / 47.8.
 bool few_items_want_four_wavefronts(const bf16_params& p, const pa_prefill_args& a) {
   int n_cu = 0;
   pa_current_device(nullptr, &n_cu);
@@ -1053,6 +1143,8 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
     p.xcd_split = 8 / a.hkv;
     per_xcd = ((int64_t)a.batch * si.n + p.xcd_split - 1) / p.xcd_split;
   }
+  auto magic = [&](int64_t x) -> uint32_t { return x > 1 && p.total_wg * x <= 0xffffffffLL ? (uint32_t)(((1ull << 32) + x - 1) / x) : 0u; };
+  p.items_magic = magic(si.n); p.hkv_magic = magic(a.hkv);
   p.b_shift = (p.B & (p.B - 1)) == 0 ? __builtin_ctz((unsigned)p.B) : -1;
   p.i_max = (int32_t)((a.seq_len - 1) / p.B);
   if (per_xcd * 8 > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
@@ -1062,7 +1154,22 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
   if (a.block_table) {
     // paged: explicit lists whose tile table fits twice over (key positions and pool rows), pool rows in 32 bits
     if (p.dense || a.max_k > 63 || (int64_t)a.max_k * p.subs > TILE_CAP / 4) return POWATTN_UNSUPPORTED;
+    p.chain = 1;
     if (a.n_pages < 1 || a.table_stride < 1 || a.n_pages * (int64_t)a.hkv * p.B > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
+  }
+
+  // A compute unit for every item: one item per workgroup, by the variant without any look-ahead.  It has two thirds of the
+  // instructions (each is fetched for the first time in such a launch), its Q rows come through LDS in the order of the
+  // fragments, and the first product waits for them and one tile only.  us, chained / one item: 32 query heads on 8, blocks of
+  // 64, N = 1000 18.0 / 15.7 (list included), 28 on 4, N = 923 17.3 / 14.9; a paged piece of 2000 at 30001 31.3 / 29.9; 206
+  // at 757, blocks of 128, 18.8 / 16.6; dense list, 16 on 2, N = 191 10.2 / 8.4.  Where only the device knows the
+  // lengths, most launches have fewer items than they could: up to twice as many as compute units (three pieces of up to 347
+  // rows, blocks of 256: 61.8 / 58.2).
+  {
+    int n_cu = 0;
+    pa_current_device(nullptr, &n_cu);
+    const int64_t slots = n_cu >= 8 ? n_cu / 8 : 1;
+    if (per_xcd <= (a.seq_len_dev ? 2 * slots : slots)) p.chain = 0;
   }
 
   // ring of 4 stages: 128 KB of LDS at head_dim 128, 64 KB at head_dim 64
