@@ -60,6 +60,7 @@ struct bwd_params {
   int32_t part;          // query blocks per part of a sink block's column
   int32_t max_parts;     // parts of the longest column
   int64_t N;
+  int64_t sink_floats;   // from dk_sink on: both sums, cleared by the dQ kernel (a multiple of 64)
   float scale, c2;
 };
 
@@ -184,11 +185,6 @@ __device__ __forceinline__ void pipelined_mfma(LoadF load, MmaF mma) {
 // Element rg (0..15) of a 32x32 accumulator is row 8(rg/4) + 4(lane/32) + rg%4, column lane%32.
 __device__ __forceinline__ int acc_row(int rg, int hh) { return 8 * (rg >> 2) + 4 * hh + (rg & 3); }
 
-__global__ __launch_bounds__(256) void pa_bwd_zero_kernel(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.f;
-}
-
 // ---------------------------------------------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------------------------------------------
@@ -210,26 +206,31 @@ void pa_bwd_dq_kernel(bwd_params p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, hh = lane >> 5;
-  const int slices = p.B / 32;
+  const int slice_bits = __builtin_ctz((unsigned)p.B / 32);      // blocks are 64, 128 or 256 keys
 
-  // item: ((b*hkv + kvh)*nb + i)*chunks + chunk
-  int64_t L = blockIdx.x;
-  const int chunk = (int)(L % p.chunks); L /= p.chunks;
-  const int i = (int)(L % p.nb); L /= p.nb;
-  const int kvh = (int)(L % p.hkv);
-  const int b = (int)(L / p.hkv);
+  // item: ((b*hkv + kvh)*nb + i)*chunks + chunk (in 32 bits: the divisions stand in front of every workgroup's first load)
+  uint32_t L = blockIdx.x, rest = L / (uint32_t)p.chunks;
+  const int chunk = (int)(L - rest * (uint32_t)p.chunks);
+  L = rest; rest = L / (uint32_t)p.nb;
+  const int i = (int)(L - rest * (uint32_t)p.nb);
+  L = rest; rest = L / (uint32_t)p.hkv;
+  const int kvh = (int)(L - rest * (uint32_t)p.hkv);
+  const int b = (int)rest;
 
   // ---- the row's tiles: every 64-key tile of every listed block up to the diagonal one ----
   // The first wavefront reads 64 list entries at a time, one per lane (a single thread walking the list pays a
   // trip to memory per entry, at the start of every workgroup); the rank of a valid entry is a prefix count.
   if (wave == 0) {
+    // (the first entries are requested beside the row's length, not after it)
+    int ahead = p.kv_idx[(int64_t)i * p.max_k + (lane < p.max_k ? lane : p.max_k - 1)];
     int n = p.kv_cnt[i];
     if (n > p.max_k) n = p.max_k;
     n = __builtin_amdgcn_readfirstlane(n);
     int blocks = 0;
     for (int base = 0; base < n; base += 64) {
       const int e = base + lane;
-      const int j = e < n ? p.kv_idx[(int64_t)i * p.max_k + e] : -1;
+      if (base > 0) ahead = e < n ? p.kv_idx[(int64_t)i * p.max_k + e] : -1;
+      const int j = e < n ? ahead : -1;
       const bool valid = j >= 0 && j <= i;
       const uint64_t vm = __builtin_amdgcn_ballot_w64(valid);
       const int rank = blocks + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(vm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vm, 0));
@@ -245,7 +246,7 @@ void pa_bwd_dq_kernel(bwd_params p) {
 
   const int task = chunk * NW + wave;
   const bool active = task < p.tasks;
-  const int g = active ? task / slices : 0, sl = active ? task % slices : 0;
+  const int g = active ? task >> slice_bits : 0, sl = active ? task & ((1 << slice_bits) - 1) : 0;
   const int h = kvh * p.G + g;
   const int64_t tok = (int64_t)i * p.B + sl * 32 + ln;          // this lane's query
   const bool ok = active && tok < p.N;
@@ -355,6 +356,12 @@ void pa_bwd_dq_kernel(bwd_params p) {
         });
   }
   wait_vmcnt<0>();
+
+  // The sums that the dK/dV kernel, next on the stream, adds to with atomics start at zero: cleared here, a share per
+  // workgroup.  (A kernel of its own for it, and items found with 64-bit divisions, gradients in us: 32 heads on 8, block 128,
+  // N = 574 92.1 / 90.0, N = 131072 11456 / 11375; head_dim 64, block 64, N = 1000 47.1 / 45.4.)
+  for (int64_t e = 4 * ((int64_t)blockIdx.x * (64 * NW) + tid); e < p.sink_floats; e += 4 * (int64_t)gridDim.x * (64 * NW))
+    *reinterpret_cast<f32x4*>(p.dk_sink + e) = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // element r of tile dt is d = 32dt + 8(r/4) + 4hh + r%4 of this lane's query row: 8-byte pieces
   if (ok) {
@@ -863,13 +870,7 @@ int pa_launch_backward_bf16(const pa_backward_args& a) {
   p.dv_sink = (float*)ws;
 
   int st = POWATTN_OK;
-  if (sink_elems > 0) {
-    const int64_t zb = (2 * (int64_t)(align256((size_t)sink_elems * sizeof(float)) / sizeof(float)) + 255) / 256;
-    hipLaunchKernelGGL(pa_bwd_zero_kernel, dim3((uint32_t)zb), dim3(256), 0, a.stream, p.dk_sink,
-                       2 * (int64_t)(align256((size_t)sink_elems * sizeof(float)) / sizeof(float)));
-    st = pa_note_hip(hipGetLastError());
-    if (st != POWATTN_OK) return st;
-  }
+  p.sink_floats = sink_elems > 0 ? 2 * (int64_t)(align256((size_t)sink_elems * sizeof(float)) / sizeof(float)) : 0;
 
   const int64_t items = (int64_t)a.batch * a.hkv * a.nb * p.chunks;
   if (items > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
