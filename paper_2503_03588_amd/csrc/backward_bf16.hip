@@ -396,7 +396,7 @@ void pa_bwd_dq_kernel(bwd_params p) {
 // matrix instruction).  Training steps with
 // 32 query heads on 8 (28 on 4 at block 256), N = 32768: block 64 2.19 -> 1.98 ms, block 256 6.29 -> 4.65 ms (of which
 // the kernel 3.9 -> 2.3); N = 2000, block 64: 232 -> 144 us, block 256: 766 -> 254 us.
-template <int NSL, int QW, int QI, bool P32>
+template <int NSL, int QW, int QI, bool P32, int NST_>
 struct dkv_geo {
   static constexpr int NW = 2 * NSL * QW;        // wavefronts
   static constexpr int TR = 32 * QW * QI;        // queries per tile
@@ -404,7 +404,7 @@ struct dkv_geo {
   static constexpr int PBUF = NSL * QW * QI * PPIECE;    // P of one tile
   template <int D> static constexpr int tileb() { return TR / tile_geo<D>::RPI * tile_geo<D>::SRB; }
   template <int D> static constexpr int stageb() { return 2 * tileb<D>() + 8 * TR; }   // Q, dO, log-sum-exps, Deltas
-  static constexpr int NST = 3;                  // tile it+1 arriving, tile it (P side), tile it-1 (dS side)
+  static constexpr int NST = NST_;               // tiles it+1 .. it+NST-2 arriving, tile it (P side), tile it-1 (dS side)
   template <int D> static constexpr size_t lds() { return NST * (size_t)stageb<D>() + 2 * (size_t)PBUF; }
 };
 // copy instruction x of a wavefront's share of a tile and, if BOTH, of the tile behind it
@@ -419,11 +419,11 @@ __device__ __forceinline__ void dkv_copy(const __bf16* qb, const __bf16* ob, uin
     default: async_copy16_at<3 * STEP>(qb, voff, dst); if (BOTH) async_copy16_at<TILEB + 3 * STEP>(ob, voff, dst); break;
   }
 }
-template <int D, int NSL, int QW, int QI, bool P32>
+template <int D, int NSL, int QW, int QI, bool P32, int NST_>
 __global__ __launch_bounds__(128 * NSL * QW) __attribute__((amdgpu_waves_per_eu(2)))
 void pa_bwd_dkv_kernel(bwd_params p) {
   using G = tile_geo<D>;
-  using W = dkv_geo<NSL, QW, QI, P32>;
+  using W = dkv_geo<NSL, QW, QI, P32, NST_>;
   constexpr int NW = W::NW, TR = W::TR, PBUF = W::PBUF, NST = W::NST;
   constexpr int NC = G::NC, ND = G::ND;
   constexpr int TILEB = W::template tileb<D>(), STAGEB = W::template stageb<D>();
@@ -578,9 +578,19 @@ void pa_bwd_dkv_kernel(bwd_params p) {
   if (n32 - TR < m_lo || slab0 + 32 * NSL > p.N) { m_lo = 0x7fffffff; m_span = 0; }     // every tile
   const uint32_t pbase = lds0 + NST * STAGEB + (slice * QW + qg) * (QI * W::PPIECE) + lane * 16;
 
-  int q_next = fill();
+  // First queries of the tiles behind the one the P side works on; the copies run AHEAD tiles in front of it.
+  constexpr int AHEAD = NST - 2;
+  static_assert(AHEAD == 1 || AHEAD == 2, "one or two tiles on their way");
+  int q_next = fill(), q_after = 0;
+  if (AHEAD == 2 && n_tiles > 1) q_after = fill();
   // (after the first tile's copies: they would queue behind these row-per-lane loads)
   reg_rows<D>((krole ? p.v : p.k) + krow * D, kok, lane, xf);
+  if (AHEAD > 1) {
+    // Touched here, the compiler waits for them here, once.  Left to their first use, inside the loop, it puts a wait for
+    // everything outstanding there, the copies just issued included.
+#pragma unroll
+    for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(xf[c]));
+  }
 
   // in a tile with a mask: whether query qi attends this lane's key (key32 <= qi < n32, in one comparison)
   const uint32_t q_span = kok ? (uint32_t)(n32 - key32) : 0u;
@@ -613,9 +623,24 @@ void pa_bwd_dkv_kernel(bwd_params p) {
         for (int r = 0; r < 16; ++r) X[r] = 0.f;
       }
       const uint32_t rows_from = KR ? dot : qt;
-      pipelined_mfma<NC, PFD>(
-          [&](int m) { return row_frag<D>(rows_from, m, half, lane); },
-          [&](int m, bf16x8 a) { X = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[m], X, 0, 0, 0); });
+      if constexpr (NSL == 1) {
+        // (one wavefront per SIMD: two sums of half the products each, or every product waits for the one before it)
+        f32x16 X2;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X2[r] = 0.f;
+        pipelined_mfma<NC, PFD>(
+            [&](int m) { return row_frag<D>(rows_from, m, half, lane); },
+            [&](int m, bf16x8 a) {
+              if (m & 1) X2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[m], X2, 0, 0, 0);
+              else X = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[m], X, 0, 0, 0);
+            });
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X[r] += X2[r];
+      } else {
+        pipelined_mfma<NC, PFD>(
+            [&](int m) { return row_frag<D>(rows_from, m, half, lane); },
+            [&](int m, bf16x8 a) { X = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf[m], X, 0, 0, 0); });
+      }
       if (!KR) {
         auto elements = [&](auto masked) {
 #pragma unroll
@@ -671,10 +696,18 @@ void pa_bwd_dkv_kernel(bwd_params p) {
   };
   // Iteration it: the P side works on tile it, the dS side on tile it-1 while the copies of tile it+1 are under way.
   // A loop per side with the same number of barriers.
+  constexpr int CPF = CPT * (EITHER ? 1 : 2);      // copies of a fill; the first wavefront's vectors come on top
   auto top = [&](int it) {
-    wait_vmcnt<0>();
+    if (AHEAD == 1 || it + 1 >= n_tiles) wait_vmcnt<0>();
+    else if (wave == 0) wait_vmcnt<CPF + (TR == 32 ? 1 : 2)>();    // (tile it+1 may still be on its way)
+    else wait_vmcnt<CPF>();
     __syncthreads();      // tile it has landed; P of tile it-1 is in LDS; everybody is done with tile it-2
-    if (it + 1 < n_tiles) q_next = fill();
+    if (AHEAD == 1) {
+      if (it + 1 < n_tiles) q_next = fill();
+    } else {
+      q_next = q_after;
+      if (it + 2 < n_tiles) q_after = fill();
+    }
   };
   uint32_t stage = 0, pbuf = pbase;
   auto moved_on = [&]() {
@@ -781,19 +814,24 @@ int launch_dq(const bwd_params& p, int64_t items, hipStream_t stream) {
   hipLaunchKernelGGL((pa_bwd_dq_kernel<D, NW>), dim3((uint32_t)items), dim3(64 * NW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
 }
-template <int D, int NSL, int QW, int QI, bool P32>
+template <int D, int NSL, int QW, int QI, bool P32, int NST = 3>
 int launch_dkv(const bwd_params& p, int batch, hipStream_t stream) {
-  constexpr size_t lds = dkv_geo<NSL, QW, QI, P32>::template lds<D>();
+  constexpr size_t lds = dkv_geo<NSL, QW, QI, P32, NST>::template lds<D>();
+  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
   const int64_t gx = ((int64_t)p.nb + (int64_t)p.sink_blocks * (p.max_parts - 1)) * (p.B / (32 * NSL));
   if (gx > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
-  const void* fn = reinterpret_cast<const void*>(&pa_bwd_dkv_kernel<D, NSL, QW, QI, P32>);
+  const void* fn = reinterpret_cast<const void*>(&pa_bwd_dkv_kernel<D, NSL, QW, QI, P32, NST>);
   static std::atomic<unsigned long long> done{0};
   if (int st = pa_allow_dynamic_lds(fn, lds, done)) return st;
-  hipLaunchKernelGGL((pa_bwd_dkv_kernel<D, NSL, QW, QI, P32>), dim3((uint32_t)gx, (uint32_t)p.hkv, (uint32_t)batch),
+  hipLaunchKernelGGL((pa_bwd_dkv_kernel<D, NSL, QW, QI, P32, NST>), dim3((uint32_t)gx, (uint32_t)p.hkv, (uint32_t)batch),
                      dim3(128 * NSL * QW), lds, stream, p);
   return pa_note_hip(hipGetLastError());
 }
 // Which form of the kernel.  Training steps (forward and backward, 32 query heads on 8), MI355X:
+//  * Where every 32-key slab has a compute unit: those, one wavefront per SIMD, and at head_dim 128 two tiles on their way
+//    (there is LDS for four stages).  Gradients in us, 64-key slabs / these: head_dim 128, 32 heads on 8, block 128, N = 574
+//    89.8 / 79.9, block 64, N = 1000 55.5 / 51.9; 16 on 2, N = 2000 107 / 92; head_dim 64, block 128, N = 600 58.9 / 54.8, but
+//    block 64, N = 1000 (256 slabs) 45.7 / 48.2; with more workgroups than compute units (16 on 2, N = 4000) 129 / 143.
 //  * Up to one 64-key slab per compute unit the length of a column decides: 64-key slabs, two query groups.  Against
 //    one group: head_dim 128, N = 2000: block 64 0.139 / 0.149 ms, block 256 0.247 / 0.291; head_dim 64, N = 1000:
 //    block 64 0.063 / 0.078, block 128 0.089 / 0.115, block 256 0.117 / 0.158.
@@ -810,6 +848,10 @@ int launch_dkv_any(const bwd_params& p, int batch, hipStream_t stream) {
   int n_cu = 1;
   pa_current_device(nullptr, &n_cu);
   const int64_t slabs64 = (int64_t)p.nb * (p.B / 64) * p.hkv * batch;
+  const int64_t parts = p.sink_blocks > 0 ? (p.nb + p.part - 1) / p.part : 1;       // of the longest sink column
+  const int64_t wgs32 = (p.nb + p.sink_blocks * (parts - 1)) * (p.B / 32) * p.hkv * batch;
+  if (D == 128 && wgs32 <= n_cu) return launch_dkv<D, 1, 2, 1, true, 4>(p, batch, stream);
+  if (D == 64 && 4 * wgs32 <= 3 * n_cu) return launch_dkv<D, 1, 2, 1, true, 3>(p, batch, stream);
   if (slabs64 <= n_cu) return launch_dkv<D, 2, 2, 1, true>(p, batch, stream);
   if (p.B == 64) return launch_dkv<D, 2, 1, 1, true>(p, batch, stream);
   if constexpr (D == 64) return launch_dkv<D, 4, 2, 1, true>(p, batch, stream);

@@ -75,6 +75,20 @@ def test_gradients_match_oracle(B, W, S, flags, hq, hkv, n, d):
     run_backward(pa.Pattern(B, W, S, flags), 1, hq, hkv, n, d, seed=51)
 
 
+@pytest.mark.parametrize("B,W,S,hq,hkv,n,d", [
+    (64, 2, 1, 2, 1, 33, 128),         # one key beyond the first 32-key slab
+    (64, 2, 1, 2, 1, 64, 64),
+    (128, 3, 1, 4, 2, 353, 128),       # odd number of slabs in the last block
+    (256, 2, 0, 3, 1, 289, 128),       # slabs whose first tile of the diagonal block starts before them
+    (256, 2, 1, 2, 2, 700, 64),        # sink column, head_dim 64
+    (64, 1, 2, 8, 1, 2048, 128),       # sink columns in parts
+])
+def test_slabs_of_32_keys(B, W, S, hq, hkv, n, d):
+    """Launches so small that every 32-key slab has a compute unit: their form of the dK/dV kernel, which keeps two tiles
+    on their way at head_dim 128."""
+    run_backward(pa.Pattern(B, W, S), 1, hq, hkv, n, d, seed=n)
+
+
 def test_batch_and_scale():
     run_backward(pa.Pattern(64, 4, 1), 2, 4, 2, 1280, 128, seed=52, scale=0.07)
 
