@@ -1158,18 +1158,19 @@ int pa_launch_prefill_bf16(const pa_prefill_args& a) {
     if (a.n_pages < 1 || a.table_stride < 1 || a.n_pages * (int64_t)a.hkv * p.B > 0x7fffffffLL) return POWATTN_UNSUPPORTED;
   }
 
-  // A compute unit for every item: one item per workgroup, by the variant without any look-ahead.  It has two thirds of the
+  // Up to one and a half items per compute unit: one item per workgroup, by the variant without any look-ahead.  It has two thirds of the
   // instructions (each is fetched for the first time in such a launch), its Q rows come through LDS in the order of the
   // fragments, and the first product waits for them and one tile only.  us, chained / one item: 32 query heads on 8, blocks of
   // 64, N = 1000 18.0 / 15.7 (list included), 28 on 4, N = 923 17.3 / 14.9; a paged piece of 2000 at 30001 31.3 / 29.9; 206
-  // at 757, blocks of 128, 18.8 / 16.6; dense list, 16 on 2, N = 191 10.2 / 8.4.  Where only the device knows the
-  // lengths, most launches have fewer items than they could: up to twice as many as compute units (three pieces of up to 347
-  // rows, blocks of 256: 61.8 / 58.2).
+  // at 757, blocks of 128, 18.8 / 16.6; dense list, 16 on 2, N = 191 10.2 / 8.4.  With more items
+  // than compute units, 32 on 8, blocks of 64: 280 items 34.4 / 31.6, 376 40.8 / 39.6, 440 55.8 / 58.3, 504 44.6 / 47.1.
+  // Where only the device knows the lengths a launch has fewer items than it could: up to twice as many as compute units
+  // (three pieces of up to 347 rows, blocks of 256: 61.8 / 58.2).
   {
     int n_cu = 0;
     pa_current_device(nullptr, &n_cu);
     const int64_t slots = n_cu >= 8 ? n_cu / 8 : 1;
-    if (per_xcd <= (a.seq_len_dev ? 2 * slots : slots)) p.chain = 0;
+    if (2 * per_xcd <= (a.seq_len_dev ? 4 : 3) * slots) p.chain = 0;
   }
 
   // ring of 4 stages: 128 KB of LDS at head_dim 128, 64 KB at head_dim 64

@@ -131,3 +131,10 @@ def test_rows_too_long_to_be_chained(hq, hkv, eight, d):
     oo, ol = orc.attention_rows(*(synth.to_numpy_storage(t.cpu()) for t in (q, k, v)), rows, oracle_pattern(pat))
     assert np.abs(o[:, :, rows].double().cpu().numpy() - oo).max() <= TOL_O["bf16"]
     assert np.abs(lse[:, :, rows].double().cpu().numpy() - ol).max() <= TOL_LSE
+
+
+# The same calls with more items than one and a half per compute unit (two where the device knows the lengths): the
+# persistent variant, whose workgroups walk through several items.
+@pytest.mark.parametrize("kind,B,hq,hkv,d,batch,n,flags", [(kind, *m[:4], 2 * m[4], *m[5:]) for m in MANY for kind in KINDS[: 3 if m[-1] & pa.DENSE else 5]])
+def test_persistent_workgroups_give_the_same_rows(kind, B, hq, hkv, d, batch, n, flags):
+    test_many_items_take_eight_wavefronts(kind, B, hq, hkv, d, batch, n, flags)
