@@ -64,6 +64,8 @@ struct dec_params {
   int32_t B, W, S; uint32_t flags;
   int32_t hq, hkv, G, splits, subs;
   uint32_t subs_magic;  // ceil(2^32 / subs) for subs > 1: slot / subs = umulhi(slot, subs_magic) for every slot of a row
+  uint32_t salt;        // goes into the tags; another (even) number for every launch
+  uint32_t per_b_magic; // persistent workgroups: ceil(2^32 / items of a sequence) where that replaces the division of any item's number (else 0)
   int32_t kvh_first;    // 1: the KV head is the fastest digit of a workgroup's number, 0: the split
   int32_t fused;        // 1: the workgroups of a (sequence, KV head) merge their partials among themselves
   float c2;
@@ -87,14 +89,17 @@ struct dec_params {
 //    finisher advanced it only after every workgroup of the pair had stored packets, hence all of its wavefronts had read
 //    g, before the barrier in front of its stores), and the very first
 //    call on a workspace meets whatever the memory held: a word there passes for a tag only if it equals
-//    ~g ^ ((split + 1) << 24) for the word g found in the same memory (never for a memory filled with one byte
-//    value, zeros included).
-//  * No workgroup waits for another one: whoever finds a packet missing simply leaves.
+//    ~g ^ salt ^ ((split + 1) << 24) for the word g found in the same memory (never for a memory filled with one byte
+//    value, zeros included, nor for the packets of the call before: the salt is even).  The salt is a number of the
+//    launch, for memory that was a workspace before and has been something else in between: its word g may be an old one
+//    again, zero for instance, and packets with the tags of that generation may still be there.
+//  * No workgroup waits for another one: whoever finds a packet missing simply leaves.  (A look before the acknowledgement
+//    may find everything in place already; only the one after it has to be there.)
 // Calls that may run at the same time must not share a workspace (they would share generation numbers).
 // With more splits than this a merge kernel follows: what a workgroup reads grows with their number (b = 1, 8 KV heads, 48
 // chunks, us: 7 splits 11.0, 12 12.1, 20 and a merge kernel 9.2; b = 4: 12 splits 24, 20 and a merge kernel 16).
 constexpr int MAX_FUSED_SPLITS = 8;
-__device__ __forceinline__ uint32_t dec_tag(uint32_t gen, int split) { return ~gen ^ ((uint32_t)(split + 1) << 24); }
+__device__ __forceinline__ uint32_t dec_tag(uint32_t key, int split) { return ~key ^ ((uint32_t)(split + 1) << 24); }
 __device__ __forceinline__ void dec_put(uint64_t* slot, float x, uint32_t tag) {
   __hip_atomic_store(slot, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -346,6 +351,7 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
 
   bf16x8 qf[D / 32];
   dec_load_q<D>(qf, p, b, kvh, g, q4);
+  const uint32_t key = gen ^ p.salt;
   const dec_row row = dec_row_of(p, len_b);
   const int n_slots = row.n_slots;
 
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
       if (d == 0) { part[D] = M; part[D + 1] = L; }                  // an idle split leaves M = -inf, L = 0
     } else {
       uint64_t* pk = p.packets + (((int64_t)b * p.hq + h) * p.splits + split) * (D + 2);
-      const uint32_t tag = dec_tag(gen, split);
+      const uint32_t tag = dec_tag(key, split);
       dec_put(pk + d, acc, tag);
       if (d == 0) { dec_put(pk + D, M, tag); dec_put(pk + D + 1, L, tag); }
     }
@@ -427,55 +433,66 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
   if (p.splits == 1 || !p.fused) return;
 
   // ---- the workgroups of this (sequence, KV head) merge among themselves (protocol above) ----
+  // Writes the outputs whose packets are all there; returns which (bit x) are left.
+  auto combine = [&](unsigned todo) -> unsigned {
+    unsigned left = 0;
+#pragma unroll
+    for (int x = 0; x < EPT; ++x) {
+      const int e = tid + x * 64 * NW;
+      if (e >= p.G * D || !(todo >> x & 1)) continue;
+      const int gg = e / D, d = e % D;
+      const int h = kvh * p.G + gg;
+      const uint64_t* pk = p.packets + ((int64_t)b * p.hq + h) * p.splits * (D + 2);
+      bool valid = true;
+      float M = -INFINITY, L = 0.f, acc = 0.f;
+      uint64_t pm[MAX_FUSED_SPLITS], pl[MAX_FUSED_SPLITS], po[MAX_FUSED_SPLITS];
+#pragma unroll
+      for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {     // all loads before any is looked at
+        pm[y] = pl[y] = po[y] = 0;
+        if (y < p.splits && y != split) {              // uniform over the workgroup; its own partial is in registers
+          const uint64_t* ps = pk + (int64_t)y * (D + 2);
+          pm[y] = dec_get(ps + D); pl[y] = dec_get(ps + D + 1); po[y] = dec_get(ps + d);
+        }
+      }
+      // the reference point of all of them first, so that their weights do not depend on one another
+      float ls[MAX_FUSED_SPLITS], ms[MAX_FUSED_SPLITS];
+#pragma unroll
+      for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
+        ms[y] = -INFINITY; ls[y] = 0.f;
+        if (y >= p.splits) break;
+        if (y == split) { ms[y] = Ms[x]; ls[y] = Ls[x]; }              // this workgroup's own partial: the same bits
+        else {
+          const uint32_t want = dec_tag(key, y);
+          valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want && (uint32_t)(po[y] >> 32) == want;
+          ms[y] = __builtin_bit_cast(float, (uint32_t)pm[y]); ls[y] = __builtin_bit_cast(float, (uint32_t)pl[y]);
+        }
+        if (ls[y] > 0.f) M = fmaxf(M, ms[y]);                          // idle splits hold no outputs
+      }
+#pragma unroll
+      for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
+        if (y >= p.splits) break;
+        const float os = y == split ? accs[x] : __builtin_bit_cast(float, (uint32_t)po[y]);
+        const float wt = ls[y] > 0.f ? __builtin_amdgcn_exp2f(ms[y] - M) : 0.f;
+        L = fmaf(wt, ls[y], L);
+        acc = ls[y] > 0.f ? fmaf(wt, os, acc) : acc;
+      }
+      // Every thread for itself: a packet that has not landed belongs to a workgroup that will write this output.  (A thread
+      // that saw the packets of all splits knows that all their wavefronts have read the generation.)
+      if (!valid) { left |= 1u << x; continue; }
+      p.o[((int64_t)b * p.hq + h) * D + d] = (__bf16)(acc / L);
+      if (p.lse && d == 0) p.lse[(int64_t)b * p.hq + h] = (M + log2f(L)) * 0.69314718055994530942f;
+      if (e == 0) __hip_atomic_store(p.gen + (int64_t)b * p.hkv + kvh, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return left;
+  };
+  // With few splits a workgroup that is behind the others finds their packets in place at once, without waiting for its own to
+  // be acknowledged (us, without / with: 2 splits, batch 16 at 64K 12.45 / 12.31, 3 splits, batch 4 7.91 / 7.82); with
+  // more, the reads that come too early cost more (4 splits 7.86 / 7.96, 7 splits 8.87 / 9.09).
+  unsigned todo = ~0u;
+  if (p.splits <= 3) todo = combine(todo);
   __builtin_amdgcn_s_waitcnt(0);                       // vmcnt(0): memory has acknowledged this thread's packets
   __syncthreads();                                     // ... and every other thread's of this workgroup
-#pragma unroll
-  for (int x = 0; x < EPT; ++x) {
-    const int e = tid + x * 64 * NW;
-    if (e >= p.G * D) continue;
-    const int gg = e / D, d = e % D;
-    const int h = kvh * p.G + gg;
-    const uint64_t* pk = p.packets + ((int64_t)b * p.hq + h) * p.splits * (D + 2);
-    bool valid = true;
-    float M = -INFINITY, L = 0.f, acc = 0.f;
-    uint64_t pm[MAX_FUSED_SPLITS], pl[MAX_FUSED_SPLITS], po[MAX_FUSED_SPLITS];
-#pragma unroll
-    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {     // all loads before any is looked at
-      pm[y] = pl[y] = po[y] = 0;
-      if (y < p.splits && y != split) {              // uniform over the workgroup; its own partial is in registers
-        const uint64_t* ps = pk + (int64_t)y * (D + 2);
-        pm[y] = dec_get(ps + D); pl[y] = dec_get(ps + D + 1); po[y] = dec_get(ps + d);
-      }
-    }
-    // the reference point of all of them first, so that their weights do not depend on one another
-    float ls[MAX_FUSED_SPLITS], ms[MAX_FUSED_SPLITS];
-#pragma unroll
-    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
-      ms[y] = -INFINITY; ls[y] = 0.f;
-      if (y >= p.splits) break;
-      if (y == split) { ms[y] = Ms[x]; ls[y] = Ls[x]; }              // this workgroup's own partial: the same bits
-      else {
-        const uint32_t want = dec_tag(gen, y);
-        valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want && (uint32_t)(po[y] >> 32) == want;
-        ms[y] = __builtin_bit_cast(float, (uint32_t)pm[y]); ls[y] = __builtin_bit_cast(float, (uint32_t)pl[y]);
-      }
-      if (ls[y] > 0.f) M = fmaxf(M, ms[y]);                          // idle splits hold no outputs
-    }
-#pragma unroll
-    for (int y = 0; y < MAX_FUSED_SPLITS; ++y) {
-      if (y >= p.splits) break;
-      const float os = y == split ? accs[x] : __builtin_bit_cast(float, (uint32_t)po[y]);
-      const float wt = ls[y] > 0.f ? __builtin_amdgcn_exp2f(ms[y] - M) : 0.f;
-      L = fmaf(wt, ls[y], L);
-      acc = ls[y] > 0.f ? fmaf(wt, os, acc) : acc;
-    }
-    // Every thread for itself: a packet that has not landed belongs to a workgroup that will write this output.  (A thread
-    // that saw the packets of all splits knows that all their wavefronts have read the generation.)
-    if (!valid) continue;
-    p.o[((int64_t)b * p.hq + h) * D + d] = (__bf16)(acc / L);
-    if (p.lse && d == 0) p.lse[(int64_t)b * p.hq + h] = (M + log2f(L)) * 0.69314718055994530942f;
-    if (e == 0) __hip_atomic_store(p.gen + (int64_t)b * p.hkv + kvh, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (todo) combine(todo);
 }
 
 // Large batches: persistent workgroups.  With many more (sequence, KV head, split) items than compute units the
@@ -501,9 +518,9 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_stream_kernel(dec_params p,
   auto item_of = [&](int w) -> item_t {
     item_t it;
     const int w2 = w < n_items ? w : n_items - 1;          // beyond the end: any valid item (its loads are not issued)
-    it.b = w2 / per_b;
+    it.b = per_b == 1 ? w2 : p.per_b_magic ? (int)__umulhi((uint32_t)w2, p.per_b_magic) : w2 / per_b;
     const int r = w2 - it.b * per_b;
-    it.kvh = r / p.splits;
+    it.kvh = p.splits == 1 ? r : r / p.splits;
     it.split = r - it.kvh * p.splits;
     return it;
   };
@@ -752,6 +769,8 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   p.hq = a.hq; p.hkv = a.hkv; p.G = a.hq / a.hkv; p.splits = a.n_split; p.subs = a.pat.block / CH;
   p.subs_magic = p.subs > 1 ? (uint32_t)(((1ull << 32) + p.subs - 1) / p.subs) : 0u;
   p.c2 = a.scale * 1.44269504088896340736f;
+  static std::atomic<uint32_t> launches{0};
+  p.salt = (launches.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B1u) << 1;
   p.block_table = a.block_table; p.table_stride = a.table_stride;
   p.last_page = (int32_t)((a.n_pages < 0x7fffffff ? a.n_pages : 0x7fffffff) - 1);
   // few enough splits that every workgroup can afford to read all the others' partials: they merge among
@@ -777,6 +796,8 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
     if (stream_splits > 0 && items <= 0x7fffffff / 4 && max_slots <= 0x7fffffff / 4) {
       p.fused = 0;
       p.splits = stream_splits;
+      const int64_t per_b = (int64_t)a.hkv * stream_splits;
+      p.per_b_magic = per_b > 1 && items * per_b <= 0xffffffffLL ? (uint32_t)(((1ull << 32) + per_b - 1) / per_b) : 0u;
       const int n_pass = (int)((max_slots + (int64_t)stream_splits * NW - 1) / ((int64_t)stream_splits * NW));
       const size_t lds2 = 2 * (a.head_dim == 128 ? dec_o_bytes<128>(p.G) : dec_o_bytes<64>(p.G));   // at most 144 KB
       static std::atomic<unsigned long long> attr_done[2];

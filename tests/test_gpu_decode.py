@@ -66,6 +66,21 @@ def test_exchange_between_splits_at_chunk_edges(W, hq, hkv, d, batch):
     run_decode(pa.Pattern(64, W, 1), batch, hq, hkv, 4096, d, edges[:batch], seed=77, calls=2)
 
 
+def test_a_workspace_whose_generation_is_an_old_one_again():
+    """Memory that was a workspace, was used for something else that put its first words back, and is a workspace again:
+    the packets of the earlier call are still there and must not be taken for this call's."""
+    pat, hq, hkv, d, cap = pa.Pattern(64, 2, 1), 4, 2, 128, 512
+    q, k, v = (t.cuda() for t in synth.decode_inputs(1, hq, hkv, cap, d, "bf16", 43))
+    ws = pa.decode_workspace(pat, 1, hq, hkv, d, cap)
+    lens = [torch.tensor([n], dtype=torch.int32, device="cuda") for n in (64, 65)]     # the second split idle, then one token
+    want = [[t.clone() for t in pa.decode(pat, q, k, v, n)] for n in lens]
+    for step in range(60):
+        ws[:256].zero_()
+        o, lse = pa.decode(pat, q, k, v, lens[step & 1], workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[step & 1][0]) and torch.equal(lse, want[step & 1][1]), step
+
+
 def test_sliding_window_flag_and_scale():
     run_decode(pa.Pattern(64, 5, 1, flags=0), 2, 4, 2, 2048, 128, [2048, 900], seed=32, scale=0.11)
 
