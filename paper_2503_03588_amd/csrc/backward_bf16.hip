@@ -10,7 +10,7 @@
 //           lane = one query.  S^T = K Q^T and dP^T = V dO^T share the K/V tiles in LDS; dQ^T += K^T dS^T.
 //           It also forms Delta = rowsum(dO * O) of its rows (dO is in its registers anyway) and leaves it, with
 //           the log-sum-exp in base-2 units, in the workspace for the kernel below.
-//   dkv   : a workgroup per (batch, KV head, slab of 64 or 128 keys of a block) walks the COLUMN of the block mask: the
+//   dkv   : a workgroup per (batch, KV head, slab of 32, 64 or 128 keys of a block) walks the COLUMN of the block mask: the
 //           query blocks j .. j+W-1 and j + 2^k (closed form), all of them for a sink block; lane = one key.
 //           Q and dO tiles go through LDS; dV^T += dO^T P, dK^T += Q^T dS.  A sink block's column is
 //           as long as the sequence: it is cut into parts that add into an fp32 buffer, converted at the end.
