@@ -77,25 +77,25 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     return OUT
 
 
-def build_host(verbose: bool = True) -> str:
+def build_host(verbose: bool = True, src: str = os.path.join(CSRC, "host.cpp"), out: str = HOST_OUT) -> str:
     """csrc/host.cpp -> _host.so: the binding's ordinary calls marshalled natively (host code only)."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
-    tmp = HOST_OUT + ".tmp"
+    tmp = out + ".tmp"
     cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-isystem", os.path.join(root, "include"), "-isystem", sysconfig.get_paths()["include"],
-           os.path.join(CSRC, "host.cpp"), "-o", tmp,
+           src, "-o", tmp,
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"the host module failed to build:\n{res.stdout}\n{res.stderr}")
-    os.replace(tmp, HOST_OUT)
+    os.replace(tmp, out)
     if verbose:
-        print(f"built {HOST_OUT}")
-    return HOST_OUT
+        print(f"built {out}")
+    return out
 
 
 def build_microbench(verbose: bool = True):

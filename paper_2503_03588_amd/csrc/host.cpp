@@ -13,6 +13,10 @@
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include "../../include/powattn.h"
 
+#ifndef POWATTN_HOST_DEVICE            // (the tests build this file for ordinary memory, where they stand in for the library)
+#define POWATTN_HOST_DEVICE at::kCUDA
+#endif
+
 namespace {
 
 // the library's entry points (addresses handed over by binding.py, which loads the library)
@@ -42,7 +46,7 @@ void need(bool ok) { if (!ok) throw other_way{}; }
 const at::Tensor& tensor(PyObject* o) {
   need((PyObject*)Py_TYPE(o) == tensor_type);
   const at::Tensor& t = THPVariable_Unpack(o);
-  need(t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous());
+  need(t.defined() && t.device().type() == POWATTN_HOST_DEVICE && t.layout() == at::kStrided && t.is_contiguous());
   static const c10::DispatchKeySet wrappers({c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::FuncTorchBatched,
                                              c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::Functionalize,
                                              c10::DispatchKey::Conjugate, c10::DispatchKey::Negative, c10::DispatchKey::ZeroTensor});
@@ -97,13 +101,21 @@ int32_t dtype_code(const at::Tensor& t) {
   need(t.scalar_type() == at::kFloat);
   return POWATTN_F32;
 }
-// the library's call, other Python threads running meanwhile
+// Other Python threads run while it lives.  The interpreter is this thread's again whichever way the scope is left: the
+// library's arguments are formed inside it, and what forms them throws.
+struct without_gil {
+  PyThreadState* ts = PyEval_SaveThread();
+  ~without_gil() { PyEval_RestoreThread(ts); }
+};
+// the library's call
 template <class F>
 void call(F&& f) {
   void* stream = current_stream();
-  PyThreadState* ts = PyEval_SaveThread();
-  const int st = f(stream);
-  PyEval_RestoreThread(ts);
+  int st;
+  {
+    without_gil others_run;
+    st = f(stream);
+  }
   need(st == POWATTN_OK);
 }
 int32_t small(int64_t x) { need(x >= 0 && x <= 0x7fffffff); return (int32_t)x; }
@@ -185,7 +197,7 @@ PyObject* f_mask_build(PyObject*, PyObject* const* a, Py_ssize_t n) {   // value
     const int64_t nb = lib.num_blocks(&pat, len);
     const int32_t mk = lib.max_k(&pat, len);
     need(nb > 0 && mk > 0);
-    const auto opt = at::TensorOptions().dtype(at::kInt).device(at::kCUDA);
+    const auto opt = at::TensorOptions().dtype(at::kInt).device(POWATTN_HOST_DEVICE);
     at::Tensor idx = at::empty({nb, (int64_t)mk}, opt), cnt = at::empty({nb}, opt);
     call([&](void* stream) { return lib.mask_build(&pat, len, (int32_t*)data(cnt), (int32_t*)data(idx), mk, nullptr, stream); });
     PyObject* t = PyTuple_New(3);

@@ -5,6 +5,7 @@ import ctypes
 import pytest
 import torch
 
+from host_on_cpu import host_cpu, stand_in  # noqa: F401 (fixtures)
 from paper_2503_03588_amd import binding as pa
 
 PAT = pa.Pattern(64, 3, 1)
@@ -35,6 +36,32 @@ def test_out_of_the_ordinary_is_left_alone():
     assert host.mask_build(PAT._values, 128.0) is NotImplemented
     with pytest.raises(TypeError):
         host.prefill(PAT._values)
+
+
+def test_a_refusal_inside_the_call_comes_back_to_python(stand_in):
+    """Sizes that do not fit the library's integers are found while its arguments are formed, with other threads running."""
+    huge = 2 ** 31
+    q, k = torch.empty(1, huge, 0, 64), torch.empty(1, 2, 0, 64)
+    q1, k1 = torch.empty(0, huge, 64), torch.empty(0, 2, 64, 64)
+    none = torch.empty(0, dtype=torch.int32)
+    cnt, idx = torch.zeros(4, dtype=torch.int32), torch.zeros(4, 4, dtype=torch.int32)
+    table = torch.zeros(1, 4, dtype=torch.int32)
+    one = torch.zeros(1, dtype=torch.int32)
+    pages = torch.empty(0, 2, 64, 64)
+    ws = torch.empty(256, dtype=torch.uint8)
+    host, v = pa._native, PAT._values
+    for args in [
+        (host.prefill, v, cnt, idx, q, k, k, None, None, 0.0, True),
+        (host.prefill_chunk, v, cnt, idx, q, k, k, 0, None, None, 0.0, True),
+        (host.prefill_chunk_paged, v, cnt, idx, q, pages, pages, table, 0, None, None, 0.0, True),
+        (host.prefill_batch_paged, v, cnt, idx, q, pages, pages, table, one, one, None, None, 0.0, True),
+        (host.prefill_varlen, v, cnt, idx, q, k, k, one, None, None, 0.0, True),
+        (host.decode, v, q1, k1, k1, none, None, None, 0.0, ws, True),
+        (host.decode_paged, v, q1, pages, pages, torch.empty(0, 4, dtype=torch.int32), none, None, None, 0.0, ws, True),
+        (host.backward, v, cnt, idx, q, k, k, q, torch.empty(1, huge, 0), q, None, None, None, 0.0, ws),
+    ]:
+        assert args[0](*args[1:]) is NotImplemented, args[0].__name__
+    assert not stand_in.seen
 
 
 def calls():
