@@ -90,7 +90,7 @@ def _enable_native():
         return
     L = lib()
     _host.bind(*(ctypes.cast(getattr(L, "powattn_" + name), ctypes.c_void_p).value for name in _NATIVE_ENTRY_POINTS),
-               torch.Tensor, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+               torch.Tensor, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
     _native = _host
 
 

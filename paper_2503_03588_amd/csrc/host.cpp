@@ -1,8 +1,8 @@
 // The calls of binding.py for the ordinary case, in one step from Python to the library: tensors that are plain, contiguous
 // and on the GPU, the current stream.  Each function takes the arguments of the Python function of the same name, looks at
 // them, allocates what the caller did not pass and calls the C entry point; it returns NotImplemented, having done nothing,
-// whenever anything is out of the ordinary (and when the library reports an error), and the Python function then goes its
-// own way, which is also where the errors come from.
+// whenever anything is out of the ordinary, and the Python function then goes its own way.  The library is called once: a
+// status it reports is raised as the Python functions raise it.
 //
 // Reason: the smallest calls take 8 to 12 us on the GPU, and marshalling them in Python took 6 to 8 us each (tensor
 // attributes, shapes, ctypes); now 3.5 to 5.  A list and a prefill of 1024 fp32 queries, two calls, were paced by it: 16.2 us
@@ -37,8 +37,10 @@ struct {
 PyObject* get_device = nullptr;       // torch._C._cuda_getDevice
 PyObject* get_stream = nullptr;       // torch._C._cuda_getCurrentRawStream
 PyObject* tensor_type = nullptr;      // torch.Tensor
+PyObject* check = nullptr;            // binding._check: raises for a status
 
 struct other_way {};                  // thrown: not the ordinary case
+struct raised {};                     // thrown: the Python exception is set
 
 void need(bool ok) { if (!ok) throw other_way{}; }
 
@@ -107,16 +109,23 @@ struct without_gil {
   PyThreadState* ts = PyEval_SaveThread();
   ~without_gil() { PyEval_RestoreThread(ts); }
 };
-// the library's call
+// the library's call, `name` being its entry point
 template <class F>
-void call(F&& f) {
+void call(const char* name, F&& f) {
   void* stream = current_stream();
   int st;
   {
     without_gil others_run;
     st = f(stream);
   }
-  need(st == POWATTN_OK);
+  if (st == POWATTN_OK) return;
+  // (not other_way: the Python way would call again, and a HIP error is reported once: the second call would launch)
+  PyObject* r = PyObject_CallFunction(check, "is", st, name);
+  if (r) {
+    Py_DECREF(r);
+    PyErr_Format(PyExc_RuntimeError, "%s: status %d", name, st);
+  }
+  throw raised{};
 }
 int32_t small(int64_t x) { need(x >= 0 && x <= 0x7fffffff); return (int32_t)x; }
 
@@ -183,6 +192,8 @@ PyObject* guarded(Py_ssize_t n, Py_ssize_t expected, F&& f) {
     PyObject* r = f();
     if (r) return r;
     PyErr_Clear();
+  } catch (const raised&) {
+    return nullptr;
   } catch (const other_way&) {
   } catch (const std::exception&) {    // (an allocation that failed: the Python way raises it)
   }
@@ -199,7 +210,7 @@ PyObject* f_mask_build(PyObject*, PyObject* const* a, Py_ssize_t n) {   // value
     need(nb > 0 && mk > 0);
     const auto opt = at::TensorOptions().dtype(at::kInt).device(POWATTN_HOST_DEVICE);
     at::Tensor idx = at::empty({nb, (int64_t)mk}, opt), cnt = at::empty({nb}, opt);
-    call([&](void* stream) { return lib.mask_build(&pat, len, (int32_t*)data(cnt), (int32_t*)data(idx), mk, nullptr, stream); });
+    call("powattn_mask_build", [&](void* stream) { return lib.mask_build(&pat, len, (int32_t*)data(cnt), (int32_t*)data(idx), mk, nullptr, stream); });
     PyObject* t = PyTuple_New(3);
     if (!t) return nullptr;
     PyTuple_SET_ITEM(t, 0, THPVariable_Wrap(cnt));
@@ -224,7 +235,7 @@ PyObject* f_prefill(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[8]);
     outputs out(a[6], a[7], a[9], q, {b, hq, len});
-    call([&](void* stream) { return lib.prefill(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill", [&](void* stream) { return lib.prefill(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                      small(k.size(1)), len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -244,7 +255,7 @@ PyObject* f_prefill_chunk(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[9]);
     outputs out(a[7], a[8], a[10], q, {b, hq, len});
-    call([&](void* stream) { return lib.prefill_chunk(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill_chunk", [&](void* stream) { return lib.prefill_chunk(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                            small(k.size(1)), start, len, k.size(2), small(d), code, scale, stream); });
     return out.pair();
   });
@@ -262,7 +273,7 @@ PyObject* f_prefill_chunk_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[10]);
     outputs out(a[8], a[9], a[11], q, {b, hq, len});
-    call([&](void* stream) { return lib.prefill_chunk_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, data(out.o), out.lse_ptr(),
+    call("powattn_prefill_chunk_paged", [&](void* stream) { return lib.prefill_chunk_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, data(out.o), out.lse_ptr(),
                                  small(b), small(hq), pg.hkv, start, len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -282,7 +293,7 @@ PyObject* f_prefill_batch_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[11]);
     outputs out(a[9], a[10], a[12], q, {b, hq, rows});
-    call([&](void* stream) { return lib.prefill_batch_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, (const int32_t*)data(start),
+    call("powattn_prefill_batch_paged", [&](void* stream) { return lib.prefill_batch_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, (const int32_t*)data(start),
                                  (const int32_t*)data(len), rows, data(out.o), out.lse_ptr(), small(b), small(hq), pg.hkv, small(d),
                                  code, scale, stream); });
     return out.pair();
@@ -304,7 +315,7 @@ PyObject* f_prefill_varlen(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[9]);
     outputs out(a[7], a[8], a[10], q, {b, hq, len}, true);
-    call([&](void* stream) { return lib.prefill_varlen(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill_varlen", [&](void* stream) { return lib.prefill_varlen(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                             small(k.size(1)), (const int32_t*)data(lens), len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -324,7 +335,7 @@ PyObject* f_decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[7]);
     outputs out(a[5], a[6], a[9], q, {b, hq});
-    call([&](void* stream) { return lib.decode(&pat, data(q), data(k), data(v), (const int32_t*)data(lens), k.size(2), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_decode", [&](void* stream) { return lib.decode(&pat, data(q), data(k), data(v), (const int32_t*)data(lens), k.size(2), data(out.o), out.lse_ptr(), small(b), small(hq),
                     small(k.size(1)), small(d), code, scale, data(ws), ws.nbytes(), stream); });
     return out.pair();
   });
@@ -343,7 +354,7 @@ PyObject* f_decode_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[8]);
     outputs out(a[6], a[7], a[10], q, {b, hq});
-    call([&](void* stream) { return lib.decode_paged(&pat, data(q), pg.k, pg.v, pg.n, pg.table, pg.stride, (const int32_t*)data(lens), data(out.o), out.lse_ptr(),
+    call("powattn_decode_paged", [&](void* stream) { return lib.decode_paged(&pat, data(q), pg.k, pg.v, pg.n, pg.table, pg.stride, (const int32_t*)data(lens), data(out.o), out.lse_ptr(),
                           small(b), small(hq), pg.hkv, small(d), code, scale, data(ws), ws.nbytes(), stream); });
     return out.pair();
   });
@@ -377,7 +388,7 @@ PyObject* f_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       need(bytes > 0);
       ws = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
     }
-    call([&](void* stream) { return lib.backward(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(o), (const float*)data(lse), data(dout),
+    call("powattn_backward", [&](void* stream) { return lib.backward(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(o), (const float*)data(lse), data(dout),
                                                  data(grad[0]), data(grad[1]), data(grad[2]), small(b), small(hq), hkv, len, small(d), code,
                                                  scale, data(ws), ws.nbytes(), stream); });
     PyObject* t = PyTuple_New(3);
@@ -390,18 +401,18 @@ PyObject* f_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// addresses of the entry points in the order of `lib`, torch.Tensor, the device and the stream look-up
+// addresses of the entry points in the order of `lib`, torch.Tensor, the device and the stream look-up, binding._check
 PyObject* f_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   constexpr Py_ssize_t N_FN = sizeof(lib) / sizeof(void*);
-  if (n != N_FN + 3) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; }
+  if (n != N_FN + 4) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; }
   void* fn[N_FN];
   for (Py_ssize_t i = 0; i < N_FN; ++i) {
     fn[i] = PyLong_AsVoidPtr(a[i]);
     if (!fn[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry point"); return nullptr; }
   }
   memcpy(&lib, fn, sizeof lib);
-  for (int i = 0; i < 3; ++i) Py_INCREF(a[N_FN + i]);
-  tensor_type = a[N_FN]; get_device = a[N_FN + 1]; get_stream = a[N_FN + 2];
+  for (int i = 0; i < 4; ++i) Py_INCREF(a[N_FN + i]);
+  tensor_type = a[N_FN]; get_device = a[N_FN + 1]; get_stream = a[N_FN + 2]; check = a[N_FN + 3];
   Py_RETURN_NONE;
 }
 

@@ -51,7 +51,7 @@ class StandIn:
 
     def bind(self, host):
         host.bind(*(ctypes.cast(getattr(self, "powattn_" + n), ctypes.c_void_p).value for n in pa._NATIVE_ENTRY_POINTS),
-                  torch.Tensor, lambda: 0, lambda device: STREAM)
+                  torch.Tensor, lambda: 0, lambda device: STREAM, pa._check)
 
 
 @pytest.fixture

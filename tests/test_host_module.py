@@ -15,7 +15,7 @@ def bound_host():
     from paper_2503_03588_amd import _host
     L = pa.lib()
     _host.bind(*(ctypes.cast(getattr(L, "powattn_" + n), ctypes.c_void_p).value for n in pa._NATIVE_ENTRY_POINTS), torch.Tensor,
-               torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+               torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, pa._check)
     return _host
 
 
@@ -62,6 +62,29 @@ def test_a_refusal_inside_the_call_comes_back_to_python(stand_in):
     ]:
         assert args[0](*args[1:]) is NotImplemented, args[0].__name__
     assert not stand_in.seen
+
+
+def test_the_library_is_called_once_and_its_status_raised(stand_in):
+    q, ws = torch.zeros(1, 2, 64, 64), torch.empty(1 << 20, dtype=torch.uint8)
+    cnt, idx = torch.zeros(1, dtype=torch.int32), torch.zeros(1, 4, dtype=torch.int32)
+    one, table, q1 = torch.ones(1, dtype=torch.int32), torch.zeros(1, 1, dtype=torch.int32), q[:, :, 0].contiguous()
+    for name, call in [
+        ("prefill", lambda: pa.prefill(PAT, cnt, idx, q, q, q)),
+        ("prefill_chunk", lambda: pa.prefill_chunk(PAT, cnt, idx, q, q, q, 0)),
+        ("prefill_chunk_paged", lambda: pa.prefill_chunk_paged(PAT, cnt, idx, q, q, q, table, 0)),
+        ("prefill_batch_paged", lambda: pa.prefill_batch_paged(PAT, cnt, idx, q, q, q, table, one, one)),
+        ("prefill_varlen", lambda: pa.prefill_varlen(PAT, cnt, idx, q, q, q, one)),
+        ("decode", lambda: pa.decode(PAT, q1, q, q, one, workspace=ws)),
+        ("decode_paged", lambda: pa.decode_paged(PAT, q1, q, q, table, one, workspace=ws)),
+        ("backward", lambda: pa.backward(PAT, cnt, idx, q, q, q, q, q[..., 0].contiguous(), q, workspace=ws)),
+        ("mask_build", lambda: pa._native.mask_build(PAT._values, 64)),
+    ]:
+        for status in (pa.HIP_ERROR, pa.WORKSPACE_TOO_SMALL):
+            stand_in.seen.clear()
+            stand_in.answers[:] = [status]
+            with pytest.raises(pa.PowattnError, match="powattn_" + name + ": status"):
+                call()
+            assert len(stand_in.seen) == 1 and not stand_in.answers, name
 
 
 def calls():
@@ -146,7 +169,7 @@ def test_every_ordinary_call_goes_the_native_way(monkeypatch):
 
 
 @pytest.mark.gpu
-def test_errors_are_the_python_ways_own():
+def test_errors_are_those_of_the_python_way():
     pa.mask_build(PAT, 64)
     q = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16, device="cuda")
     cnt, idx, _ = pa.mask_build(PAT, 64)
