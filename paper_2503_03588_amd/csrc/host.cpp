@@ -7,6 +7,9 @@
 // Reason: the smallest calls take 8 to 12 us on the GPU, and marshalling them in Python took 6 to 8 us each (tensor
 // attributes, shapes, ctypes); now 3.5 to 5.  A list and a prefill of 1024 fp32 queries, two calls, were paced by it: 16.2 us
 // -> 12.0; a call that is waited for: one decode step 21.7 -> 18.6 us, a chunk 46.3 -> 42.7, list and prefill 32.8 -> 25.6.
+#include <algorithm>
+#include <array>
+#include <initializer_list>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -103,13 +106,14 @@ int32_t dtype_code(const at::Tensor& t) {
   need(t.scalar_type() == at::kFloat);
   return POWATTN_F32;
 }
-// Other Python threads run while it lives.  The interpreter is this thread's again whichever way the scope is left: the
-// library's arguments are formed inside it, and what forms them throws.
+// Other Python threads run while it lives, as in torch's own allocations (one that waits for the GPU may wait for a callback
+// that needs the interpreter).  The interpreter is this thread's again whichever way the scope is left: the outputs are
+// allocated and the library's arguments formed inside it, and both throw.
 struct without_gil {
   PyThreadState* ts = PyEval_SaveThread();
   ~without_gil() { PyEval_RestoreThread(ts); }
 };
-// the library's call, `name` being its entry point
+// the allocations and the library's call, `name` being its entry point
 template <class F>
 void call(const char* name, F&& f) {
   void* stream = current_stream();
@@ -129,20 +133,30 @@ void call(const char* name, F&& f) {
 }
 int32_t small(int64_t x) { need(x >= 0 && x <= 0x7fffffff); return (int32_t)x; }
 
-// o and lse: the caller's, or new ones; returned as the pair that the Python functions return
+// o and lse: the caller's, or new ones (allocate(), with other threads running); returned as the pair that the Python
+// functions return
 struct outputs {
   PyObject* o_arg; PyObject* lse_arg;
+  const at::Tensor& q;
+  std::array<int64_t, 3> lse_shape;
+  size_t lse_dims;
+  bool new_lse, zeros;
   at::Tensor o, lse;
-  bool zeroed;
-  outputs(PyObject* o_in, PyObject* lse_in, PyObject* want_lse, const at::Tensor& q, at::IntArrayRef lse_shape, bool zeros = false)
-      : o_arg(o_in), lse_arg(lse_in), zeroed(zeros) {
+  outputs(PyObject* o_in, PyObject* lse_in, PyObject* want_lse, const at::Tensor& queries, std::initializer_list<int64_t> shape,
+          bool zeroed = false)
+      : o_arg(o_in), lse_arg(lse_in), q(queries), lse_dims(shape.size()), zeros(zeroed) {
     need(want_lse == Py_True || want_lse == Py_False);
+    std::copy(shape.begin(), shape.end(), lse_shape.begin());
     if (o_arg != Py_None) o = tensor(o_arg);
     if (lse_arg != Py_None) lse = tensor(lse_arg);
+    new_lse = lse_arg == Py_None && want_lse == Py_True;
+  }
+  void allocate() {
     if (o_arg == Py_None) o = zeros ? at::zeros_like(q) : at::empty_like(q);
-    if (lse_arg == Py_None && want_lse == Py_True) {
+    if (new_lse) {
       const auto opt = q.options().dtype(at::kFloat);
-      lse = zeros ? at::zeros(lse_shape, opt) : at::empty(lse_shape, opt);
+      const at::IntArrayRef shape(lse_shape.data(), lse_dims);
+      lse = zeros ? at::zeros(shape, opt) : at::empty(shape, opt);
     }
   }
   float* lse_ptr() { return lse.defined() ? (float*)data(lse) : nullptr; }
@@ -209,8 +223,12 @@ PyObject* f_mask_build(PyObject*, PyObject* const* a, Py_ssize_t n) {   // value
     const int32_t mk = lib.max_k(&pat, len);
     need(nb > 0 && mk > 0);
     const auto opt = at::TensorOptions().dtype(at::kInt).device(POWATTN_HOST_DEVICE);
-    at::Tensor idx = at::empty({nb, (int64_t)mk}, opt), cnt = at::empty({nb}, opt);
-    call("powattn_mask_build", [&](void* stream) { return lib.mask_build(&pat, len, (int32_t*)data(cnt), (int32_t*)data(idx), mk, nullptr, stream); });
+    at::Tensor idx, cnt;
+    call("powattn_mask_build", [&](void* stream) {
+      idx = at::empty({nb, (int64_t)mk}, opt);
+      cnt = at::empty({nb}, opt);
+      return lib.mask_build(&pat, len, (int32_t*)data(cnt), (int32_t*)data(idx), mk, nullptr, stream);
+    });
     PyObject* t = PyTuple_New(3);
     if (!t) return nullptr;
     PyTuple_SET_ITEM(t, 0, THPVariable_Wrap(cnt));
@@ -235,7 +253,7 @@ PyObject* f_prefill(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[8]);
     outputs out(a[6], a[7], a[9], q, {b, hq, len});
-    call("powattn_prefill", [&](void* stream) { return lib.prefill(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill", [&](void* stream) { out.allocate(); return lib.prefill(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                      small(k.size(1)), len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -255,7 +273,7 @@ PyObject* f_prefill_chunk(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[9]);
     outputs out(a[7], a[8], a[10], q, {b, hq, len});
-    call("powattn_prefill_chunk", [&](void* stream) { return lib.prefill_chunk(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill_chunk", [&](void* stream) { out.allocate(); return lib.prefill_chunk(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                            small(k.size(1)), start, len, k.size(2), small(d), code, scale, stream); });
     return out.pair();
   });
@@ -273,7 +291,7 @@ PyObject* f_prefill_chunk_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[10]);
     outputs out(a[8], a[9], a[11], q, {b, hq, len});
-    call("powattn_prefill_chunk_paged", [&](void* stream) { return lib.prefill_chunk_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, data(out.o), out.lse_ptr(),
+    call("powattn_prefill_chunk_paged", [&](void* stream) { out.allocate(); return lib.prefill_chunk_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, data(out.o), out.lse_ptr(),
                                  small(b), small(hq), pg.hkv, start, len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -293,7 +311,7 @@ PyObject* f_prefill_batch_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[11]);
     outputs out(a[9], a[10], a[12], q, {b, hq, rows});
-    call("powattn_prefill_batch_paged", [&](void* stream) { return lib.prefill_batch_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, (const int32_t*)data(start),
+    call("powattn_prefill_batch_paged", [&](void* stream) { out.allocate(); return lib.prefill_batch_paged(&pat, l.cnt, l.idx, l.max_k, data(q), pg.k, pg.v, pg.table, pg.stride, pg.n, (const int32_t*)data(start),
                                  (const int32_t*)data(len), rows, data(out.o), out.lse_ptr(), small(b), small(hq), pg.hkv, small(d),
                                  code, scale, stream); });
     return out.pair();
@@ -315,7 +333,7 @@ PyObject* f_prefill_varlen(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[9]);
     outputs out(a[7], a[8], a[10], q, {b, hq, len}, true);
-    call("powattn_prefill_varlen", [&](void* stream) { return lib.prefill_varlen(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_prefill_varlen", [&](void* stream) { out.allocate(); return lib.prefill_varlen(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(out.o), out.lse_ptr(), small(b), small(hq),
                             small(k.size(1)), (const int32_t*)data(lens), len, small(d), code, scale, stream); });
     return out.pair();
   });
@@ -335,7 +353,7 @@ PyObject* f_decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[7]);
     outputs out(a[5], a[6], a[9], q, {b, hq});
-    call("powattn_decode", [&](void* stream) { return lib.decode(&pat, data(q), data(k), data(v), (const int32_t*)data(lens), k.size(2), data(out.o), out.lse_ptr(), small(b), small(hq),
+    call("powattn_decode", [&](void* stream) { out.allocate(); return lib.decode(&pat, data(q), data(k), data(v), (const int32_t*)data(lens), k.size(2), data(out.o), out.lse_ptr(), small(b), small(hq),
                     small(k.size(1)), small(d), code, scale, data(ws), ws.nbytes(), stream); });
     return out.pair();
   });
@@ -354,7 +372,7 @@ PyObject* f_decode_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int32_t code = dtype_code(q);
     const float scale = number(a[8]);
     outputs out(a[6], a[7], a[10], q, {b, hq});
-    call("powattn_decode_paged", [&](void* stream) { return lib.decode_paged(&pat, data(q), pg.k, pg.v, pg.n, pg.table, pg.stride, (const int32_t*)data(lens), data(out.o), out.lse_ptr(),
+    call("powattn_decode_paged", [&](void* stream) { out.allocate(); return lib.decode_paged(&pat, data(q), pg.k, pg.v, pg.n, pg.table, pg.stride, (const int32_t*)data(lens), data(out.o), out.lse_ptr(),
                           small(b), small(hq), pg.hkv, small(d), code, scale, data(ws), ws.nbytes(), stream); });
     return out.pair();
   });
@@ -382,15 +400,18 @@ PyObject* f_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     at::Tensor grad[3], ws;
     for (int i = 0; i < 3; ++i) if (a[9 + i] != Py_None) grad[i] = tensor(a[9 + i]);
     if (a[13] != Py_None) ws = tensor(a[13]);
-    for (int i = 0; i < 3; ++i) if (!grad[i].defined()) grad[i] = at::empty_like(*like[i]);
+    size_t bytes = 0;
     if (!ws.defined()) {
-      const size_t bytes = lib.backward_workspace_bytes(&pat, small(b), small(hq), hkv, len, small(d));
+      bytes = lib.backward_workspace_bytes(&pat, small(b), small(hq), hkv, len, small(d));
       need(bytes > 0);
-      ws = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
     }
-    call("powattn_backward", [&](void* stream) { return lib.backward(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(o), (const float*)data(lse), data(dout),
-                                                 data(grad[0]), data(grad[1]), data(grad[2]), small(b), small(hq), hkv, len, small(d), code,
-                                                 scale, data(ws), ws.nbytes(), stream); });
+    call("powattn_backward", [&](void* stream) {
+      for (int i = 0; i < 3; ++i) if (!grad[i].defined()) grad[i] = at::empty_like(*like[i]);
+      if (!ws.defined()) ws = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
+      return lib.backward(&pat, l.cnt, l.idx, l.max_k, data(q), data(k), data(v), data(o), (const float*)data(lse), data(dout),
+                          data(grad[0]), data(grad[1]), data(grad[2]), small(b), small(hq), hkv, len, small(d), code,
+                          scale, data(ws), ws.nbytes(), stream);
+    });
     PyObject* t = PyTuple_New(3);
     if (!t) return nullptr;
     for (int i = 0; i < 3; ++i) {

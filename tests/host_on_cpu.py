@@ -14,12 +14,31 @@ from paper_2503_03588_amd import build as b
 
 STREAM = 0x5150
 
+# Beside the module: how many allocations were made with the GIL held, and without, since the last look.
+WATCH = """
+namespace {
+struct watching : c10::Allocator {
+  c10::Allocator* real;
+  int held = 0, released = 0;
+  c10::DataPtr allocate(size_t n) override { ++(PyGILState_Check() ? held : released); return real->allocate(n); }
+  c10::DeleterFnPtr raw_deleter() const override { return real->raw_deleter(); }
+  void copy_data(void* to, const void* from, size_t n) const override { real->copy_data(to, from, n); }
+} watch;
+}
+extern "C" void watch_allocations(int on) {
+  if (on) { watch.real = c10::GetAllocator(c10::kCPU); watch.held = watch.released = 0; c10::SetAllocator(c10::kCPU, &watch, 200); }
+  else c10::SetAllocator(c10::kCPU, watch.real, 200);
+}
+extern "C" int allocations_with_gil() { return watch.held; }
+extern "C" int allocations_without_gil() { return watch.released; }
+"""
+
 
 @pytest.fixture(scope="session")
 def host_cpu(tmp_path_factory):
     d = tmp_path_factory.mktemp("host")
     src = d / "host_cpu.cpp"
-    src.write_text(f'#define POWATTN_HOST_DEVICE at::kCPU\n#include "{os.path.join(b.CSRC, "host.cpp")}"\n')
+    src.write_text(f'#define POWATTN_HOST_DEVICE at::kCPU\n#include "{os.path.join(b.CSRC, "host.cpp")}"\n' + WATCH)
     out = b.build_host(verbose=False, src=str(src), out=str(d / "_host.so"))
     loader = importlib.machinery.ExtensionFileLoader("host_cpu._host", out)
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("host_cpu._host", loader))

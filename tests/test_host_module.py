@@ -87,6 +87,30 @@ def test_the_library_is_called_once_and_its_status_raised(stand_in):
             assert len(stand_in.seen) == 1 and not stand_in.answers, name
 
 
+def test_other_threads_run_while_outputs_are_allocated(stand_in):
+    watch = ctypes.CDLL(pa._native.__file__)
+    q, ws = torch.zeros(1, 2, 64, 64), torch.empty(1 << 20, dtype=torch.uint8)
+    cnt, idx = torch.zeros(1, dtype=torch.int32), torch.zeros(1, 4, dtype=torch.int32)
+    one, table, q1, lse = torch.ones(1, dtype=torch.int32), torch.zeros(1, 1, dtype=torch.int32), q[:, :, 0].contiguous(), q[..., 0].contiguous()
+    for new, call in [
+        (2, lambda: pa._native.mask_build(PAT._values, 64)),
+        (2, lambda: pa.prefill(PAT, cnt, idx, q, q, q)),
+        (2, lambda: pa.prefill_chunk(PAT, cnt, idx, q, q, q, 0)),
+        (2, lambda: pa.prefill_chunk_paged(PAT, cnt, idx, q, q, q, table, 0)),
+        (2, lambda: pa.prefill_batch_paged(PAT, cnt, idx, q, q, q, table, one, one)),
+        (2, lambda: pa.prefill_varlen(PAT, cnt, idx, q, q, q, one)),
+        (2, lambda: pa.decode(PAT, q1, q, q, one, workspace=ws)),
+        (1, lambda: pa.decode_paged(PAT, q1, q, q, table, one, workspace=ws, want_lse=False)),
+        (4, lambda: pa.backward(PAT, cnt, idx, q, q, q, q, lse, q)),
+    ]:
+        watch.watch_allocations(1)
+        try:
+            call()
+        finally:
+            watch.watch_allocations(0)
+        assert (watch.allocations_with_gil(), watch.allocations_without_gil()) == (0, new)
+
+
 def calls():
     """(name, function of no arguments) of every entry point that is marshalled natively; fresh outputs each time."""
     gen = torch.Generator(device="cuda")
