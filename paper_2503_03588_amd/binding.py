@@ -94,6 +94,16 @@ def _enable_native():
     _native = _host
 
 
+def _after_fork():
+    # A child of a process that has initialised the GPU cannot use it.  The Python marshalling finds that out (_stream) and
+    # raises; the native one would go on to the GPU.  (A child that may use the GPU enables it afresh, at its first call.)
+    global _native, _native_tried
+    _native, _native_tried = None, False
+
+
+os.register_at_fork(after_in_child=_after_fork)
+
+
 def lib() -> ctypes.CDLL:
     """Loads the built library (never builds it, never falls back)."""
     global _lib, _native, _native_tried

@@ -1,6 +1,7 @@
 """The native marshalling of the binding's ordinary calls (csrc/host.cpp) against the Python marshalling: the same results
 for the calls it takes, nothing done for the ones it leaves alone, the same errors."""
 import ctypes
+import os
 
 import pytest
 import torch
@@ -109,6 +110,21 @@ def test_other_threads_run_while_outputs_are_allocated(stand_in):
         finally:
             watch.watch_allocations(0)
         assert (watch.allocations_with_gil(), watch.allocations_without_gil()) == (0, new)
+
+
+def test_a_forked_child_starts_without_the_native_way(monkeypatch):
+    monkeypatch.setattr(pa, "_native", object())
+    monkeypatch.setattr(pa, "_native_tried", True)
+    r, w = os.pipe()
+    child = os.fork()
+    if child == 0:
+        os.write(w, repr((pa._native, pa._native_tried)).encode())
+        os._exit(0)
+    os.waitpid(child, 0)
+    assert os.read(r, 100) == b"(None, False)"
+    os.close(r)
+    os.close(w)
+    assert pa._native is not None and pa._native_tried
 
 
 def calls():
