@@ -8,6 +8,7 @@ import torch
 
 from host_on_cpu import host_cpu, stand_in  # noqa: F401 (fixtures)
 from paper_2503_03588_amd import binding as pa
+from paper_2503_03588_amd import build
 
 PAT = pa.Pattern(64, 3, 1)
 
@@ -110,6 +111,18 @@ def test_other_threads_run_while_outputs_are_allocated(stand_in):
         finally:
             watch.watch_allocations(0)
         assert (watch.allocations_with_gil(), watch.allocations_without_gil()) == (0, new)
+
+
+@pytest.mark.parametrize("compiler,why", [("/nonexistent/compiler", "No such file"), ("false", "failed to build")])
+def test_the_build_does_without_a_host_module(monkeypatch, tmp_path, capsys, compiler, why):
+    old = tmp_path / "_host.so"
+    old.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(build, "HOST_OUT", str(old))
+    monkeypatch.setenv("CXX", compiler)
+    assert build.build_host_or_do_without() is None
+    assert not old.exists()
+    said = capsys.readouterr().err
+    assert "_host.so was not built" in said and why in said
 
 
 def test_a_forked_child_starts_without_the_native_way(monkeypatch):
