@@ -11,6 +11,7 @@ import ctypes
 import functools
 import operator
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -76,6 +77,7 @@ _lib = None
 # answered with NotImplemented, nothing done, for everything out of the ordinary, which then goes through Python as ever.
 _native = None
 _native_tried = False
+HOST_PATH = os.path.join(_HERE, "_host.so")
 _NATIVE_ENTRY_POINTS = ("num_blocks", "max_k", "mask_build", "prefill", "prefill_chunk", "prefill_chunk_paged",
                         "prefill_batch_paged", "prefill_varlen", "decode", "decode_paged", "backward_workspace_bytes",
                         "backward")
@@ -84,9 +86,12 @@ _NATIVE_ENTRY_POINTS = ("num_blocks", "max_k", "mask_build", "prefill", "prefill
 def _enable_native():
     global _native, _native_tried
     _native_tried = True
+    if not os.path.exists(HOST_PATH):    # not built: the Python marshalling below does the same
+        return
     try:
         from . import _host
-    except ImportError:                  # not built: the Python marshalling below does the same
+    except ImportError as e:             # built for another torch or Python, for instance
+        warnings.warn(f"{HOST_PATH} cannot be loaded, calls are marshalled in Python: {e}", RuntimeWarning, stacklevel=2)
         return
     L = lib()
     _host.bind(*(ctypes.cast(getattr(L, "powattn_" + name), ctypes.c_void_p).value for name in _NATIVE_ENTRY_POINTS),

@@ -2,6 +2,8 @@
 for the calls it takes, nothing done for the ones it leaves alone, the same errors."""
 import ctypes
 import os
+import sys
+import warnings
 
 import pytest
 import torch
@@ -123,6 +125,24 @@ def test_the_build_does_without_a_host_module(monkeypatch, tmp_path, capsys, com
     assert not old.exists()
     said = capsys.readouterr().err
     assert "_host.so was not built" in said and why in said
+
+
+def test_a_host_module_that_cannot_be_loaded_is_reported(monkeypatch, tmp_path):
+    monkeypatch.setattr(pa, "_native", None)
+    monkeypatch.setattr(pa, "_native_tried", False)
+    monkeypatch.setitem(sys.modules, "paper_2503_03588_amd._host", None)     # its import fails
+    monkeypatch.delattr("paper_2503_03588_amd._host", raising=False)
+    broken = tmp_path / "_host.so"
+    broken.write_bytes(b"")
+    monkeypatch.setattr(pa, "HOST_PATH", str(broken))
+    with pytest.warns(RuntimeWarning, match="cannot be loaded"):
+        pa._enable_native()
+    assert pa._native is None and pa._native_tried
+    monkeypatch.setattr(pa, "HOST_PATH", str(tmp_path / "not built"))
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        pa._enable_native()
+    assert pa._native is None
 
 
 def test_a_forked_child_starts_without_the_native_way(monkeypatch):
