@@ -64,9 +64,9 @@ struct dec_params {
   int32_t B, W, S; uint32_t flags;
   int32_t hq, hkv, G, splits, subs;
   uint32_t subs_magic;  // ceil(2^32 / subs) for subs > 1: slot / subs = umulhi(slot, subs_magic) for every slot of a row
-  uint32_t salt;        // goes into the tags; another (even) number for every launch
   uint32_t per_b_magic; // persistent workgroups: ceil(2^32 / items of a sequence) where that replaces the division of any item's number (else 0)
   int32_t kvh_first;    // 1: the KV head is the fastest digit of a workgroup's number, 0: the split
+  int32_t through;      // 1: packets are taken back with stores that go through to memory
   int32_t fused;        // 1: the workgroups of a (sequence, KV head) merge their partials among themselves
   float c2;
   const int32_t* block_table;   // paged cache: page of block j of sequence b at [b * table_stride + j]; else null
@@ -85,23 +85,37 @@ struct dec_params {
 //    the latest one loads after that, when every other workgroup's packets are in memory.
 //  * Several may finish: they combine the same values in the same order and write the same bits.  (Each thread decides for
 //    the outputs it owns: a vote of the workgroup took another 0.6 us.)
-//  * Nothing stale is taken for valid: what the workspace holds from the call before carries generation g - 1 (the
-//    finisher advanced it only after every workgroup of the pair had stored packets, hence all of its wavefronts had read
-//    g, before the barrier in front of its stores), and the very first
-//    call on a workspace meets whatever the memory held: a word there passes for a tag only if it equals
-//    ~g ^ salt ^ ((split + 1) << 24) for the word g found in the same memory (never for a memory filled with one byte
-//    value, zeros included, nor for the packets of the call before: the salt is even).  The salt is a number of the
-//    launch, for memory that was a workspace before and has been something else in between: its word g may be an old one
-//    again, zero for instance, and packets with the tags of that generation may still be there.
+//  * Nothing stale is taken for valid.  An output's packet is taken back by the thread that used it (its tag becomes 0, and
+//    a valid one is odd): no call leaves one behind, whatever the memory is used for before it is a workspace again, its
+//    words g put back to old ones included, and also where a graph replays the launch.  Maxima and sums are shared by the
+//    threads of a head and stay; those of the call before carry generation g - 1 (the finisher advanced it only after every
+//    workgroup of the pair had stored packets, hence all of its wavefronts had read g, before the barrier in front of its
+//    stores), and older ones whose generation is back do not fit the output's packet, whose tag is formed with the bits of
+//    the maximum and the sum that go with it.  The very first call on a workspace meets whatever the memory held: a word
+//    there passes for the tag of a maximum only if it equals ~g ^ ((split + 1) << 24) for the word g found in the same
+//    memory (never for a memory filled with one byte value, zeros included).
 //  * No workgroup waits for another one: whoever finds a packet missing simply leaves.  (A look before the acknowledgement
 //    may find everything in place already; only the one after it has to be there.)
 // Calls that may run at the same time must not share a workspace (they would share generation numbers).
 // With more splits than this a merge kernel follows: what a workgroup reads grows with their number (b = 1, 8 KV heads, 48
 // chunks, us: 7 splits 11.0, 12 12.1, 20 and a merge kernel 9.2; b = 4: 12 splits 24, 20 and a merge kernel 16).
 constexpr int MAX_FUSED_SPLITS = 8;
-__device__ __forceinline__ uint32_t dec_tag(uint32_t key, int split) { return ~key ^ ((uint32_t)(split + 1) << 24); }
+__device__ __forceinline__ uint32_t dec_tag(uint32_t gen, int split) { return ~gen ^ ((uint32_t)(split + 1) << 24); }
+// ... of an output: with the maximum and the sum of its head; odd
+__device__ __forceinline__ uint32_t dec_tag_of_output(uint32_t tag, uint32_t m_bits, uint32_t l_bits) {
+  return (tag ^ m_bits ^ (l_bits << 16 | l_bits >> 16)) | 1u;
+}
 __device__ __forceinline__ void dec_put(uint64_t* slot, float x, uint32_t tag) {
   __hip_atomic_store(slot, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The launch that has to see it is a later one, so an ordinary store is enough; where the launch fills the chip, it is better
+// written through at once than left for the end of the kernel (us, 32 query heads on 8, not taken back / ordinary / through:
+// batch 1 7.9 / 8.0 / 8.4, batch 4 9.05 / 9.05 / 9.32, batch 16 12.15 / 12.75 / 12.21).
+template <int SCOPE>
+__device__ __forceinline__ void dec_take_back(uint64_t* first, int splits, int stride) {
+#pragma unroll
+  for (int y = 0; y < MAX_FUSED_SPLITS; ++y)
+    if (y < splits) __hip_atomic_store(first + (int64_t)y * stride, (uint64_t)0, __ATOMIC_RELAXED, SCOPE);
 }
 __device__ __forceinline__ uint64_t dec_get(const uint64_t* slot) {
   return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -351,7 +365,6 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
 
   bf16x8 qf[D / 32];
   dec_load_q<D>(qf, p, b, kvh, g, q4);
-  const uint32_t key = gen ^ p.salt;
   const dec_row row = dec_row_of(p, len_b);
   const int n_slots = row.n_slots;
 
@@ -425,8 +438,8 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
       if (d == 0) { part[D] = M; part[D + 1] = L; }                  // an idle split leaves M = -inf, L = 0
     } else {
       uint64_t* pk = p.packets + (((int64_t)b * p.hq + h) * p.splits + split) * (D + 2);
-      const uint32_t tag = dec_tag(key, split);
-      dec_put(pk + d, acc, tag);
+      const uint32_t tag = dec_tag(gen, split);
+      dec_put(pk + d, acc, dec_tag_of_output(tag, __builtin_bit_cast(uint32_t, M), __builtin_bit_cast(uint32_t, L)));
       if (d == 0) { dec_put(pk + D, M, tag); dec_put(pk + D + 1, L, tag); }
     }
   }
@@ -442,7 +455,7 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
       if (e >= p.G * D || !(todo >> x & 1)) continue;
       const int gg = e / D, d = e % D;
       const int h = kvh * p.G + gg;
-      const uint64_t* pk = p.packets + ((int64_t)b * p.hq + h) * p.splits * (D + 2);
+      uint64_t* pk = p.packets + ((int64_t)b * p.hq + h) * p.splits * (D + 2);
       bool valid = true;
       float M = -INFINITY, L = 0.f, acc = 0.f;
       uint64_t pm[MAX_FUSED_SPLITS], pl[MAX_FUSED_SPLITS], po[MAX_FUSED_SPLITS];
@@ -462,8 +475,9 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
         if (y >= p.splits) break;
         if (y == split) { ms[y] = Ms[x]; ls[y] = Ls[x]; }              // this workgroup's own partial: the same bits
         else {
-          const uint32_t want = dec_tag(key, y);
-          valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want && (uint32_t)(po[y] >> 32) == want;
+          const uint32_t want = dec_tag(gen, y);
+          valid = valid && (uint32_t)(pm[y] >> 32) == want && (uint32_t)(pl[y] >> 32) == want
+                  && (uint32_t)(po[y] >> 32) == dec_tag_of_output(want, (uint32_t)pm[y], (uint32_t)pl[y]);
           ms[y] = __builtin_bit_cast(float, (uint32_t)pm[y]); ls[y] = __builtin_bit_cast(float, (uint32_t)pl[y]);
         }
         if (ls[y] > 0.f) M = fmaxf(M, ms[y]);                          // idle splits hold no outputs
@@ -477,10 +491,13 @@ __global__ __launch_bounds__(64 * NW) void pa_decode_kernel(dec_params p) {
         acc = ls[y] > 0.f ? fmaf(wt, os, acc) : acc;
       }
       // Every thread for itself: a packet that has not landed belongs to a workgroup that will write this output.  (A thread
-      // that saw the packets of all splits knows that all their wavefronts have read the generation.)
+      // that saw the packets of all splits knows that all their wavefronts have read the generation.)  Packets that are taken
+      // back are missing to the other workgroups' threads for the same output, which has been written then.
       if (!valid) { left |= 1u << x; continue; }
       p.o[((int64_t)b * p.hq + h) * D + d] = (__bf16)(acc / L);
       if (p.lse && d == 0) p.lse[(int64_t)b * p.hq + h] = (M + log2f(L)) * 0.69314718055994530942f;
+      if (p.through) dec_take_back<__HIP_MEMORY_SCOPE_AGENT>(pk + d, p.splits, D + 2);
+      else dec_take_back<__HIP_MEMORY_SCOPE_WORKGROUP>(pk + d, p.splits, D + 2);
       if (e == 0) __hip_atomic_store(p.gen + (int64_t)b * p.hkv + kvh, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return left;
@@ -769,8 +786,6 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   p.hq = a.hq; p.hkv = a.hkv; p.G = a.hq / a.hkv; p.splits = a.n_split; p.subs = a.pat.block / CH;
   p.subs_magic = p.subs > 1 ? (uint32_t)(((1ull << 32) + p.subs - 1) / p.subs) : 0u;
   p.c2 = a.scale * 1.44269504088896340736f;
-  static std::atomic<uint32_t> launches{0};
-  p.salt = (launches.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B1u) << 1;
   p.block_table = a.block_table; p.table_stride = a.table_stride;
   p.last_page = (int32_t)((a.n_pages < 0x7fffffff ? a.n_pages : 0x7fffffff) - 1);
   // few enough splits that every workgroup can afford to read all the others' partials: they merge among
@@ -782,6 +797,7 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   // a pair are on one XCD: their exchange is quicker, but where the launch fills the chip the loads are slower.  us, KV head /
   // split fastest: batch 1 8.1 / 8.2, batch 4 (one query head per KV head) 7.5 / 7.8, batch 16 12.8 / 12.4.
   p.kvh_first = 2 * (int64_t)a.batch * a.hkv * a.n_split <= n_cu;
+  p.through = 2 * (int64_t)a.batch * a.hkv * a.n_split > n_cu;
   // As many work items as compute units, or more: persistent workgroups that keep bytes in flight across items.
   // With at least one (sequence, KV head) pair per compute unit a pair is one item, walked in passes of NW chunks, and the
   // outputs are written by the same kernel; with fewer pairs but still four (sequence, KV head, split) items per

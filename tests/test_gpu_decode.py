@@ -81,6 +81,34 @@ def test_a_workspace_whose_generation_is_an_old_one_again():
         assert torch.equal(o, want[step & 1][0]) and torch.equal(lse, want[step & 1][1]), step
 
 
+@pytest.mark.parametrize("W,splits", [(2, 2), (9, 3), (20, 6)])      # with and without the early look at the others' packets
+def test_a_replayed_call_whose_generation_is_an_old_one_again(W, splits):
+    """The same inside a graph, whose launches are the same at every replay: the graph itself puts the workspace's first words
+    back, as a graph does that uses the workspace's memory for something else; the lengths change between the replays."""
+    pat, hq, hkv, d, cap = pa.Pattern(64, W, 1), 4, 2, 128, 4096
+    q, k, v = (t.cuda() for t in synth.decode_inputs(1, hq, hkv, cap, d, "bf16", 43))
+    ws = pa.decode_workspace(pat, 1, hq, hkv, d, cap)
+    assert ws.numel() == 256 + -(-hq * splits * (d + 2) * 8 // 256) * 256
+    lens = [torch.tensor([n], dtype=torch.int32, device="cuda") for n in (64, 65, 4096, 1000)]
+    want = [[t.clone() for t in pa.decode(pat, q, k, v, n)] for n in lens]
+    n = lens[0].clone()
+    o, lse = torch.empty_like(q), torch.empty(1, hq, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        pa.decode(pat, q, k, v, n, o=o, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ws[:256].fill_(0)
+        pa.decode(pat, q, k, v, n, o=o, lse=lse, workspace=ws)
+    for step in range(200):
+        n.copy_(lens[step % 4])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, want[step % 4][0]) and torch.equal(lse, want[step % 4][1]), step
+
+
 def test_sliding_window_flag_and_scale():
     run_decode(pa.Pattern(64, 5, 1, flags=0), 2, 4, 2, 2048, 128, [2048, 900], seed=32, scale=0.11)
 
@@ -112,8 +140,8 @@ def test_context_of_131072_tokens():
 
 
 def test_decode_replayed_from_a_hip_graph():
-    # The call keeps no per-call state on the host (the generation numbers of the merge live in the workspace), so
-    # a captured launch can be replayed: capture one decode step per entry point, replay each several times with
+    # What tells a call's partials from those of the call before lives in the workspace, nothing of it in the launch's
+    # arguments, so a captured launch can be replayed: capture one decode step per entry point, replay each several times with
     # eager calls on the same inputs and changed inputs in between, and compare every replay with the eager result.
     pat = pa.Pattern(64, 4, 1)
     batch, hq, hkv, cap, d = 4, 8, 2, 8192, 128
