@@ -793,10 +793,12 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   p.fused = (a.n_split > 1 && a.n_split <= MAX_FUSED_SPLITS) ? 1 : 0;
   int n_cu = 1;
   pa_current_device(nullptr, &n_cu);
-  // Workgroups are dealt to the eight XCDs in turn, so with the KV head as the fastest digit (and eight of them) all splits of
-  // a pair are on one XCD: their exchange is quicker, but where the launch fills the chip the loads are slower.  us, KV head /
-  // split fastest: batch 1 8.1 / 8.2, batch 4 (one query head per KV head) 7.5 / 7.8, batch 16 12.8 / 12.4.
-  p.kvh_first = 2 * (int64_t)a.batch * a.hkv * a.n_split <= n_cu;
+  // Workgroups are dealt to the eight XCDs in turn, so with the KV head as the fastest digit, and a multiple of eight of them,
+  // all splits of a pair are on one XCD: their exchange is quicker, but where the launch fills the chip the loads are slower.
+  // us, KV head / split fastest, 32 query heads on 8: batch 1 8.10 / 8.20, 2 8.51 / 8.70, 4 9.06 / 9.11, 8 9.62 / 9.72 (short rows
+  // 7.98 / 8.43), 16 12.8 / 12.4; 16 heads on 16 8.38 / 8.52.  With four KV heads the splits of a pair are on several XCDs
+  // either way, and of every XCD's pairs on more: 28 on 4, batch 2 10.62 / 10.29, 4 11.45 / 10.85, 8 12.04 / 11.23.
+  p.kvh_first = a.hkv % 8 == 0 && 2 * (int64_t)a.batch * a.hkv * a.n_split <= n_cu;
   p.through = 2 * (int64_t)a.batch * a.hkv * a.n_split > n_cu;
   // As many work items as compute units, or more: persistent workgroups that keep bytes in flight across items.
   // With at least one (sequence, KV head) pair per compute unit a pair is one item, walked in passes of NW chunks, and the
