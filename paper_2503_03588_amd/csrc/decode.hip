@@ -27,8 +27,8 @@
 //    the result; with several, every workgroup leaves its unnormalised partial
 //    in the workspace as tagged 8-byte packets, waits until memory has taken
 //    them, and then reads the packets of the other workgroups: the one whose
-//    packets landed last finds all of them in place and writes the output (a
-//    second launch would cost more than the whole merge).  The wavefronts' partials are read for the wavefronts that have
+//    packets landed last finds all of them in place and writes the output
+//    (with many splits a merge kernel does that instead).  The wavefronts' partials are read for the wavefronts that have
 //    a chunk, and the weights of the splits do not wait for one another.  There are no
 //    counters and nothing in the workspace has to be initialised: a packet
 //    is valid when its tag matches the generation number that the (sequence,
@@ -97,9 +97,12 @@ struct dec_params {
 //  * No workgroup waits for another one: whoever finds a packet missing simply leaves.  (A look before the acknowledgement
 //    may find everything in place already; only the one after it has to be there.)
 // Calls that may run at the same time must not share a workspace (they would share generation numbers).
-// With more splits than this a merge kernel follows: what a workgroup reads grows with their number (b = 1, 8 KV heads, 48
-// chunks, us: 7 splits 11.0, 12 12.1, 20 and a merge kernel 9.2; b = 4: 12 splits 24, 20 and a merge kernel 16).
-constexpr int MAX_FUSED_SPLITS = 8;
+// With more splits than this a merge kernel follows: what a workgroup reads grows with their number.  us, merged among
+// themselves / by the kernel, 32 query heads on 8: 7 splits, batch 2 10.35 / 8.9, 5 19.8 / 15.2 (batch 1 level); 8 splits, batch 4,
+// 29 chunks 12.3 / 10.9, 62 chunks 18.2 / 15.7, batch 8 37.8 / 32.5, 128 heads on 8 24.2 / 13.5.  Up to 6 the kernel's time on the
+// GPU is no longer either (6 splits, batch 1 8.7 / 7.85), but its launch takes the host longer than the step takes the GPU:
+// launched from Python, one after another, such steps were paced at 8.7 to 9.1 us on some hosts.
+constexpr int MAX_FUSED_SPLITS = 6;
 __device__ __forceinline__ uint32_t dec_tag(uint32_t gen, int split) { return ~gen ^ ((uint32_t)(split + 1) << 24); }
 // ... of an output: with the maximum and the sum of its head; odd
 __device__ __forceinline__ uint32_t dec_tag_of_output(uint32_t tag, uint32_t m_bits, uint32_t l_bits) {
@@ -110,7 +113,8 @@ __device__ __forceinline__ void dec_put(uint64_t* slot, float x, uint32_t tag) {
 }
 // The launch that has to see it is a later one, so an ordinary store is enough; where the launch fills the chip, it is better
 // written through at once than left for the end of the kernel (us, 32 query heads on 8, not taken back / ordinary / through:
-// batch 1 7.9 / 8.0 / 8.4, batch 4 9.05 / 9.05 / 9.32, batch 16 12.15 / 12.75 / 12.21).
+// batch 1 7.9 / 8.0 / 8.4, batch 4 9.05 / 9.05 / 9.32, batch 16 12.15 / 12.75 / 12.21; 28 on 4, ordinary: batch 2 9.4 / 9.9, 4
+// 10.15 / 10.6; all of them at the end of the kernel instead: 0 to 0.5 more).
 template <int SCOPE>
 __device__ __forceinline__ void dec_take_back(uint64_t* first, int splits, int stride) {
 #pragma unroll
@@ -714,7 +718,8 @@ int launch_decode(const dec_params& p, int batch, hipStream_t stream) {
 // Where that leaves compute units idle, more of them pull on the memory system: about four chunks each, in at most half of
 // the compute units (the exchange of the partials costs more with every workgroup).  us, 8 KV heads, 12 or 13 chunks,
 // 2 / 3 / 4 / 6 / 8 splits: batch 1 8.5 / 7.9 / 7.7 / 8.1 / 8.9, 4 9.2 / 8.8 / 9.0 / 10.5 / 12.0, 8 9.6 / 9.5 / 10.6 / 16.7 / 19.5.
-// Longer rows of small batches are cut finer still, and a merge kernel follows (figures at MAX_FUSED_SPLITS).
+// Rows of 29 chunks or more are cut to one workgroup per compute unit, and a merge kernel follows from 7 splits on (figures at
+// MAX_FUSED_SPLITS; batch 1, 48 chunks: 7 splits 11.0, 20 and a merge kernel 9.2).
 int32_t pa_decode_splits(const powattn_pattern* pat, int32_t batch, int32_t hkv, int64_t capacity) {
   const int32_t mk = powattn_max_k(pat, capacity);
   if (mk < 1) return 0;
@@ -724,7 +729,7 @@ int32_t pa_decode_splits(const powattn_pattern* pat, int32_t batch, int32_t hkv,
   if (s > 8) s = 8;
   if (base * s < 256) {                              // not enough workgroups to cover the chip
     int64_t want = (slots + 3) / 4;
-    if (want < MAX_FUSED_SPLITS) {
+    if (want < 8) {
       if (want > 128 / base) want = 128 / base;
     } else {
       const int64_t cap = slots / 2;
