@@ -76,7 +76,9 @@ void pa_prefill_f32_kernel(f32_params p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 15, kg = lane >> 4;
-  const int dpart = DS == 1 ? 0 : (int)blockIdx.x / p.q_tiles;             // (at most four: a compare each)
+  int dpart = 0;                                               // (a quotient below four: a compare each)
+#pragma unroll
+  for (int x = 1; x < DS; ++x) dpart += (int)blockIdx.x >= x * p.q_tiles;
   const int qx = (int)blockIdx.x - dpart * p.q_tiles, qblk = quot(qx, p.B / QR, p.per_block_magic);
   const int qb = p.nb - 1 - qblk;                              // longest rows first
   const int q_in_blk = (qx - qblk * (p.B / QR)) * QR;
@@ -346,8 +348,9 @@ int launch(f32_params p, int32_t batch, hipStream_t stream) {
 // At most 64 queries at head_dim 64 and 32 at 128, which is what the 256 registers of a wavefront hold.
 // Where even workgroups of 16 queries leave half of the compute units idle, the output's columns are dealt to two or four
 // workgroups: half of a workgroup's products are those of the output, and the scores are
-// formed anew.  us with the list, one / more workgroups: head_dim 128, 2 heads, N = 1000 17.8 / 16.0, N = 130 (four) 12.1 / 11.0;
-// head_dim 64, 2 heads, N = 1024 12.15 / 11.9.  (Steps of six or eight key tiles instead of four at head_dim 64: 12.5, 13.2.)
+// formed anew.  us with the list, one / more workgroups: head_dim 128, 2 heads, N = 1000 17.8 / 16.0, N = 130 (four) 12.1 / 11.0.
+// Without it, head_dim 64: 2 heads, N = 1024 10.46 / 10.13, 512 10.10 / 9.81, 130 7.06 / 6.72; 4 heads, N = 500 8.28 / 7.81; 8, N = 200
+// 7.55 / 7.15.  (With the list: steps of six or eight key tiles instead of four at head_dim 64: 12.5, 13.2 where four take 12.1.)
 template <int D>
 int launch_d(const f32_params& p, int32_t batch, hipStream_t stream) {
   constexpr int MQ_MAX = 256 / D;
