@@ -113,7 +113,7 @@ def test_many_items_take_eight_wavefronts(kind, B, hq, hkv, d, batch, n, flags):
 @pytest.mark.parametrize("hq,hkv,eight", [(4, 1, False), (28, 4, True)])      # 2 and 16 half-size items a block
 def test_rows_too_long_to_be_chained(hq, hkv, eight, d):
     # more than 63 entries in a row: one workgroup to an item, of four or eight wavefronts; the window covers everything,
-    # so the result is that of the dense list, which is chained; a padded batch gives the same rows
+    # so the result is that of the dense list (in the larger case its persistent workgroups'); a padded batch gives the same rows
     n, B = 4200, 64
     cus = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
     assert (hkv * half_size_items(B, hq // hkv, 0, n) > cus) == eight
@@ -137,4 +137,25 @@ def test_rows_too_long_to_be_chained(hq, hkv, eight, d):
 # persistent variant, whose workgroups walk through several items.
 @pytest.mark.parametrize("kind,B,hq,hkv,d,batch,n,flags", [(kind, *m[:4], 2 * m[4], *m[5:]) for m in MANY for kind in KINDS[: 3 if m[-1] & pa.DENSE else 5]])
 def test_persistent_workgroups_give_the_same_rows(kind, B, hq, hkv, d, batch, n, flags):
+    test_many_items_take_eight_wavefronts(kind, B, hq, hkv, d, batch, n, flags)
+
+
+# Query blocks of at most four tasks: four wavefronts whatever the number of items, here more of them than two per compute unit,
+# so their persistent variant, against the one-item variant of the one-sequence launches.
+FOUR = [
+    (64, 8, 8, 64, 12, 500, pa.POWER),            # two tasks a block
+    (64, 8, 8, 128, 12, 500, pa.POWER),
+    (64, 4, 2, 64, 40, 500, pa.POWER),            # four; two KV heads, whose items the XCDs share
+    (64, 4, 2, 128, 40, 500, 0),
+    (128, 8, 8, 128, 14, 700, pa.POWER),          # four slices of one head
+    (64, 8, 8, 64, 12, 500, pa.DENSE),
+    (128, 8, 8, 128, 14, 700, pa.DENSE),
+]
+
+
+@pytest.mark.parametrize("kind,B,hq,hkv,d,batch,n,flags", [(kind, *m) for m in FOUR for kind in KINDS[: 3 if m[-1] & pa.DENSE else 5]])
+def test_persistent_workgroups_of_four_wavefronts(kind, B, hq, hkv, d, batch, n, flags):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    a = 0 if kind in ("prompts", "varlen") else 97
+    assert hq // hkv * B // 32 <= 4 and batch * hkv * half_size_items(B, hq // hkv, a, n - a) > 2 * cus
     test_many_items_take_eight_wavefronts(kind, B, hq, hkv, d, batch, n, flags)
