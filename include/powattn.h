@@ -285,7 +285,9 @@ size_t powattn_decode_workspace_bytes(const powattn_pattern* pattern, int32_t ba
  *                  partial results of the workgroups that share a (sequence,
  *                  KV head), each value tagged with a generation number that is
  *                  also kept there and advanced by every call, so that a call
- *                  tells its own partials from whatever the memory held before.
+ *                  tells its own partials from whatever the memory held before,
+ *                  also where a graph replays it and uses the memory otherwise
+ *                  in between.
  *                  Two calls that may run at the same time must not share a
  *                  workspace; there is no other limit on calls in flight.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE_TOO_SMALL, HIP_ERROR.

@@ -802,7 +802,7 @@ int pa_launch_decode_bf16(const pa_decode_args& a) {
   // all splits of a pair are on one XCD: their exchange is quicker, but where the launch fills the chip the loads are slower.
   // us, KV head / split fastest, 32 query heads on 8: batch 1 8.10 / 8.20, 2 8.51 / 8.70, 4 9.06 / 9.11, 8 9.62 / 9.72 (short rows
   // 7.98 / 8.43), 16 12.8 / 12.4; 16 heads on 16 8.38 / 8.52.  With four KV heads the splits of a pair are on several XCDs
-  // either way, and of every XCD's pairs on more: 28 on 4, batch 2 10.62 / 10.29, 4 11.45 / 10.85, 8 12.04 / 11.23.
+  // either way, and the split fastest is quicker: 28 on 4, batch 2 10.62 / 10.29, 4 11.45 / 10.85, 8 12.04 / 11.23 (two: level).
   p.kvh_first = a.hkv % 8 == 0 && 2 * (int64_t)a.batch * a.hkv * a.n_split <= n_cu;
   p.through = 2 * (int64_t)a.batch * a.hkv * a.n_split > n_cu;
   // As many work items as compute units, or more: persistent workgroups that keep bytes in flight across items.
