@@ -89,6 +89,22 @@ def test_slabs_of_32_keys(B, W, S, hq, hkv, n, d):
     run_backward(pa.Pattern(B, W, S), 1, hq, hkv, n, d, seed=n)
 
 
+@pytest.mark.parametrize("B,W,S,hq,hkv,n,d", [
+    (64, 3, 1, 8, 8, 1090, 128),       # two keys in the last block
+    (64, 3, 1, 16, 8, 1090, 64),
+    (128, 2, 1, 8, 8, 1101, 128),
+    (128, 4, 0, 8, 8, 1101, 64),
+    (256, 2, 1, 8, 8, 1100, 64),
+    (256, 2, 0, 8, 8, 1100, 128),
+])
+def test_slabs_of_64_keys_with_two_query_groups(B, W, S, hq, hkv, n, d):
+    """More 32-key slabs than compute units, not more 64-key slabs: those, the queries of a tile dealt to two groups."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    slabs = -(-n // B) * (B // 64) * hkv
+    assert slabs <= cus < 2 * slabs
+    run_backward(pa.Pattern(B, W, S), 1, hq, hkv, n, d, seed=n + B)
+
+
 def test_batch_and_scale():
     run_backward(pa.Pattern(64, 4, 1), 2, 4, 2, 1280, 128, seed=52, scale=0.07)
 
