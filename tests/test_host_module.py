@@ -242,7 +242,7 @@ def test_every_ordinary_call_goes_the_native_way(monkeypatch):
 
 
 @pytest.mark.gpu
-def test_errors_are_those_of_the_python_way():
+def test_errors_are_the_python_ways_own():
     pa.mask_build(PAT, 64)
     q = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16, device="cuda")
     cnt, idx, _ = pa.mask_build(PAT, 64)
